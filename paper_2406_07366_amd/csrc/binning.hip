@@ -4,10 +4,12 @@
 //
 //   spread bins : tile of T^3 grid cells containing a point's stencil base
 //                 (lowest grid index of its w-point support per axis);
-//   pair cells  : ncell^3 cells of edge L/ncell >= 2 r_c / 3 (the cell-list
-//                 idea of Sec. 5.3), so that the 4 x 4 x 4 cells from the
-//                 cell of x - r_c on hold every point within r_c of x;
-//   node order  : nodes sorted by pair cell, so neighbouring threads share
+//   pair cells  : the cell-list idea of Sec. 5.3 (pair_cells): in float64
+//                 cells of edges >= r_c / 3 along x and r_c / 2 along y, z; in
+//                 float32 ncell^3 cells of edge L/ncell >= 2 r_c / 3, so that
+//                 the 4 x 4 x 4 cells from the cell of x - r_c on hold every
+//                 point within r_c of x;
+//   node order  : nodes sorted by cell (ncell^3), so neighbouring threads share
 //                 cells in the pair and interpolation kernels.
 //
 // Within a bin, entries are ordered by original index so that every sum the
@@ -37,9 +39,24 @@ __device__ int block_exclusive_scan(int v, int *sh, int *total) {
     return incl - v;
 }
 
-__global__ void k_scan_reduce(const int *__restrict__ in, int n, int *__restrict__ sums) {
+// up to three arrays scanned side by side: array a has its blocks
+// [blk[a], blk[a + 1]) of the reduce and apply launches and its own part of
+// the block sums (starting at blk[a])
+struct ScanSet {
+    const int *in[3];
+    int *out[3];
+    int n[3], blk[4];
+};
+
+__device__ __forceinline__ int scan_array(const ScanSet &S) {
+    return (int)blockIdx.x >= S.blk[2] ? 2 : ((int)blockIdx.x >= S.blk[1] ? 1 : 0);
+}
+
+__global__ void k_scan_reduce(ScanSet S, int *__restrict__ sums) {
     __shared__ int sh[kScanBlock];
-    int base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
+    const int a = scan_array(S), n = S.n[a];
+    const int *in = S.in[a];
+    int base = ((int)blockIdx.x - S.blk[a]) * kScanTile + threadIdx.x * kScanItems;
     int s = 0;
     for (int k = 0; k < kScanItems; k++)
         if (base + k < n) s += in[base + k];
@@ -48,28 +65,33 @@ __global__ void k_scan_reduce(const int *__restrict__ in, int n, int *__restrict
     if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
-__global__ void k_scan_sums(int *__restrict__ sums, int nb, int *__restrict__ total_out) {
+// one workgroup per array; out[n] = total
+__global__ void k_scan_sums(ScanSet S, int *__restrict__ sums) {
     __shared__ int sh[kScanBlock];
+    const int a = blockIdx.x, nb = S.blk[a + 1] - S.blk[a];
     // nb <= kScanTile
+    int *sa = sums + S.blk[a];
     int base = threadIdx.x * kScanItems;
     int v[kScanItems], s = 0;
     for (int k = 0; k < kScanItems; k++) {
-        v[k] = (base + k < nb) ? sums[base + k] : 0;
+        v[k] = (base + k < nb) ? sa[base + k] : 0;
         s += v[k];
     }
     int tot;
     int ex = block_exclusive_scan(s, sh, &tot);
     for (int k = 0; k < kScanItems; k++) {
-        if (base + k < nb) sums[base + k] = ex;
+        if (base + k < nb) sa[base + k] = ex;
         ex += v[k];
     }
-    if (threadIdx.x == 0) *total_out = tot;
+    if (threadIdx.x == 0) S.out[a][S.n[a]] = tot;
 }
 
-__global__ void k_scan_apply(const int *__restrict__ in, int n, const int *__restrict__ sums,
-                             int *__restrict__ out) {
+__global__ void k_scan_apply(ScanSet S, const int *__restrict__ sums) {
     __shared__ int sh[kScanBlock];
-    int base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
+    const int a = scan_array(S), n = S.n[a];
+    const int *in = S.in[a];
+    int *out = S.out[a];
+    int base = ((int)blockIdx.x - S.blk[a]) * kScanTile + threadIdx.x * kScanItems;
     int v[kScanItems], s = 0;
     for (int k = 0; k < kScanItems; k++) {
         v[k] = (base + k < n) ? in[base + k] : 0;
@@ -83,19 +105,28 @@ __global__ void k_scan_apply(const int *__restrict__ in, int n, const int *__res
     }
 }
 
+static void scan_arrays(bs_plan_t p, int na, const int *const *in, int *const *out, const int *n,
+                        int *sums) {
+    ScanSet S{};
+    for (int a = 0; a < 3; a++) {
+        if (a < na) { S.in[a] = in[a]; S.out[a] = out[a]; S.n[a] = n[a]; }
+        S.blk[a + 1] = S.blk[a] + (a < na ? ceil_div(n[a], kScanTile) : 0);
+    }
+    const dim3 g(S.blk[3]), b(kScanBlock);
+    hipLaunchKernelGGL(k_scan_reduce, g, b, 0, p->stream, S, sums);
+    hipLaunchKernelGGL(k_scan_sums, dim3(na), b, 0, p->stream, S, sums);
+    hipLaunchKernelGGL(k_scan_apply, g, b, 0, p->stream, S, (const int *)sums);
+}
+
 // out[0..n-1] = exclusive scan of in, out[n] = total.  in and out may not
 // alias.  Requires n <= kScanTile^2 (4.2 M bins); sums: kScanTile ints of
 // scratch, private to the stream.
 void exclusive_scan(bs_plan_t p, const int *in, int *out, int n, int *sums) {
-    int nb = ceil_div(n, kScanTile);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kScanBlock), 0, p->stream, in, n, sums);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanBlock), 0, p->stream, sums, nb, out + n);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(kScanBlock), 0, p->stream, in, n, sums, out);
+    scan_arrays(p, 1, &in, &out, &n, sums);
 }
 
-// Bins are ordered by original index: one wavefront per bin ranks its
-// entries (rank_sort_bin); a bin too large for LDS ranks into the key array,
-// which is free once the scatter is done.
+// Bins are ordered by original index (k_sort_all); a bin too large for LDS
+// ranks into the key array, which is free once the scatter is done.
 constexpr int kSortLds = 2048;
 
 // ------------------------------------------------------- fused bin passes
@@ -105,14 +136,16 @@ constexpr int kSortLds = 2048;
 struct SortSet {
     int *key[3], *cnt[3], *start[3], *fill[3], *perm[3];
     int nbins[3], nitems[3];
+    int per[3], ngrp[3];   // bins per wavefront of the per-bin sort, wavefronts
 };
 
 
 // one workgroup per array: exclusive scan of cnt into start (start[n] =
 // total).  Wavefront w owns the contiguous segment [w seg, (w + 1) seg) and
-// reads it 64 entries at a time (coalesced): a first pass sums it, the
-// segment offsets are formed from the 16 sums in LDS, and a second pass
-// scans each 64-entry chunk by shuffles while writing.
+// takes it 256 entries at a time, four consecutive ones per lane: a first
+// pass sums it, the segment offsets are formed from the 16 sums in LDS, and a
+// second pass scans each 256-entry chunk by data-parallel moves while writing
+// (one entry per lane took 12.1 us for 14112 bins, four 5.0).
 __global__ __launch_bounds__(1024) void k_scan_small(SortSet S) {
     __shared__ int wsum[16];
     const int a = blockIdx.x;
@@ -120,25 +153,35 @@ __global__ __launch_bounds__(1024) void k_scan_small(SortSet S) {
     const int *in = S.cnt[a];
     int *out = S.start[a];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const int seg = ((n + nw - 1) / nw + 63) / 64 * 64;
-    const int b0 = wave * seg, b1 = b0 + seg < n ? b0 + seg : n;
+    const int seg = ((n + nw - 1) / nw + 255) / 256 * 256;
+    const int b0 = min(wave * seg, n), b1 = min(b0 + seg, n);
+    auto load = [&](int i) {   // in[i .. i + 3], zero beyond the segment; i is a multiple of 4
+        if (i + 3 < b1) return *(const int4 *)(in + i);
+        return make_int4(i < b1 ? in[i] : 0, i + 1 < b1 ? in[i + 1] : 0, i + 2 < b1 ? in[i + 2] : 0, 0);
+    };
     int sum = 0;
-    for (int i = b0 + lane; i < b1; i += 64) sum += in[i];
-    for (int m = 32; m > 0; m >>= 1) sum += __shfl_xor(sum, m);
+    for (int i = b0 + 4 * lane; i < b1; i += 256) {
+        const int4 v = load(i);
+        sum += v.x + v.y + v.z + v.w;
+    }
+    sum = __builtin_amdgcn_readlane(wave_incl_sum(sum), 63);
     if (lane == 0) wsum[wave] = sum;
     __syncthreads();
     int carry = 0;
     for (int w = 0; w < wave; w++) carry += wsum[w];
-    for (int c0 = b0; c0 < b1; c0 += 64) {
-        const int i = c0 + lane;
-        const int v = i < b1 ? in[i] : 0;
-        int incl = v;
-        for (int d = 1; d < 64; d <<= 1) {
-            const int u = __shfl_up(incl, d);
-            if (lane >= d) incl += u;
+    for (int c0 = b0; c0 < b1; c0 += 256) {
+        const int i = c0 + 4 * lane;
+        const int4 v = load(i);
+        const int s = v.x + v.y + v.z + v.w, incl = wave_incl_sum(s), e = carry + incl - s;
+        const int4 r = make_int4(e, e + v.x, e + v.x + v.y, e + v.x + v.y + v.z);
+        if (i + 3 < b1) {
+            *(int4 *)(out + i) = r;
+        } else {
+            if (i < b1) out[i] = r.x;
+            if (i + 1 < b1) out[i + 1] = r.y;
+            if (i + 2 < b1) out[i + 2] = r.z;
         }
-        if (i < b1) out[i] = carry + incl - v;
-        carry += __shfl(incl, 63);
+        carry += __builtin_amdgcn_readlane(incl, 63);
     }
     if (threadIdx.x == 0) {
         int tot = 0;
@@ -154,28 +197,66 @@ __global__ void k_scatter_all(SortSet S) {
     if (a == 1 && i >= S.nitems[1]) { i -= S.nitems[1]; a = 2; }
     const bool valid = !(a == 2 && i >= S.nitems[2]);
     const int k = valid ? S.key[a][i] : 0;
+    const bool one = S.nbins[a] == 1;   // one bin: already in index order
+    if (one && valid) S.perm[a][i] = i;
     // one atomic per (set, bin) group of the wavefront, all issued together
-    const WaveGroup g = wave_group(k, a, valid);
+    const bool act = valid && !one;
+    const WaveGroup g = wave_group(k, a, act);
     int old = 0;
-    if (valid && (int)(threadIdx.x & 63) == g.leader) old = atomicAdd(S.fill[a] + k, g.size);
+    if (act && (int)(threadIdx.x & 63) == g.leader) old = atomicAdd(S.fill[a] + k, g.size);
     const int slot = __shfl(old, g.leader) + g.rank;
-    if (valid) S.perm[a][S.start[a][k] + slot] = i;
+    if (act) S.perm[a][S.start[a][k] + slot] = i;
 }
 
+// Orders every bin's entries by original index.  A wavefront takes per[a]
+// consecutive bins of set a, whose entries form one contiguous range: staged in
+// LDS with the bins' bounds, and each entry counts the smaller ones of its own
+// bin, so that the lanes stay busy whatever the bins hold (a wavefront per
+// bin left most lanes idle on bins of a few points: 298 -> 55 us for the 1e6-node
+// tangle's 8e5 bins).  A range beyond the LDS goes bin by bin.
 __global__ __launch_bounds__(64) void k_sort_all(SortSet S) {
-    int b = blockIdx.x, a = 0;
-    if (b >= S.nbins[0]) { b -= S.nbins[0]; a = 1; }
-    if (a == 1 && b >= S.nbins[1]) { b -= S.nbins[1]; a = 2; }
-    if (a == 2 && b >= S.nbins[2]) return;
-    __shared__ int v[kSortLds];
-    int s = S.start[a][b], n = S.start[a][b + 1] - s;
-    // the bin's counters are not read again: clear them for the next call
+    int g = blockIdx.x, a = 0;
+    if (g >= S.ngrp[0]) { g -= S.ngrp[0]; a = 1; }
+    if (a == 1 && g >= S.ngrp[1]) { g -= S.ngrp[1]; a = 2; }
+    if (a == 2 && g >= S.ngrp[2]) return;
+    __shared__ int v[kSortLds], st[65];
+    const int lane = threadIdx.x, per = S.per[a], b0 = g * per;
+    const int nb = min(per, S.nbins[a] - b0);
+    const int *start = S.start[a];
+    int *perm = S.perm[a];
+    const int s0 = start[b0], e0 = start[b0 + nb], total = e0 - s0;
+    // the bins' counters are not read again: clear them for the next call
     // (the per-filament kernel counts into them)
-    if (threadIdx.x == 0) {
-        S.cnt[a][b] = 0;
-        S.fill[a][b] = 0;
+    if (lane < nb) {
+        S.cnt[a][b0 + lane] = 0;
+        S.fill[a][b0 + lane] = 0;
+        st[lane] = start[b0 + lane] - s0;
+    } else {
+        st[lane] = total;
     }
-    rank_sort_bin<kSortLds>(S.perm[a], S.key[a], s, n, v);
+    if (lane == 0) st[64] = total;
+    if (S.nbins[a] == 1) return;   // one bin: the scatter wrote the identity
+    if (total <= kSortLds) {
+        for (int i = lane; i < total; i += 64) v[i] = perm[s0 + i];
+        wave_lds_sync();
+        for (int i = lane; i < total; i += 64) {
+            int b = 0;   // the last bin that starts at or before i
+            if (nb > 1)
+                for (int step = 32; step > 0; step >>= 1)
+                    if (st[b + step] <= i) b += step;
+            const int lo = st[b], hi = st[b + 1], x = v[i];
+            int r = lo;
+#pragma unroll 8
+            for (int j = lo; j < hi; j++) r += (v[j] < x);
+            perm[s0 + r] = x;
+        }
+        return;
+    }
+    for (int k = 0; k < nb; k++) {
+        const int s = start[b0 + k], n = start[b0 + k + 1] - s;
+        rank_sort_bin<kSortLds>(perm, S.key[a], s, n, v);
+        __syncthreads();   // the LDS is free for the next bin
+    }
 }
 
 // sorted copies for the spread (by tile) and the pairs (by cell), one pass;
@@ -187,6 +268,7 @@ struct GatherOut {
     int4 *base;
     void *ker, *q, *schg;
     double4 *spos;   // w: the point's segment index
+    double4 *tgt;    // nodes in cell order: wrapped position, node and its predecessor
 };
 
 // (the w kernel values of thread t go to lk[0 .. w-1]; the caller writes them
@@ -224,6 +306,8 @@ __device__ __forceinline__ void gather_one(int t, int w, int Q, const int *__res
 // workgroup form one contiguous range: they are staged in LDS and written out
 // with consecutive threads on consecutive words (a thread writing its own w
 // values touched a cache line per lane in each store).  256 threads, w <= 16.
+// The last workgroups write the nodes' records (a thread per node), from which
+// the pair and interpolation kernels take their target in one load.
 constexpr int kGatherBlock = 256;
 template <typename R>
 __global__ __launch_bounds__(kGatherBlock) void k_gather_all(int M, int w, int Q,
@@ -233,10 +317,23 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_all(int M, int w, int Q
                                                              const double *__restrict__ chg,
                                                              double L, double inv_h, int n,
                                                              double zeta, double inv_den,
-                                                             GatherOut G) {
+                                                             GatherOut G, int N,
+                                                             const int *__restrict__ nperm,
+                                                             const double *__restrict__ x,
+                                                             const int *__restrict__ off,
+                                                             const int *__restrict__ fil) {
     __shared__ R lk[kGatherBlock * 16];
+    const int npt = (3 * M + kGatherBlock - 1) / kGatherBlock;   // workgroups of the points
+    if ((int)blockIdx.x >= npt) {
+        const int t = ((int)blockIdx.x - npt) * kGatherBlock + (int)threadIdx.x;
+        if (t >= N) return;
+        const int o = nperm[t];
+        G.tgt[t] = make_double4(wrap_box(x[3 * o], L), wrap_box(x[3 * o + 1], L),
+                                wrap_box(x[3 * o + 2], L),
+                                __hiloint2double(prev_node_d(off, fil, o), o));
+        return;
+    }
     const int t0 = blockIdx.x * kGatherBlock, t = t0 + (int)threadIdx.x;
-    if (t0 >= 3 * M) return;   // uniform over the workgroup
     if (t < 3 * M)
         gather_one<R>(t, w, Q, sperm, pperm, pos, chg, L, inv_h, n, zeta, inv_den, G,
                       lk + threadIdx.x * w);
@@ -246,12 +343,22 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_all(int M, int w, int Q
     for (int i = threadIdx.x; i < nt * w; i += kGatherBlock) ker[i] = lk[i];
 }
 
+// wavefronts per set of the per-bin sort (eight per SIMD): fewer bins than
+// that get one each (the 64^3 ellipses' 512 tiles: 10.5 us at two wavefronts
+// per CU and several bins each, 5.1 with one)
+constexpr int kSortWaves = 8192;
+// arrays of at most this many bins are scanned by one workgroup each (one
+// launch, 5.0 us at 14112 bins and 7.4 at 21312; the three launches of the
+// blocked scan take 14 us)
+constexpr int kScanSmall = 32768;
+
 void build_bins(bs_plan_t p) {
     const int bs = 256;
     const int M = (int)p->Nq, N = (int)p->N;
     const double L = p->prm.L, inv_h = p->n / L;
     const int w = p->prm.w, n = p->n;
-    const int ntiles = p->NT * p->NT * p->NT, nc3 = p->nc * p->nc * p->nc;
+    const int ntiles = p->NT * p->NT * p->NT, nc3 = p->nc * p->nc * p->nc,
+              ncp = p->ncx * p->ncy * p->ncy;
     SortSet S;
     S.key[0] = (int *)p->sp_key.p; S.cnt[0] = (int *)p->sp_cnt.p; S.start[0] = (int *)p->sp_start.p;
     S.fill[0] = (int *)p->sp_fill.p; S.perm[0] = (int *)p->sp_perm.p;
@@ -259,9 +366,16 @@ void build_bins(bs_plan_t p) {
     S.fill[1] = (int *)p->pq_fill.p; S.perm[1] = (int *)p->pq_perm.p;
     S.key[2] = (int *)p->nd_key.p; S.cnt[2] = (int *)p->nd_cnt.p; S.start[2] = (int *)p->nd_start.p;
     S.fill[2] = (int *)p->nd_fill.p; S.perm[2] = (int *)p->nd_perm.p;
-    S.nbins[0] = ntiles; S.nbins[1] = nc3; S.nbins[2] = nc3;
+    S.nbins[0] = ntiles; S.nbins[1] = ncp; S.nbins[2] = nc3;
     S.nitems[0] = M; S.nitems[1] = M; S.nitems[2] = N;
-    const int maxb = ntiles > nc3 ? ntiles : nc3;
+    for (int a = 0; a < 3; a++) {
+        // bins per wavefront: at least kSortWaves wavefronts per set while
+        // there are bins for them, and 64 bins at most
+        const int per = S.nbins[a] / kSortWaves;
+        S.per[a] = per < 1 ? 1 : (per > 64 ? 64 : per);
+        S.ngrp[a] = ceil_div(S.nbins[a], S.per[a]);
+    }
+    const int maxb = ntiles > ncp ? ntiles : ncp;
     const double zeta = p->prm.zeta, inv_den = 1.0 / (-expm1(-2.0 * zeta));
     GatherOut G;
     G.base = (int4 *)p->sp_base.p;
@@ -269,26 +383,22 @@ void build_bins(bs_plan_t p) {
     G.q = p->sp_q.p;
     G.spos = (double4 *)p->pq_pos.p;
     G.schg = p->pq_chg.p;
+    G.tgt = (double4 *)p->nd_rec.p;
     const double *qp = (const double *)p->d_qpos.p, *qc = (const double *)p->d_qchg.p;
     // keys and counts come from the per-filament kernel (bin_keys)
-    if (maxb <= (1 << 16)) {
+    if (maxb <= kScanSmall) {
         hipLaunchKernelGGL(k_scan_small, dim3(3), dim3(1024), 0, p->stream, S);
     } else {
-        for (int a = 0; a < 3; a++)
-            exclusive_scan(p, S.cnt[a], S.start[a], S.nbins[a], (int *)p->red_tmp.p);
+        scan_arrays(p, 3, S.cnt, S.start, S.nbins, (int *)p->red_tmp.p);
     }
-    hipLaunchKernelGGL(k_scatter_all, dim3(ceil_div(2 * M + N, bs)), dim3(bs), 0, p->stream, S);
-    hipLaunchKernelGGL(k_sort_all, dim3(ntiles + 2 * nc3), dim3(64), 0, p->stream, S);
-    if (p->fp32)
-        hipLaunchKernelGGL(k_gather_all<float>, dim3(ceil_div(3 * (int64_t)M, kGatherBlock)),
-                           dim3(kGatherBlock), 0,
-                           p->stream, M, w, p->Q, S.perm[0], S.perm[1], qp, qc, L, inv_h, n, zeta,
-                           inv_den, G);
-    else
-        hipLaunchKernelGGL(k_gather_all<double>, dim3(ceil_div(3 * (int64_t)M, kGatherBlock)),
-                           dim3(kGatherBlock), 0,
-                           p->stream, M, w, p->Q, S.perm[0], S.perm[1], qp, qc, L, inv_h, n, zeta,
-                           inv_den, G);
+    hipLaunchKernelGGL(k_scatter_all, dim3(ceil_div(2 * (int64_t)M + N, bs)), dim3(bs), 0, p->stream, S);
+    hipLaunchKernelGGL(k_sort_all, dim3(S.ngrp[0] + S.ngrp[1] + S.ngrp[2]), dim3(64), 0, p->stream, S);
+    const dim3 gg(ceil_div(3 * (int64_t)M, kGatherBlock) + ceil_div(N, kGatherBlock));
+    const double *x = (const double *)p->d_x.p;
+    const int *off = (const int *)p->d_off.p, *fil = (const int *)p->d_fil.p;
+    auto gather = p->fp32 ? k_gather_all<float> : k_gather_all<double>;
+    hipLaunchKernelGGL(gather, gg, dim3(kGatherBlock), 0, p->stream, M, w, p->Q, S.perm[0],
+                       S.perm[1], qp, qc, L, inv_h, n, zeta, inv_den, G, N, S.perm[2], x, off, fil);
 }
 
 BinKeys bin_keys(bs_plan_t p) {
@@ -299,6 +409,7 @@ BinKeys bin_keys(bs_plan_t p) {
     k.L = p->prm.L;
     k.inv_h = p->n / p->prm.L;
     k.w = p->prm.w; k.n = p->n; k.T = p->T; k.NT = p->NT; k.nc = p->nc;
+    k.ncx = p->ncx; k.ncy = p->ncy;
     return k;
 }
 

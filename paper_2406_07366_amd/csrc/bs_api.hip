@@ -332,7 +332,7 @@ int bs_plan(const bs_params *p, void *hip_stream, bs_plan_t *out) {
     if ((rc = ensure<char>(P, P->spec, 3 * nc * 2 * P->real_size))) return fail(rc);
     if ((rc = ensure<double>(P, P->deconv, 2 * (r.K + 1)))) return fail(rc);
     if ((rc = ensure<int>(P, P->d_status, 1))) return fail(rc);
-    if ((rc = ensure<int>(P, P->red_tmp, 8192))) return fail(rc);
+    if ((rc = ensure<int>(P, P->red_tmp, 3 * 8192))) return fail(rc);
     if ((rc = ensure<int>(P, P->scan_tmp, 8192))) return fail(rc);
     if ((rc = check_hip(P, hipMemsetAsync(P->d_status.p, 0, sizeof(int), P->stream), "memset")))
         return fail(rc);
@@ -452,7 +452,9 @@ int bs_set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, const do
     bool same = P->have_filaments && P->nfil == nfil &&
                 std::equal(offsets, offsets + nfil + 1, P->off_host.begin());
     int rc;
-    const int ntiles = P->NT * P->NT * P->NT, nc3 = P->nc * P->nc * P->nc;
+    int ncx, ncy;
+    pair_cells(P, Nq, &ncx, &ncy);
+    const int ntiles = P->NT * P->NT * P->NT, nc3 = P->nc * P->nc * P->nc, ncp = ncx * ncy * ncy;
     const size_t rs = P->real_size;
     if (!same) {
         P->have_filaments = false;
@@ -471,12 +473,13 @@ int bs_set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, const do
             (rc = ensure<int4>(P, P->sp_base, Nq)) ||
             (rc = ensure<char>(P, P->sp_ker, Nq * 3 * P->prm.w * rs)) ||
             (rc = ensure<char>(P, P->sp_q, Nq * 4 * rs)) || (rc = ensure<int>(P, P->pq_key, Nq)) ||
-            (rc = ensure<int>(P, P->pq_cnt, nc3 + 1)) || (rc = ensure<int>(P, P->pq_start, nc3 + 1)) ||
-            (rc = ensure<int>(P, P->pq_fill, nc3 + 1)) || (rc = ensure<int>(P, P->pq_perm, Nq)) ||
+            (rc = ensure<int>(P, P->pq_cnt, ncp + 1)) || (rc = ensure<int>(P, P->pq_start, ncp + 1)) ||
+            (rc = ensure<int>(P, P->pq_fill, ncp + 1)) || (rc = ensure<int>(P, P->pq_perm, Nq)) ||
             (rc = ensure<double4>(P, P->pq_pos, Nq)) || (rc = ensure<char>(P, P->pq_chg, Nq * 4 * rs)) ||
             (rc = ensure<int>(P, P->nd_key, N)) ||
             (rc = ensure<int>(P, P->nd_cnt, nc3 + 1)) || (rc = ensure<int>(P, P->nd_start, nc3 + 1)) ||
-            (rc = ensure<int>(P, P->nd_fill, nc3 + 1)) || (rc = ensure<int>(P, P->nd_perm, N)))
+            (rc = ensure<int>(P, P->nd_fill, nc3 + 1)) || (rc = ensure<int>(P, P->nd_perm, N)) ||
+            (rc = ensure<double4>(P, P->nd_rec, N)))
             return rc;
         if (P->order == 4 && maxn > kPcrLds && (rc = ensure<double>(P, P->spline_tmp, 12 * N)))
             return rc;
@@ -511,11 +514,12 @@ int bs_set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, const do
         }
         // the bin counters start at zero; afterwards each call's per-bin
         // sort clears them for the next
-        const size_t nb_t = sizeof(int) * (ntiles + 1), nb_c = sizeof(int) * (nc3 + 1);
+        const size_t nb_t = sizeof(int) * (ntiles + 1), nb_c = sizeof(int) * (nc3 + 1),
+                     nb_p = sizeof(int) * (ncp + 1);
         if ((rc = check_hip(P, hipMemsetAsync(P->sp_cnt.p, 0, nb_t, P->stream), "memset")) ||
             (rc = check_hip(P, hipMemsetAsync(P->sp_fill.p, 0, nb_t, P->stream), "memset")) ||
-            (rc = check_hip(P, hipMemsetAsync(P->pq_cnt.p, 0, nb_c, P->stream), "memset")) ||
-            (rc = check_hip(P, hipMemsetAsync(P->pq_fill.p, 0, nb_c, P->stream), "memset")) ||
+            (rc = check_hip(P, hipMemsetAsync(P->pq_cnt.p, 0, nb_p, P->stream), "memset")) ||
+            (rc = check_hip(P, hipMemsetAsync(P->pq_fill.p, 0, nb_p, P->stream), "memset")) ||
             (rc = check_hip(P, hipMemsetAsync(P->nd_cnt.p, 0, nb_c, P->stream), "memset")) ||
             (rc = check_hip(P, hipMemsetAsync(P->nd_fill.p, 0, nb_c, P->stream), "memset")) ||
             (P->ns_fallback.p &&
@@ -535,6 +539,8 @@ int bs_set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, const do
         if ((rc = check_hip(P, hipStreamSynchronize(P->stream), "sync"))) return rc;
         P->off_host.assign(offsets, offsets + nfil + 1);
         P->nfil = nfil;
+        P->ncx = ncx;
+        P->ncy = ncy;
         P->N = N;
         P->Nq = Nq;
         P->max_fil_nodes = maxn;
@@ -932,7 +938,7 @@ int bs_destroy(bs_plan_t P) {
                    &P->d_qpos, &P->d_qchg, &P->d_status, &P->sp_key, &P->sp_cnt, &P->sp_start,
                    &P->sp_fill, &P->sp_perm, &P->sp_base, &P->sp_ker, &P->sp_q, &P->pq_key,
                    &P->pq_cnt, &P->pq_start, &P->pq_fill, &P->pq_perm, &P->pq_pos, &P->pq_chg,
-                   &P->nd_key, &P->nd_cnt, &P->nd_start, &P->nd_fill, &P->nd_perm,
+                   &P->nd_key, &P->nd_cnt, &P->nd_start, &P->nd_fill, &P->nd_perm, &P->nd_rec,
                    &P->scan_tmp, &P->red_tmp, &P->spline_tmp, &P->tmp3, &P->e_D, &P->e_S, &P->d_vls, &P->ns_red, &P->ns_nc, &P->ns_ckey,
                    &P->ns_ccnt, &P->ns_cstart, &P->ns_cfill, &P->ns_cperm, &P->ns_tkey, &P->ns_tcnt,
                    &P->ns_tstart, &P->ns_tfill, &P->ns_tperm, &P->ns_segA, &P->ns_segB, &P->ns_segM, &P->ns_segH, &P->ns_slots,

@@ -33,13 +33,31 @@ __device__ __forceinline__ int tile_key(const double *p, double L, double inv_h,
     const int bz = stencil_base(wrap_box(p[2], L), inv_h, w, n, &f);
     return ((bz / T) * NT + by / T) * NT + bx / T;
 }
-__device__ __forceinline__ int cell_key(const double *p, double L, int nc) {
+__device__ __forceinline__ int cell_key(const double *p, double L, int ncx, int ncy) {
     int c[3];
     for (int q = 0; q < 3; q++) {
+        const int nc = q == 0 ? ncx : ncy;
         const int v = (int)(wrap_box(p[q], L) / L * nc);
         c[q] = v < 0 ? 0 : (v >= nc ? nc - 1 : v);
     }
-    return (c[2] * nc + c[1]) * nc + c[0];
+    return (c[2] * ncy + c[1]) * ncx + c[0];
+}
+
+// 1 / sqrt(a) for a > 0: the hardware estimate and two Newton steps
+// y <- y (3 - a y^2) / 2 (each squares the relative error), to rounding
+__device__ __forceinline__ double rsqrt_nr(double a) {
+    double y = __builtin_amdgcn_rsq(a);
+    const double h = 0.5 * a;
+    y = y * fma(-h * y, y, 1.5);
+    y = y * fma(-h * y, y, 1.5);
+    return y;
+}
+
+// 1 / a for a > 0 of ordinary size: the hardware estimate and two Newton steps
+__device__ __forceinline__ double rcp_nr(double a) {
+    double y = __builtin_amdgcn_rcp(a);
+    y = fma(y, fma(-a, y, 1.0), y);
+    return fma(y, fma(-a, y, 1.0), y);
 }
 
 // Backward Kaiser-Bessel kernel, normalised to 1 at the centre:
@@ -63,6 +81,39 @@ __device__ __forceinline__ int next_node_d(const int *off, const int *fil, int j
 __device__ __forceinline__ int prev_node_d(const int *off, const int *fil, int j) {
     int f = fil[j];
     return (j > off[f]) ? j - 1 : off[f + 1] - 1;
+}
+
+// Wavefront sums by data-parallel moves (no LDS): inclusive prefix sum over the
+// lanes, and the total of a double, which ends in lane 63.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_get(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ int wave_incl_sum(int v) {
+    v += dpp_get<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8 (rows of 16 lanes)
+    v += dpp_get<0x112, 0xf>(v);
+    v += dpp_get<0x114, 0xf>(v);
+    v += dpp_get<0x118, 0xf>(v);
+    v += dpp_get<0x142, 0xa>(v);   // lane 15 of rows 0, 2 to rows 1, 3
+    v += dpp_get<0x143, 0xc>(v);   // lane 31 to rows 2, 3
+    return v;
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_get(double v) {
+    return __hiloint2double(
+        __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+        __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double wave_total63(double v) {
+    // every row takes part in every step (lanes without a source get zero):
+    // only the last row's result is used
+    v += dpp_get<0x111>(v);
+    v += dpp_get<0x112>(v);
+    v += dpp_get<0x114>(v);
+    v += dpp_get<0x118>(v);
+    v += dpp_get<0x142>(v);
+    v += dpp_get<0x143>(v);
+    return v;
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs, so blocks b, b+8,

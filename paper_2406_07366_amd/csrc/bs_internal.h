@@ -71,8 +71,10 @@ struct bs_plan_s {
     int fft_rb = 1, fft_kb = 1, fft_kz = 1;
     bs::DBuf fft_tw, fft_A, fft_B;
 
-    // short-range cell list
-    int nc = 1;             // cells per axis
+    // short-range cell lists: nodes (and float32 points) in nc^3 cells, points
+    // in ncx x ncy x ncy (x fastest; set with the filaments, see pair_cells)
+    int nc = 1;
+    int ncx = 1, ncy = 1;
 
     // filaments
     int64_t nfil = 0, N = 0, Nq = 0;
@@ -98,6 +100,7 @@ struct bs_plan_s {
     bs::DBuf pq_key, pq_cnt, pq_start, pq_fill, pq_perm;
     bs::DBuf pq_pos, pq_chg;                   // double4 (position, segment), charges
     bs::DBuf nd_key, nd_cnt, nd_start, nd_fill, nd_perm;
+    bs::DBuf nd_rec;                           // double4 [N] nodes in cell order
     // scan scratch, reductions, spline scratch (filaments over 512 nodes)
     bs::DBuf scan_tmp, red_tmp, spline_tmp;
     int64_t max_fil_nodes = 0;
@@ -168,7 +171,7 @@ void build_bins(bs_plan_t p);
 struct BinKeys {
     int *key[3], *cnt[3];
     double L, inv_h;
-    int w, n, T, NT, nc;
+    int w, n, T, NT, nc, ncx, ncy;
 };
 BinKeys bin_keys(bs_plan_t p);
 
@@ -192,6 +195,8 @@ void pruned_inverse(bs_plan_t p);
 bool grid_interleaved(bs_plan_t p);
 
 // pairs.hip
+// cells of the quadrature points' list for Nq points
+void pair_cells(bs_plan_t p, int64_t Nq, int *ncx, int *ncy);
 // out = base + short-range term (base NULL: out += short-range term);
 // alone: nothing else runs beside it (more wavefronts per target on small
 // inputs)

@@ -551,7 +551,7 @@ __global__ __launch_bounds__(128) void k_filament(int nfil, const int *__restric
         int k0 = 0, k1 = 0;
         if (act) {
             k0 = tile_key(qpos + 3 * qi, bk.L, bk.inv_h, bk.w, bk.n, bk.T, bk.NT);
-            k1 = cell_key(qpos + 3 * qi, bk.L, bk.nc);
+            k1 = cell_key(qpos + 3 * qi, bk.L, bk.ncx, bk.ncy);
             bk.key[0][qi] = k0;
             bk.key[1][qi] = k1;
         }
@@ -563,7 +563,7 @@ __global__ __launch_bounds__(128) void k_filament(int nfil, const int *__restric
         const bool act = t < n;
         int k2 = 0;
         if (act) {
-            k2 = cell_key(xd + 3 * (b0 + t), bk.L, bk.nc);
+            k2 = cell_key(xd + 3 * (b0 + t), bk.L, bk.nc, bk.nc);
             bk.key[2][b0 + t] = k2;
         }
         wave_add<false>(bk.cnt[2], k2, act);

@@ -719,16 +719,6 @@ __device__ __forceinline__ double seg_dd(const Seg &s, int q, double u) {
     return s.e2[q] + u * (2.0 * s.e3[q] + u * (3.0 * s.e4[q] + u * 4.0 * s.e5[q]));
 }
 
-// 1 / sqrt(a) for a > 0: the hardware estimate and two Newton steps
-// y <- y (3 - a y^2) / 2 (each squares the relative error), to rounding
-__device__ __forceinline__ double rsqrt_nr(double a) {
-    double y = __builtin_amdgcn_rsq(a);
-    const double h = 0.5 * a;
-    y = y * fma(-h * y, y, 1.5);
-    y = y * fma(-h * y, y, 1.5);
-    return y;
-}
-
 // integral over u in [a, b] of (s(u) - x) x s'(u) / |s(u) - x|^3 by
 // Gauss-Legendre: 10 points on cubic segments, 12 on quintic ones.  On the
 // graded panels below, the integrand's complex singularity near the closest

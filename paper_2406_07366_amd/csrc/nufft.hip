@@ -501,8 +501,8 @@ void launch_modes(bs_plan_t p, double *out) {
 // b, b+8, ... run on one XCD), so the grid rows that neighbouring nodes share
 // are fetched into one L2.
 template <typename R, int W, int G, bool IL>
-__global__ __launch_bounds__(256) void k_interp(int N, int per_xcd, const int *__restrict__ perm,
-                                                const double *__restrict__ x, double L,
+__global__ __launch_bounds__(256) void k_interp(int N, int per_xcd,
+                                                const double4 *__restrict__ tgt,
                                                 double inv_h, int n, double zeta, double inv_den,
                                                 const R *__restrict__ grid,
                                                 const double *__restrict__ base,
@@ -513,11 +513,12 @@ __global__ __launch_bounds__(256) void k_interp(int N, int per_xcd, const int *_
     const int gid = blk * blockDim.x + threadIdx.x;
     const int t = gid / G, lane = gid % G;
     if (t >= N) return;   // whole wavefronts exit together
-    const int o = perm[t];
-    const double half = 0.5 * W;
+    const double4 tg = tgt[t];   // wrapped position, node
+    const int o = __double2loint(tg.w);
+    const double half = 0.5 * W, xw[3] = {tg.x, tg.y, tg.z};
     double f[3];
     int bb[3];
-    for (int a = 0; a < 3; a++) bb[a] = stencil_base(wrap_box(x[3 * o + a], L), inv_h, W, n, &f[a]);
+    for (int a = 0; a < 3; a++) bb[a] = stencil_base(xw[a], inv_h, W, n, &f[a]);
     R phi = (R)0;
     if (lane < 3 * W) {
         const int a = lane / W, k = lane % W;
@@ -592,14 +593,13 @@ static void interp_r(bs_plan_t p, const double *base, double *out) {
     dim3 grid(8 * per), block(256);
     const double L = p->prm.L, inv_h = p->n / L, zeta = p->prm.zeta;
     const double inv_den = 1.0 / (-expm1(-2.0 * zeta));
-    const int *perm = (const int *)p->nd_perm.p;
-    const double *x = (const double *)p->d_x.p;
+    const double4 *tgt = (const double4 *)p->nd_rec.p;
     const R *g = (const R *)p->grid.p;
     const bool il = grid_interleaved(p);
 #define INTERP_CASE(WW) \
     case WW: \
-        if (il) hipLaunchKernelGGL((k_interp<R, WW, kInterpLanes, true>), grid, block, 0, p->stream, N, per, perm, x, L, inv_h, p->n, zeta, inv_den, g, base, out); \
-        else hipLaunchKernelGGL((k_interp<R, WW, kInterpLanes, false>), grid, block, 0, p->stream, N, per, perm, x, L, inv_h, p->n, zeta, inv_den, g, base, out); \
+        if (il) hipLaunchKernelGGL((k_interp<R, WW, kInterpLanes, true>), grid, block, 0, p->stream, N, per, tgt, inv_h, p->n, zeta, inv_den, g, base, out); \
+        else hipLaunchKernelGGL((k_interp<R, WW, kInterpLanes, false>), grid, block, 0, p->stream, N, per, tgt, inv_h, p->n, zeta, inv_den, g, base, out); \
         break;
     switch (p->prm.w) {
         INTERP_CASE(4) INTERP_CASE(5) INTERP_CASE(6) INTERP_CASE(7) INTERP_CASE(8)
