@@ -361,8 +361,17 @@ int bs_plan(const bs_params *p, void *hip_stream, bs_plan_t *out) {
         hipfftSetStream(P->fft_inv, P->stream) != HIPFFT_SUCCESS)
         return fail(set_error(P, BS_EDEVICE, "hipfftSetStream failed"));
     // pruned transforms: twiddles exp(-+2 pi i k / n), k < n/2, from float64
-    P->pruned = r.fft_mode == BS_FFT_PRUNED;   // resolved: never BS_FFT_AUTO here
+    // BS_FFT_AUTO resolves to BS_FFT_LIBRARY on grids that are no power of two
+    // (BS_FFT_PRUNED refuses them) and below 64; in float64 the plan still runs
+    // its own transforms there where it has them: hipFFT's form all modes
+    // and need a pass of the spectral operator (384^3: 5.69 ms against 1.91;
+    // 160^3: 280 us, 162; 32^3: 20.5, 15).  In
+    // float32 their rounding would change results, so those stay on hipFFT, as
+    // does an explicit BS_FFT_LIBRARY.
+    P->pruned = r.fft_mode == BS_FFT_PRUNED ||
+                (p->fft_mode == BS_FFT_AUTO && !P->fp32 && pruned_ops(P->n, false));
     if (P->pruned) {
+        P->fft_ops = pruned_ops(P->n, P->fp32);
         const size_t cs = 2 * P->real_size, K1 = r.K + 1, NY = 2 * r.K + 1;
         pruned_batches(P->n, cs, &P->fft_rb, &P->fft_kb, &P->fft_kz);
         if ((rc = ensure<char>(P, P->fft_tw, 2 * n * cs)) ||

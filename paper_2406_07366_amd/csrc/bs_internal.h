@@ -33,7 +33,12 @@ struct DBuf {
     size_t bytes = 0;
 };
 
-struct Geometry;  // device views, see geometry.hip
+// pruned transforms of one grid size and precision (fft_kernels.h)
+struct FftOps {
+    void (*forward)(bs_plan_t);
+    void (*spectral)(bs_plan_t, int psi);
+    void (*inverse)(bs_plan_t);
+};
 
 }  // namespace bs
 
@@ -65,9 +70,10 @@ struct bs_plan_s {
     bs::DBuf spec;          // [3][n][n][n/2+1] complex
     bs::DBuf deconv;        // [K+1] float64: 1 / F(m)^2 per axis
     bs::DBuf fftwork;
-    // pruned transforms (power-of-two grids): twiddles [n forward][n
+    // pruned transforms: twiddles [n forward][n
     // inverse], A [3][n][n][K+1] and B [3][2K+1][n][K+1] complex; batch sizes
     bool pruned = false;
+    const bs::FftOps *fft_ops = nullptr;
     int fft_rb = 1, fft_kb = 1, fft_kz = 1;
     bs::DBuf fft_tw, fft_A, fft_B;
 
@@ -186,6 +192,12 @@ int fft_inverse(bs_plan_t p);
 
 // fft.hip
 bool pruned_fft_ok(int n, size_t csize);
+// the passes for a grid of n points per axis, NULL if there are none
+const FftOps *pruned_ops(int n, bool fp32);
+const FftOps *mixed_ops_a(int n);
+const FftOps *mixed_ops_b(int n);
+const FftOps *mixed_ops_c(int n);
+const FftOps *mixed_ops_d(int n);
 void pruned_batches(int n, size_t csize, int *rb, int *kb, int *kz);
 void pruned_forward(bs_plan_t p);
 void pruned_spectral_op(bs_plan_t p, int psi);
