@@ -97,7 +97,10 @@ __global__ __launch_bounds__(64 * WAVES) void k_spread(int n, int NT, int nbv, i
     const int t0[3] = {tx * TT, ty * TT, tz * TT};
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lx = lane % TT, ly = (lane / TT) % TT, lz0 = (lane / (TT * TT)) * ZL;
-    static_assert(!MMA || (TT == 8 && WAVES == 1), "the matrix-core form: 8^3 tiles, one wavefront");
+    static_assert(!MMA || TT == 8, "the matrix-core form: 8^3 tiles");
+    // a wavefront's own staging area: its rounds need no barrier with the
+    // others in the matrix-core form
+    auto stage_sync = [] { if constexpr (MMA) wave_lds_sync(); else __syncthreads(); };
     typedef typename Mfma4<R>::V V4;
     const int i16 = lane & 15, k4 = lane >> 4;
     R acc[3][ZL];
@@ -225,7 +228,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_spread(int n, int NT, int nbv, i
                 s[3 * TT + 2] = q[4 * (size_t)g + 2];
             }
         }
-        __syncthreads();
+        stage_sync();
         const int na = __popcll(m);
         if constexpr (MMA) {
             // candidates 4 at a time: A[(c, z)][k] = q_c wz[z] (rows 0..15: c = 0, 1;
@@ -271,13 +274,38 @@ __global__ __launch_bounds__(64 * WAVES) void k_spread(int n, int NT, int nbv, i
                 }
             }
         }
-        __syncthreads();
+        stage_sync();
     }
     const size_t n3 = (size_t)n * n * n;
     if constexpr (MMA) {
         // result element (row block a, column block b, v): row r = 16 a + row(k4, v)
         // (component r / 8, z = r % 8; rows 24..31 are padding), column
         // 16 b + i16 (y = 2 b + i16 / 8, x = i16 % 8)
+        if constexpr (WAVES > 1) {
+            // partial tiles through LDS, summed in wavefront order: thread t
+            // takes the cells t, t + 64 WAVES, ... of the 3 T3
+            __syncthreads();   // every wavefront is done with its staging area
+#pragma unroll
+            for (int a = 0; a < 2; a++)
+#pragma unroll
+                for (int b = 0; b < 4; b++)
+#pragma unroll
+                    for (int v = 0; v < 4; v++) {
+                        const int r = 16 * a + Mfma4<R>::row(k4, v);
+                        if (r < 24) lds[(wave * 24 + r) * 64 + 16 * b + i16] = dacc[a][b][v];
+                    }
+            __syncthreads();
+#pragma unroll
+            for (int i = threadIdx.x; i < 3 * T3; i += 64 * WAVES) {
+                R v = lds[i];
+                for (int w2 = 1; w2 < WAVES; w2++) v += lds[w2 * 3 * T3 + i];
+                const int r = i >> 6, cell = i & 63;
+                const size_t gi = ((size_t)(t0[2] + (r & 7)) * n + (t0[1] + (cell >> 3))) * n +
+                                  (t0[0] + (cell & 7));
+                grid[(size_t)(r >> 3) * n3 + gi] = v;
+            }
+            return;
+        }
 #pragma unroll
         for (int a = 0; a < 2; a++)
 #pragma unroll
@@ -321,12 +349,14 @@ __global__ __launch_bounds__(64 * WAVES) void k_spread(int n, int NT, int nbv, i
     }
 }
 
-// grids with fewer tiles than this split each tile's candidates over 4
-// wavefronts (more parallelism for small grids), and float32 grids of at most
-// kSpreadWideTiles tiles over 8 (a 64^3 grid of 8^3 tiles: the busiest tile
-// holds ~5x the mean candidate count).  The float64 variant stays at 4: at 8
-// its staging area (112 KB) leaves one workgroup per CU
+// Grids with fewer tiles than this split each tile's candidates over 4
+// wavefronts (more parallelism for small grids), in float64 on the matrix
+// cores: at 64^3 (512 tiles) 21.5 us against 42.3 with one wavefront per tile,
+// at 128^3 (4096) 73.4 against 49.8 and at 160^3 (8000) 145 against 59 (the
+// vector form: 22, 75 and 148).  float32 grids keep their summation order: the
+// vector form below 8192 tiles, over 8 wavefronts up to kSpreadWideTiles.
 constexpr int kSpreadSplitTiles = 8192;
+constexpr int kSpreadSplitTiles64 = 2048;
 constexpr int kSpreadWideTiles = 512;
 
 template <typename R, int TT>
@@ -337,7 +367,7 @@ static void spread_tt(bs_plan_t p) {
     if (nbv > nb) return;   // the kernel's bin table holds nb^3 bins
     const int ntiles = p->NT * p->NT * p->NT;
     const int per = ceil_div(ntiles, 8);
-    const bool split = ntiles < kSpreadSplitTiles;
+    const bool split = ntiles < (sizeof(R) == 8 ? kSpreadSplitTiles64 : kSpreadSplitTiles);
     const bool wide = sizeof(R) == 4 && TT == 8 && ntiles <= kSpreadWideTiles;
     dim3 grid(8 * per), block(wide ? 512 : (split ? 256 : 64));
     const int *start = (const int *)p->sp_start.p;
@@ -354,8 +384,8 @@ static void spread_tt(bs_plan_t p) {
             }                                                                                    \
         }                                                                                        \
         if (split)                                                                               \
-            hipLaunchKernelGGL((k_spread<R, WW, TT, 4, false>), grid, block, 0, p->stream, p->n, \
-                               p->NT, nbv, per, start, base, ker, q, g);                         \
+            hipLaunchKernelGGL((k_spread<R, WW, TT, 4, TT == 8 && sizeof(R) == 8>), grid, block,  \
+                               0, p->stream, p->n, p->NT, nbv, per, start, base, ker, q, g);     \
         else                                                                                     \
             hipLaunchKernelGGL((k_spread<R, WW, TT, 1, TT == 8>), grid, block, 0, p->stream,     \
                                p->n, p->NT, nbv, per, start, base, ker, q, g);                   \
