@@ -278,15 +278,14 @@ __device__ __forceinline__ void gather_one(int t, int w, int Q, const int *__res
                                            const int *__restrict__ pperm,
                                            const double *__restrict__ pos,
                                            const double *__restrict__ chg, double L, double inv_h,
-                                           int n, double zeta, double inv_den, const GatherOut &G,
-                                           R *lk) {
+                                           int n, const KbPhi &kb, const GatherOut &G, R *lk) {
     const int p = t / 3, d = t - 3 * p;
     R *q = (R *)G.q, *schg = (R *)G.schg;
     int o = sperm[p];
     double f;
     const int b = stencil_base(wrap_box(pos[3 * o + d], L), inv_h, w, n, &f);
     const double half = 0.5 * w;
-    for (int k = 0; k < w; k++) lk[k] = (R)kb_phi((k - f) / half, zeta, inv_den);
+    for (int k = 0; k < w; k++) lk[k] = kb_value<R>((k - f) / half, kb);
     int *bp = (int *)(G.base + p);
     bp[d] = b;
     q[4 * (size_t)p + d] = (R)chg[3 * o + d];
@@ -316,8 +315,7 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_all(int M, int w, int Q
                                                              const double *__restrict__ pos,
                                                              const double *__restrict__ chg,
                                                              double L, double inv_h, int n,
-                                                             double zeta, double inv_den,
-                                                             GatherOut G, int N,
+                                                             KbPhi kb, GatherOut G, int N,
                                                              const int *__restrict__ nperm,
                                                              const double *__restrict__ x,
                                                              const int *__restrict__ off,
@@ -335,8 +333,7 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_all(int M, int w, int Q
     }
     const int t0 = blockIdx.x * kGatherBlock, t = t0 + (int)threadIdx.x;
     if (t < 3 * M)
-        gather_one<R>(t, w, Q, sperm, pperm, pos, chg, L, inv_h, n, zeta, inv_den, G,
-                      lk + threadIdx.x * w);
+        gather_one<R>(t, w, Q, sperm, pperm, pos, chg, L, inv_h, n, kb, G, lk + threadIdx.x * w);
     __syncthreads();
     const int nt = 3 * M - t0 < kGatherBlock ? 3 * M - t0 : kGatherBlock;
     R *ker = (R *)G.ker + (size_t)t0 * w;
@@ -376,7 +373,6 @@ void build_bins(bs_plan_t p) {
         S.ngrp[a] = ceil_div(S.nbins[a], S.per[a]);
     }
     const int maxb = ntiles > ncp ? ntiles : ncp;
-    const double zeta = p->prm.zeta, inv_den = 1.0 / (-expm1(-2.0 * zeta));
     GatherOut G;
     G.base = (int4 *)p->sp_base.p;
     G.ker = p->sp_ker.p;
@@ -398,7 +394,7 @@ void build_bins(bs_plan_t p) {
     const int *off = (const int *)p->d_off.p, *fil = (const int *)p->d_fil.p;
     auto gather = p->fp32 ? k_gather_all<float> : k_gather_all<double>;
     hipLaunchKernelGGL(gather, gg, dim3(kGatherBlock), 0, p->stream, M, w, p->Q, S.perm[0],
-                       S.perm[1], qp, qc, L, inv_h, n, zeta, inv_den, G, N, S.perm[2], x, off, fil);
+                       S.perm[1], qp, qc, L, inv_h, n, p->kb, G, N, S.perm[2], x, off, fil);
 }
 
 BinKeys bin_keys(bs_plan_t p) {

@@ -6,6 +6,7 @@
 #include <string>
 
 #include "bs_internal.h"
+#include "direct.h"
 
 namespace bs {
 
@@ -346,6 +347,10 @@ int bs_plan(const bs_params *p, void *hip_stream, bs_plan_t *out) {
     if ((rc = check_hip(P, hipMemcpy(P->deconv.p, tab.data(), tab.size() * sizeof(double),
                                      hipMemcpyHostToDevice), "copy table")))
         return fail(rc);
+    P->kb.zeta = r.zeta;
+    P->kb.c2 = exp(-2.0 * r.zeta);
+    P->kb.inv_den = 1.0 / (-expm1(-2.0 * r.zeta));
+    P->kb.edge = 2.0 * r.zeta * exp(-r.zeta) * P->kb.inv_den;
     // FFT plans: 3 transforms of n^3 (real) <-> n^2 (n/2+1) (complex)
     int dims[3] = {P->n, P->n, P->n};
     size_t ws = 0;
@@ -375,7 +380,7 @@ int bs_plan(const bs_params *p, void *hip_stream, bs_plan_t *out) {
         const size_t cs = 2 * P->real_size, K1 = r.K + 1, NY = 2 * r.K + 1;
         pruned_batches(P->n, cs, &P->fft_rb, &P->fft_kb, &P->fft_kz);
         if ((rc = ensure<char>(P, P->fft_tw, 2 * n * cs)) ||
-            (rc = ensure<char>(P, P->fft_A, 3 * n * n * K1 * cs)) ||
+            (P->n > kFftXYMax && (rc = ensure<char>(P, P->fft_A, 3 * n * n * K1 * cs))) ||
             (rc = ensure<char>(P, P->fft_B, 3 * NY * n * K1 * cs)))
             return fail(rc);
         // [n] exp(-2 pi i k / n), then [n] exp(+2 pi i k / n)
@@ -437,19 +442,20 @@ int bs_set_periods(bs_plan_t P, int64_t nfil, const int64_t *periods) {
     return BS_OK;
 }
 
-int bs_set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, const double *xyz,
-                     const double *gamma) {
+// filaments at positions xyz, or xyz + c kstage (a Runge-Kutta stage)
+static int set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, const double *xyz,
+                         const double *kstage, double c, const double *gamma) {
     if (!P) return set_error(nullptr, BS_EINVAL, "null plan");
     if (nfil < 1 || !offsets || !xyz || !gamma)
         return set_error(P, BS_EINVAL, "need nfil >= 1 and non-null offsets, xyz, gamma");
     if (offsets[0] != 0) return set_error(P, BS_EINVAL, "offsets[0] must be 0");
     int64_t maxn = 0;
     for (int64_t f = 0; f < nfil; f++) {
-        int64_t c = offsets[f + 1] - offsets[f];
-        if (c < 3) return set_error(P, BS_EINVAL, "every filament needs at least 3 nodes");
-        if (P->order == 6 && c < 6)
+        int64_t len = offsets[f + 1] - offsets[f];
+        if (len < 3) return set_error(P, BS_EINVAL, "every filament needs at least 3 nodes");
+        if (P->order == 6 && len < 6)
             return set_error(P, BS_EINVAL, "quintic splines need at least 6 nodes per filament");
-        maxn = std::max(maxn, c);
+        maxn = std::max(maxn, len);
     }
     const int64_t N = offsets[nfil], Nq = N * P->Q;
     if (Nq >= ((int64_t)1 << 31) / 4) return set_error(P, BS_EINVAL, "too many nodes");
@@ -535,7 +541,15 @@ int bs_set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, const do
              (rc = check_hip(P, hipMemsetAsync(P->ns_fallback.p, 0, P->ns_fallback.bytes,
                                                P->stream), "memset"))))
             return rc;
-        std::vector<int> off32(nfil + 1), fil32(N);
+        std::vector<int> off32(nfil + 1), fil32(N), pfirst(nfil + 1, 0);
+        for (int64_t f = 0; f < nfil; f++)
+            pfirst[f + 1] = pfirst[f] + (int)ceil_div(offsets[f + 1] - offsets[f], kPiece);
+        if (direct_path(P, Nq) &&
+            ((rc = ensure<Piece>(P, P->d_piece, pfirst[nfil])) ||
+             (rc = ensure<int>(P, P->d_pfirst, nfil + 1)) ||
+             (rc = check_hip(P, hipMemcpyAsync(P->d_pfirst.p, pfirst.data(), sizeof(int) * (nfil + 1),
+                                               hipMemcpyHostToDevice, P->stream), "copy pieces"))))
+            return rc;
         for (int64_t f = 0; f <= nfil; f++) off32[f] = (int)offsets[f];
         for (int64_t f = 0; f < nfil; f++)
             for (int64_t j = offsets[f]; j < offsets[f + 1]; j++) fil32[j] = (int)f;
@@ -550,12 +564,14 @@ int bs_set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, const do
         P->nfil = nfil;
         P->ncx = ncx;
         P->ncy = ncy;
+        P->direct = direct_path(P, Nq);
+        P->npiece = (int)pfirst[nfil];
         P->N = N;
         P->Nq = Nq;
         P->max_fil_nodes = maxn;
     }
     stage_begin(P, 0);
-    launch_filaments(P, xyz, gamma);   // also takes the plan's copies of xyz and gamma
+    launch_filaments(P, xyz, kstage, c, gamma);   // also takes the plan's copies of xyz and gamma
     stage_end(P, 0);
     if (P->prm.ns_mode != BS_NS_OFF) {
         // the pair search needs only the geometry: it runs on the side stream,
@@ -578,13 +594,20 @@ int bs_set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, const do
             P->side_pending = true;
         }
     }
-    stage_begin(P, 1);
-    build_bins(P);
-    stage_end(P, 1);
+    if (!P->direct) {
+        stage_begin(P, 1);
+        build_bins(P);
+        stage_end(P, 1);
+    }
     if ((rc = launch_status(P, "geometry kernels"))) return rc;
     P->have_filaments = true;
     stage_collect(P);
     return BS_OK;
+}
+
+int bs_set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, const double *xyz,
+                     const double *gamma) {
+    return set_filaments(P, nfil, offsets, xyz, nullptr, 0.0, gamma);
 }
 
 // out += near-singular correction; base: the velocity terms formed so far at
@@ -604,13 +627,16 @@ static int launch_ns(bs_plan_t P, double *out, const double *base) {
 }
 
 // out = base + long-range term (base NULL: out += long-range term); with
-// join set, the interpolation waits for that event first
+// join set, the interpolation waits for that event first; spread: whether the
+// grid still has to be written
 static int long_range(bs_plan_t P, int psi, const double *base, double *out,
-                      hipEvent_t join = nullptr) {
+                      hipEvent_t join = nullptr, bool spread = true) {
     int rc;
-    stage_begin(P, 3);
-    launch_spread(P);
-    stage_end(P, 3);
+    if (spread) {
+        stage_begin(P, 3);
+        launch_spread(P);
+        stage_end(P, 3);
+    }
     if (P->pruned) {
         stage_begin(P, 4);
         pruned_forward(P);
@@ -657,8 +683,15 @@ int bs_velocity(bs_plan_t P, double *v_out) {
     // same sum, bitwise).  With per-stage timing on, everything stays on the
     // plan stream, so that each stage's events bracket its own kernels only.
     double *t3 = (double *)P->tmp3.p;
+    // Small inputs without the correction need no second stream: the pair sums
+    // run in the spread's launch.
     const bool side = !P->prof;
     int rc;
+    if (side && P->direct && P->prm.ns_mode == BS_NS_OFF) {
+        launch_spread_pairs(P, (const double *)P->d_vls.p, t3);
+        if ((rc = long_range(P, 0, t3, v_out, nullptr, false))) return rc;
+        return launch_status(P, "velocity kernels");
+    }
     if (!side && (rc = join_side(P))) return rc;
     if (side &&
         ((rc = check_hip(P, hipEventRecord(P->ev_fork, P->stream), "hipEventRecord")) ||
@@ -786,12 +819,7 @@ int bs_status(bs_plan_t P) {
     return BS_OK;
 }
 
-// classical RK4 stage helpers on [N][3] float64 arrays
-__global__ void k_axpy_stage(size_t n, const double *__restrict__ x, const double *__restrict__ k,
-                             double c, double *__restrict__ y) {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] = x[i] + c * k[i];
-}
+// classical RK4 update of [N][3] float64 positions
 __global__ void k_rk4_final(size_t n, double *__restrict__ x, const double *__restrict__ k1,
                             const double *__restrict__ k2, const double *__restrict__ k3,
                             const double *__restrict__ k4, double dt) {
@@ -807,17 +835,15 @@ int bs_rk4_step(bs_plan_t P, int64_t nfil, const int64_t *offsets, double *xyz,
     const int64_t N = offsets[nfil];
     const size_t n3 = 3 * (size_t)N;
     int rc;
-    if ((rc = ensure<double>(P, P->rk_k, 4 * n3)) || (rc = ensure<double>(P, P->rk_s, n3))) return rc;
-    double *k = (double *)P->rk_k.p, *s = (double *)P->rk_s.p;
+    if ((rc = ensure<double>(P, P->rk_k, 4 * n3))) return rc;
+    double *k = (double *)P->rk_k.p;
     const dim3 g((unsigned)((n3 + 255) / 256)), b(256);
     const double c[4] = {0.0, 0.5 * dt, 0.5 * dt, dt};
     for (int st = 0; st < 4; st++) {
-        const double *pos = xyz;
-        if (st > 0) {
-            hipLaunchKernelGGL(k_axpy_stage, g, b, 0, P->stream, n3, xyz, k + (st - 1) * n3, c[st], s);
-            pos = s;
-        }
-        if ((rc = bs_set_filaments(P, nfil, offsets, pos, gamma))) return rc;
+        // the stage's positions x + c k are formed as they are read
+        if ((rc = set_filaments(P, nfil, offsets, xyz, st ? k + (st - 1) * n3 : nullptr, c[st],
+                                gamma)))
+            return rc;
         if ((rc = bs_velocity(P, k + st * n3))) return rc;
     }
     hipLaunchKernelGGL(k_rk4_final, g, b, 0, P->stream, n3, xyz, k, k + n3, k + 2 * n3, k + 3 * n3, dt);
@@ -953,7 +979,7 @@ int bs_destroy(bs_plan_t P) {
                    &P->ns_tstart, &P->ns_tfill, &P->ns_tperm, &P->ns_segA, &P->ns_segB, &P->ns_segM, &P->ns_segH, &P->ns_slots,
                    &P->ns_cnt, &P->ns_start, &P->ns_pairs, &P->ns_pnode, &P->ns_pout,
                    &P->ns_X, &P->ns_Y, &P->ns_fallback, &P->ns_learn, &P->ns_fblist, &P->ns_vs, &P->rk_k,
-                   &P->rk_s};
+                   &P->d_piece, &P->d_pfirst};
     for (DBuf *b : all) release(*b);
     delete P;
     return BS_OK;

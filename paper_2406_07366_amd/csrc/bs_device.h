@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "bs_internal.h"
+
 namespace bs {
 
 // Position folded into [0, L).  Anything that does not land there (NaN,
@@ -60,6 +62,24 @@ __device__ __forceinline__ double rcp_nr(double a) {
     return fma(y, fma(-a, y, 1.0), y);
 }
 
+// four-deep matrix-core products of 16 x 16 tiles and the row of a lane's
+// result element v (lanes k4 = lane / 16)
+template <typename R> struct Mfma4;
+template <> struct Mfma4<double> {
+    typedef double V __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ V op(double a, double b, V c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ constexpr int row(int k4, int v) { return k4 + 4 * v; }
+};
+template <> struct Mfma4<float> {
+    typedef float V __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ V op(float a, float b, V c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ constexpr int row(int k4, int v) { return 4 * k4 + v; }
+};
+
 // Backward Kaiser-Bessel kernel, normalised to 1 at the centre:
 //   phi(z) = sinh(zeta sqrt(1-z^2)) / (sinh(zeta) sqrt(1-z^2)),  |z| <= 1
 // (eq:kaiser_bessel_bw up to the constant pi/sinh(zeta), which the
@@ -71,6 +91,23 @@ __device__ __forceinline__ double kb_phi(double z, double zeta, double inv_den) 
     if (s2 <= 0.0) return 2.0 * zeta * exp(-zeta) * inv_den;
     double s = sqrt(s2);
     return exp(zeta * (s - 1.0)) * (-expm1(-2.0 * zeta * s)) / s * inv_den;
+}
+
+// The same in float64 for one exponential: with a = exp(zeta (s - 1)) and c2 =
+// exp(-2 zeta), phi = (a - c2 / a) / s * inv_den.  The difference loses
+// relative digits only near s = 0, where phi is ~1e-6 of its centre value
+// (absolute error there ~1e-22); ~60 instructions instead of ~200.
+__device__ __forceinline__ double kb_phi64(double z, const KbPhi &K) {
+    const double s2 = 1.0 - z * z;
+    if (s2 <= 0.0) return K.edge;
+    const double r = rsqrt_nr(s2);
+    const double a = exp(K.zeta * (s2 * r - 1.0));
+    return (a - K.c2 * rcp_nr(a)) * r * K.inv_den;
+}
+template <typename R>
+__device__ __forceinline__ R kb_value(double z, const KbPhi &K) {
+    if constexpr (sizeof(R) == 8) return kb_phi64(z, K);
+    else return (R)kb_phi(z, K.zeta, K.inv_den);
 }
 
 

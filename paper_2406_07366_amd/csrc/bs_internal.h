@@ -33,6 +33,12 @@ struct DBuf {
     size_t bytes = 0;
 };
 
+// Kaiser-Bessel kernel: shape parameter, exp(-2 zeta), 1 / (1 - exp(-2 zeta))
+// and the value at the support's edge
+struct KbPhi {
+    double zeta, c2, inv_den, edge;
+};
+
 // pruned transforms of one grid size and precision (fft_kernels.h)
 struct FftOps {
     void (*forward)(bs_plan_t);
@@ -81,6 +87,13 @@ struct bs_plan_s {
     // in ncx x ncy x ncy (x fastest; set with the filaments, see pair_cells)
     int nc = 1;
     int ncx = 1, ncy = 1;
+    // small float64 inputs: points and targets in index order, no sorts
+    // (direct.h; set with the filaments)
+    bool direct = false;
+    bs::KbPhi kb{};            // the kernel's constants
+    // pieces of filaments (direct path): boxes, first piece of each filament
+    int npiece = 0;
+    bs::DBuf d_piece, d_pfirst;
 
     // filaments
     int64_t nfil = 0, N = 0, Nq = 0;
@@ -132,7 +145,7 @@ struct bs_plan_s {
                                                // path hands to the graded panels
     bs::DBuf ns_vs;                            // f64 [1 + blocks]: velocity scale
     // RK4 stage buffers
-    bs::DBuf rk_k, rk_s;
+    bs::DBuf rk_k;
     // graph replay of bs_step
     bool use_graph = false;
     hipGraph_t graph = nullptr;
@@ -159,7 +172,9 @@ int check_hip(bs_plan_t p, hipError_t e, const char *what);
 // geometry.hip
 // chord lengths, spline, quadrature points, charges, segment lengths and the
 // velocity's local-minus-self term (d_vls), one workgroup per filament
-void launch_filaments(bs_plan_t p, const double *xyz, const double *gamma);
+// (positions xyz, or xyz + c kstage when kstage is given)
+void launch_filaments(bs_plan_t p, const double *xyz, const double *kstage, double c,
+                      const double *gamma);
 // spline through periodic nodal data (such as the streamfunction) on the
 // plan's knots: slopes (and, quintic, second derivatives) into Dout, Sout
 void launch_spline_data(bs_plan_t p, const double *data, double *Dout, double *Sout);
@@ -181,6 +196,13 @@ struct BinKeys {
 };
 BinKeys bin_keys(bs_plan_t p);
 
+// direct.hip
+bool direct_path(bs_plan_t p, int64_t Nq);
+void launch_direct_gather(bs_plan_t p);
+void launch_spread_direct(bs_plan_t p);
+// the spread and out = base + short-range velocity term in one launch
+void launch_spread_pairs(bs_plan_t p, const double *base, double *out);
+
 // nufft.hip
 void launch_spread(bs_plan_t p);
 void launch_spectral(bs_plan_t p, int psi);
@@ -191,6 +213,9 @@ int fft_forward(bs_plan_t p);
 int fft_inverse(bs_plan_t p);
 
 // fft.hip
+// grids up to this one take a whole (component, z) plane per workgroup and
+// need no array between the x and y transforms
+constexpr int kFftXYMax = 64;
 bool pruned_fft_ok(int n, size_t csize);
 // the passes for a grid of n points per axis, NULL if there are none
 const FftOps *pruned_ops(int n, bool fp32);

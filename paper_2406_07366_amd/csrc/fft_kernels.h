@@ -701,7 +701,6 @@ __global__ __launch_bounds__(kFftMaxThreads) void k_fft_zt_spectral(
 // K + 1 columns (and the reverse for the inverse), so the plane needs one
 // launch and no intermediate array in HBM.  A 64^2 plane in float64 needs
 // 93 KB of LDS (one workgroup per CU; 192 workgroups).
-constexpr int kFftXYMax = 64;
 
 template <typename C>
 __host__ __device__ constexpr size_t xy_lds(int n, int K1) {

@@ -25,6 +25,7 @@
 // unique, so this is the paper's curve).
 #include "bs_internal.h"
 #include "bs_device.h"
+#include "direct.h"
 
 namespace bs {
 
@@ -39,7 +40,7 @@ __device__ __forceinline__ int prev_node(const int *off, const int *fil, int j) 
 
 // ------------------------------------------------------------- chord lengths
 // Chord lengths of filament f from the caller's node positions, which are
-// copied into the plan's own array on the way (xs may alias xd); also the
+// copied into the plan's own array on the way; also the
 // plan's copy of the filament's circulation and the end node of every
 // segment in the segment's own frame (xn).  An infinite filament
 // (s(tau + T) = s(tau) + n L, Sec. 2.1) has its period shift n L in shift;
@@ -47,7 +48,15 @@ __device__ __forceinline__ int prev_node(const int *off, const int *fil, int j) 
 // filaments closed.  Non-finite positions and zero-length segments set bit 0
 // of the status word (their chord is taken as 1 so that the rest stays
 // finite).
-__device__ void chord_fil(int f, int b0, int n, const double *xs, double *xd,
+// Positions may be those of a Runge-Kutta stage, x + c k, formed here.
+struct StagePos {
+    const double *x, *k;   // k NULL: x itself
+    double c;
+    __device__ __forceinline__ double operator[](int i) const {
+        return k ? x[i] + c * k[i] : x[i];
+    }
+};
+__device__ void chord_fil(int f, int b0, int n, const StagePos &xs, double *xd,
                           double *__restrict__ xn, const double *__restrict__ shift,
                           const double *__restrict__ gs, double *__restrict__ gd,
                           double *__restrict__ dtau, int *__restrict__ status) {
@@ -80,72 +89,72 @@ __device__ void chord_fil(int f, int b0, int n, const double *xs, double *xd,
 // couplings left after six steps lie below rounding and x = r / b.
 constexpr int kPcrSteps = 6;
 
+// Rows are kept scaled to a unit diagonal, so that a step needs one
+// reciprocal and the solution is the final right-hand side.
 struct PcrArrays {
-    double *a, *b, *c, *r;     // r holds 3 components: r[3*k + comp]
+    double *a, *c, *r;     // r holds 3 components: r[3*k + comp]
 };
 
-__device__ void pcr_solve(int n, PcrArrays A, PcrArrays B) {
-    // A holds the system on entry; ping-pong with B; the solution of the
-    // final step is left in whichever holds the last result.
-    int d = 1;
-    PcrArrays src = A, dst = B;
+__device__ void pcr_solve(int n, PcrArrays src, PcrArrays dst) {
+    // src holds the system on entry; ping-pong with dst
+    int dm = 1;   // 2^s mod n
+#pragma unroll 1
     for (int s = 0; s < kPcrSteps; s++) {
-        int dm = d % n;
         for (int i = threadIdx.x; i < n; i += blockDim.x) {
             int im = i - dm; if (im < 0) im += n;
             int ip = i + dm; if (ip >= n) ip -= n;
-            double k1 = src.a[i] / src.b[im];
-            double k2 = src.c[i] / src.b[ip];
-            dst.a[i] = -k1 * src.a[im];
-            dst.c[i] = -k2 * src.c[ip];
-            dst.b[i] = src.b[i] - k1 * src.c[im] - k2 * src.a[ip];
+            const double k1 = src.a[i], k2 = src.c[i];
+            const double w = rcp_nr(1.0 - k1 * src.c[im] - k2 * src.a[ip]);
+            dst.a[i] = -k1 * src.a[im] * w;
+            dst.c[i] = -k2 * src.c[ip] * w;
 #pragma unroll
             for (int q = 0; q < 3; q++)
-                dst.r[3 * i + q] = src.r[3 * i + q] - k1 * src.r[3 * im + q] - k2 * src.r[3 * ip + q];
+                dst.r[3 * i + q] =
+                    w * (src.r[3 * i + q] - k1 * src.r[3 * im + q] - k2 * src.r[3 * ip + q]);
         }
         __syncthreads();
         PcrArrays t = src; src = dst; dst = t;
-        d *= 2;
+        dm *= 2;
+        if (dm >= n) dm -= n;
     }
-    // the last step wrote B if kPcrSteps is odd, A if it is even
+    // the last step wrote the second array if kPcrSteps is odd, else the first
 }
 
 // slopes D of the cubic spline through the nodal data x of one filament
 // (nodes b0 .. b0+n-1); xn: end node of each segment in its own frame, for
 // positions (NULL for periodic data such as the streamfunction); the whole
 // workgroup takes part
-__device__ void spline_cubic_fil(int b0, int n, const double *__restrict__ x,
-                                 const double *__restrict__ xn,
-                                 const double *__restrict__ dtau, double *__restrict__ D,
-                                 double *__restrict__ gscratch) {
-    __shared__ double lds[2 * 6 * kPcrLds];
+__device__ __forceinline__ void spline_cubic_fil(int b0, int n, const double *__restrict__ x,
+                                                 const double *__restrict__ xn,
+                                                 const double *__restrict__ dtau,
+                                                 double *__restrict__ D,
+                                                 double *__restrict__ gscratch) {
+    __shared__ double lds[2 * 5 * kPcrLds];
     double *base;
     if (n <= kPcrLds) base = lds;
-    else base = gscratch + (size_t)12 * b0;   // 12 doubles per node
+    else base = gscratch + (size_t)12 * b0;   // 10 doubles per node
     int stride = (n <= kPcrLds) ? kPcrLds : n;
-    PcrArrays A{base, base + stride, base + 2 * stride, base + 3 * stride};
-    PcrArrays B{base + 6 * stride, base + 7 * stride, base + 8 * stride, base + 9 * stride};
+    PcrArrays A{base, base + stride, base + 2 * stride};
+    PcrArrays B{base + 5 * stride, base + 6 * stride, base + 7 * stride};
     for (int k = threadIdx.x; k < n; k += blockDim.x) {
         int km = (k == 0) ? n - 1 : k - 1, kp = (k + 1 == n) ? 0 : k + 1;
-        double hm = dtau[b0 + km], hk = dtau[b0 + k];
-        A.a[k] = hk;
-        A.b[k] = 2.0 * (hm + hk);
-        A.c[k] = hm;
+        const double hm = dtau[b0 + km], hk = dtau[b0 + k];
+        const double w = rcp_nr(2.0 * (hm + hk));
+        A.a[k] = hk * w;
+        A.c[k] = hm * w;
+        const double fm = 3.0 * w * hk * rcp_nr(hm), fp = 3.0 * w * hm * rcp_nr(hk);
 #pragma unroll
         for (int q = 0; q < 3; q++) {
             const double s0 = x[3 * (b0 + k) + q], sm = x[3 * (b0 + km) + q];
             const double dm = (xn ? xn[3 * (b0 + km) + q] : s0) - sm;
             const double dp = (xn ? xn[3 * (b0 + k) + q] : x[3 * (b0 + kp) + q]) - s0;
-            A.r[3 * k + q] = 3.0 * (hk * dm / hm + hm * dp / hk);
+            A.r[3 * k + q] = fm * dm + fp * dp;
         }
     }
     __syncthreads();
     pcr_solve(n, A, B);
     PcrArrays R = (kPcrSteps & 1) ? B : A;
-    for (int k = threadIdx.x; k < n; k += blockDim.x) {
-#pragma unroll
-        for (int q = 0; q < 3; q++) D[3 * (b0 + k) + q] = R.r[3 * k + q] / R.b[k];
-    }
+    for (int i = threadIdx.x; i < 3 * n; i += blockDim.x) D[3 * b0 + i] = R.r[i];
 }
 
 __global__ void k_spline(int nfil, const int *__restrict__ off, const double *__restrict__ x,
@@ -172,12 +181,13 @@ __global__ void k_spline(int nfil, const int *__restrict__ off, const double *__
 // the same node and their two couplings are merged.
 constexpr int kPcr5Steps = 8;
 
+// Rows are kept multiplied by the inverse of their diagonal block.
 struct Blk {
-    double L[4], M[4], U[4], R[6];   // 2x2 blocks row-major; R[row * 3 + comp]
+    double L[4], U[4], R[6];   // 2x2 blocks row-major; R[row * 3 + comp]
 };
 
 __device__ __forceinline__ void inv2(const double *A, double *B) {
-    const double id = 1.0 / (A[0] * A[3] - A[1] * A[2]);
+    const double id = rcp_nr(A[0] * A[3] - A[1] * A[2]);
     B[0] = A[3] * id;
     B[1] = -A[1] * id;
     B[2] = -A[2] * id;
@@ -200,94 +210,95 @@ __device__ __forceinline__ void sub_mulR(const double *K, const double *V, doubl
     for (int r = 0; r < 2; r++)
         for (int q = 0; q < 3; q++) R[3 * r + q] -= K[2 * r] * V[q] + K[2 * r + 1] * V[3 + q];
 }
+// o = M^-1 (L, U, R)
+__device__ __forceinline__ void scale_row(const double *M, const double *L, const double *U,
+                                          const double *R, Blk &o) {
+    double Mi[4], t[4];
+    inv2(M, Mi);
+    mul2(Mi, L, t);
+    for (int k = 0; k < 4; k++) o.L[k] = t[k];
+    mul2(Mi, U, t);
+    for (int k = 0; k < 4; k++) o.U[k] = t[k];
+    for (int r = 0; r < 2; r++)
+        for (int q = 0; q < 3; q++) o.R[3 * r + q] = Mi[2 * r] * R[q] + Mi[2 * r + 1] * R[3 + q];
+}
 
 // slopes D and second derivatives S of the quintic spline through the nodal
 // data x of one filament; the whole workgroup takes part
-__device__ void spline_quintic_fil(int b0, int n, const double *__restrict__ x,
-                                   const double *__restrict__ xn,
-                                   const double *__restrict__ dtau, double *__restrict__ D,
-                                   double *__restrict__ S, double *__restrict__ gscratch) {
+__device__ __forceinline__ void spline_quintic_fil(int b0, int n, const double *__restrict__ x,
+                                                   const double *__restrict__ xn,
+                                                   const double *__restrict__ dtau,
+                                                   double *__restrict__ D, double *__restrict__ S,
+                                                   double *__restrict__ gscratch) {
     __shared__ Blk lds[2 * kPcr5Lds];
     Blk *src, *dst;
     if (n <= kPcr5Lds) {
         src = lds;
         dst = lds + kPcr5Lds;
     } else {
-        src = (Blk *)(gscratch + (size_t)36 * b0);   // 2 x 18 doubles per node
+        src = (Blk *)(gscratch + (size_t)36 * b0);   // 2 x 14 doubles per node
         dst = src + n;
     }
     for (int k = threadIdx.x; k < n; k += blockDim.x) {
         const int km = (k == 0) ? n - 1 : k - 1, kp = (k + 1 == n) ? 0 : k + 1;
-        const double hm = dtau[b0 + km], hp = dtau[b0 + k];
-        const double im1 = 1.0 / hm, ip1 = 1.0 / hp;
+        const double im1 = rcp_nr(dtau[b0 + km]), ip1 = rcp_nr(dtau[b0 + k]);
         const double im2 = im1 * im1, ip2 = ip1 * ip1, im3 = im2 * im1, ip3 = ip2 * ip1;
-        Blk &e = src[k];
-        e.L[0] = -8.0 * im2;  e.L[1] = -im1;
-        e.L[2] = 14.0 * im3;  e.L[3] = 2.0 * im2;
-        e.M[0] = 12.0 * (ip2 - im2);   e.M[1] = 3.0 * (im1 + ip1);
-        e.M[2] = 16.0 * (im3 + ip3);   e.M[3] = -3.0 * (im2 - ip2);
-        e.U[0] = 8.0 * ip2;   e.U[1] = -ip1;
-        e.U[2] = 14.0 * ip3;  e.U[3] = -2.0 * ip2;
+        const double L[4] = {-8.0 * im2, -im1, 14.0 * im3, 2.0 * im2};
+        const double M[4] = {12.0 * (ip2 - im2), 3.0 * (im1 + ip1), 16.0 * (im3 + ip3),
+                             -3.0 * (im2 - ip2)};
+        const double U[4] = {8.0 * ip2, -ip1, 14.0 * ip3, -2.0 * ip2};
+        double R[6];
 #pragma unroll
         for (int q = 0; q < 3; q++) {
             const double s0 = x[3 * (b0 + k) + q], sm = x[3 * (b0 + km) + q];
             const double dm = (xn ? xn[3 * (b0 + km) + q] : s0) - sm;
             const double dp = (xn ? xn[3 * (b0 + k) + q] : x[3 * (b0 + kp) + q]) - s0;
-            e.R[q] = 20.0 * (dp * ip3 - dm * im3);
-            e.R[3 + q] = 30.0 * (dm * im3 * im1 + dp * ip3 * ip1);
+            R[q] = 20.0 * (dp * ip3 - dm * im3);
+            R[3 + q] = 30.0 * (dm * im3 * im1 + dp * ip3 * ip1);
         }
+        scale_row(M, L, U, R, src[k]);
     }
     __syncthreads();
-    int d = 1;
+    int dm = 1;   // 2^st mod n
+#pragma unroll 1
     for (int st = 0; st < kPcr5Steps; st++) {
-        const int dm = d % n;
         for (int i = threadIdx.x; i < n; i += blockDim.x) {
             int im = i - dm; if (im < 0) im += n;
             int ip = i + dm; if (ip >= n) ip -= n;
-            const Blk &e = src[i];
-            Blk &o = dst[i];
-            double Mi[4], K[4];
-            for (int k = 0; k < 4; k++) o.M[k] = e.M[k];
-            for (int k = 0; k < 6; k++) o.R[k] = e.R[k];
+            const Blk e = src[i];
+            double M[4] = {1.0, 0.0, 0.0, 1.0}, L[4], U[4], R[6];
+            for (int k = 0; k < 6; k++) R[k] = e.R[k];
             if (2 * dm == n) {
                 // both neighbours are node ip: one coupling L_i + U_i
                 double Ci[4], Cj[4];
                 for (int k = 0; k < 4; k++) {
                     Ci[k] = e.L[k] + e.U[k];
                     Cj[k] = src[ip].L[k] + src[ip].U[k];
+                    L[k] = U[k] = 0.0;
                 }
-                inv2(src[ip].M, Mi);
-                mul2(Ci, Mi, K);
-                sub_mul2(K, Cj, o.M);
-                sub_mulR(K, src[ip].R, o.R);
-                for (int k = 0; k < 4; k++) o.L[k] = o.U[k] = 0.0;
+                sub_mul2(Ci, Cj, M);
+                sub_mulR(Ci, src[ip].R, R);
             } else {
-                inv2(src[im].M, Mi);
-                mul2(e.L, Mi, K);             // K1 = L_i M_im^-1
-                mul2(K, src[im].L, o.L);
-                for (int k = 0; k < 4; k++) o.L[k] = -o.L[k];
-                sub_mul2(K, src[im].U, o.M);
-                sub_mulR(K, src[im].R, o.R);
-                inv2(src[ip].M, Mi);
-                mul2(e.U, Mi, K);             // K2 = U_i M_ip^-1
-                mul2(K, src[ip].U, o.U);
-                for (int k = 0; k < 4; k++) o.U[k] = -o.U[k];
-                sub_mul2(K, src[ip].L, o.M);
-                sub_mulR(K, src[ip].R, o.R);
+                mul2(e.L, src[im].L, L);
+                mul2(e.U, src[ip].U, U);
+                for (int k = 0; k < 4; k++) { L[k] = -L[k]; U[k] = -U[k]; }
+                sub_mul2(e.L, src[im].U, M);
+                sub_mul2(e.U, src[ip].L, M);
+                sub_mulR(e.L, src[im].R, R);
+                sub_mulR(e.U, src[ip].R, R);
             }
+            scale_row(M, L, U, R, dst[i]);
         }
         __syncthreads();
         Blk *t = src; src = dst; dst = t;
-        d *= 2;
+        dm *= 2;
+        if (dm >= n) dm -= n;
     }
     for (int k = threadIdx.x; k < n; k += blockDim.x) {
-        double Mi[4];
-        inv2(src[k].M, Mi);
 #pragma unroll
         for (int q = 0; q < 3; q++) {
-            const double r0 = src[k].R[q], r1 = src[k].R[3 + q];
-            D[3 * (b0 + k) + q] = Mi[0] * r0 + Mi[1] * r1;
-            S[3 * (b0 + k) + q] = Mi[2] * r0 + Mi[3] * r1;
+            D[3 * (b0 + k) + q] = src[k].R[q];
+            S[3 * (b0 + k) + q] = src[k].R[3 + q];
         }
     }
 }
@@ -323,21 +334,23 @@ __device__ __forceinline__ void geometry_seg(int j, int jn, double g, int Q, con
     SegPoly<ORDER> sp;
     sp.load(x, xn, j, D, sdd, j, jn, h);
     if constexpr (ORDER == 4) {
+        const double ih = rcp_nr(h), f = 2.0 * ih * ih;
 #pragma unroll
-        for (int q = 0; q < 3; q++) sdd[3 * j + q] = 2.0 * sp.c[2][q] / (h * h);
+        for (int q = 0; q < 3; q++) sdd[3 * j + q] = f * sp.c[2][q];
     }
     double len = 0.0;
     for (int i = 0; i < Q; i++) {
-        double u = gl.h[i], p[3], der[3];
+        const double u = gl.h[i], gw = g * gl.w[i];
+        double p[3], der[3];
         sp.pos(u, p);
-        sp.der(u, der);
+        sp.der(u, der);   // ds/du = h ds/dtau: charge Gamma w h ds/dtau
 #pragma unroll
         for (int q = 0; q < 3; q++) {
-            der[q] /= h;
             qpos[3 * (j * Q + i) + q] = p[q];
-            qchg[3 * (j * Q + i) + q] = g * gl.w[i] * h * der[q];
+            qchg[3 * (j * Q + i) + q] = gw * der[q];
         }
-        len += gl.w[i] * h * sqrt(der[0] * der[0] + der[1] * der[1] + der[2] * der[2]);
+        const double d2 = der[0] * der[0] + der[1] * der[1] + der[2] * der[2];
+        len += gl.w[i] * sqrt(d2);
     }
     ell[j] = len;
 }
@@ -517,8 +530,9 @@ __global__ __launch_bounds__(256) void k_local_self(int N, LocalArgs la, const d
 // SIMD; 82 without, five), so inputs that need more wavefronts than that
 // leave it to k_local_self, one thread per node (1e6 nodes in 1e4 filaments:
 // 0.40 -> 0.29 ms for both launches); the others keep the single launch.
-template <int ORDER, bool LOCAL>
-__global__ __launch_bounds__(128) void k_filament(int nfil, const int *__restrict__ off, const double *xs,
+// KEYS: form the bin sorts' keys and counts (not on the direct path).
+template <int ORDER, bool LOCAL, bool KEYS>
+__global__ __launch_bounds__(128) void k_filament(int nfil, const int *__restrict__ off, StagePos xs,
                            double *xd, double *__restrict__ xn,
                            const double *__restrict__ shift,
                            const double *__restrict__ gs, double *__restrict__ gd,
@@ -540,33 +554,35 @@ __global__ __launch_bounds__(128) void k_filament(int nfil, const int *__restric
         geometry_seg<ORDER>(b0 + k, b0 + (k + 1 == n ? 0 : k + 1), g, la.Q, gl, xd, xn, dtau, D,
                             qpos, qchg, sdd, ell);
     __syncthreads();
-    // bin keys and counts of the filament's quadrature points (spread tile,
-    // pair cell) and nodes (pair cell); whole-workgroup trip counts, as the
-    // counting is wavefront-aggregated
-    const int nq = n * la.Q;
-    for (int t0 = 0; t0 < nq; t0 += blockDim.x) {
-        const int t = t0 + threadIdx.x;
-        const bool act = t < nq;
-        const int qi = b0 * la.Q + t;
-        int k0 = 0, k1 = 0;
-        if (act) {
-            k0 = tile_key(qpos + 3 * qi, bk.L, bk.inv_h, bk.w, bk.n, bk.T, bk.NT);
-            k1 = cell_key(qpos + 3 * qi, bk.L, bk.ncx, bk.ncy);
-            bk.key[0][qi] = k0;
-            bk.key[1][qi] = k1;
+    if constexpr (KEYS) {
+        // bin keys and counts of the filament's quadrature points (spread tile,
+        // pair cell) and nodes (pair cell); whole-workgroup trip counts, as the
+        // counting is wavefront-aggregated
+        const int nq = n * la.Q;
+        for (int t0 = 0; t0 < nq; t0 += blockDim.x) {
+            const int t = t0 + threadIdx.x;
+            const bool act = t < nq;
+            const int qi = b0 * la.Q + t;
+            int k0 = 0, k1 = 0;
+            if (act) {
+                k0 = tile_key(qpos + 3 * qi, bk.L, bk.inv_h, bk.w, bk.n, bk.T, bk.NT);
+                k1 = cell_key(qpos + 3 * qi, bk.L, bk.ncx, bk.ncy);
+                bk.key[0][qi] = k0;
+                bk.key[1][qi] = k1;
+            }
+            wave_add<false>(bk.cnt[0], k0, act);
+            wave_add<false>(bk.cnt[1], k1, act);
         }
-        wave_add<false>(bk.cnt[0], k0, act);
-        wave_add<false>(bk.cnt[1], k1, act);
-    }
-    for (int t0 = 0; t0 < n; t0 += blockDim.x) {
-        const int t = t0 + threadIdx.x;
-        const bool act = t < n;
-        int k2 = 0;
-        if (act) {
-            k2 = cell_key(xd + 3 * (b0 + t), bk.L, bk.nc, bk.nc);
-            bk.key[2][b0 + t] = k2;
+        for (int t0 = 0; t0 < n; t0 += blockDim.x) {
+            const int t = t0 + threadIdx.x;
+            const bool act = t < n;
+            int k2 = 0;
+            if (act) {
+                k2 = cell_key(xd + 3 * (b0 + t), bk.L, bk.nc, bk.nc);
+                bk.key[2][b0 + t] = k2;
+            }
+            wave_add<false>(bk.cnt[2], k2, act);
         }
-        wave_add<false>(bk.cnt[2], k2, act);
     }
     if constexpr (LOCAL) {
         for (int k = threadIdx.x; k < n; k += blockDim.x)
@@ -574,6 +590,169 @@ __global__ __launch_bounds__(128) void k_filament(int nfil, const int *__restric
                                    b0 + (k + 1 == n ? 0 : k + 1), g, la, xd, xn, dtau, D, sdd,
                                    ell, qpos, qchg, vls);
     }
+}
+
+// The same for the direct path (filaments of at most kDirectFil nodes), with
+// everything between the stages in LDS and the arrays written at the end: a
+// barrier then waits for LDS alone, where the kernel above waits for global
+// stores and loads back at every stage (on one
+// 64-node ring: launch 1.4, chords 1.7, spline 3.5, geometry 0.5, local terms 2,
+// kernel values 4.3, records and stores 2 us; on the 64^3 ellipses it takes 16 us
+// where the kernel above and the gather took 15 + 6.5 and the sorts 14).
+// Four lanes per node share the local - self term; the kernel values of the
+// spread and the records of the pair sums are written here too.
+template <int ORDER>
+struct FilLds {
+    static constexpr int M = kDirectFil;
+    double x[3 * M], xn[3 * M], h[M], D[3 * M], S[3 * M], ell[M];
+    double qp[3 * kMaxQ * M], qc[3 * kMaxQ * M];
+};
+
+// velocity's local - self term of node k (neighbours km, kp): lanes 0, 1 of
+// the four take the segment before the node, lanes 2, 3 the one after it, each
+// lane every other quadrature point of its segment; the sum ends in all four
+template <int ORDER>
+__device__ __forceinline__ void local_self_quad(int k, int km, int kp, double g,
+                                                const LocalArgs &la, const FilLds<ORDER> &F,
+                                                double *acc) {
+    const int sub4 = threadIdx.x & 3, side = sub4 >> 1, odd = sub4 & 1, Q = la.Q;
+    const double inv4pi = 1.0 / (4.0 * kPi), eps = la.eps, alpha = la.alpha;
+    const int j = side ? k : km, jn = side ? kp : k;
+    const double *xi = side ? F.x + 3 * k : F.xn + 3 * km;
+    double l = F.ell[j];
+    acc[0] = acc[1] = acc[2] = 0.0;
+    if (eps < 1.0) {
+        SegPoly<ORDER> seg;
+        seg.load(F.x, F.xn, j, F.D, F.S, j, jn, F.h[j]);
+        l = 0.0;
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            double dv[3];
+            seg.der(side ? kG3h[q] * eps : 1.0 - eps + kG3h[q] * eps, dv);
+            const double d2 = dv[0] * dv[0] + dv[1] * dv[1] + dv[2] * dv[2];
+            l += kG3w[q] * eps * (d2 * rsqrt_nr(d2));
+        }
+        // the rest of the segment, distance u from the node in [eps, 1]
+        int t = 0;
+        for (double u0 = eps; u0 < 1.0; u0 *= 2.0) {
+            const double u1 = fmin(2.0 * u0, 1.0);
+            for (int q = 0; q < 3; q++, t++) {
+                if ((t & 1) != odd) continue;
+                const double uu = u0 + kG3h[q] * (u1 - u0), u = side ? uu : 1.0 - uu;
+                double p[3], dv[3], r[3];
+                seg.pos(u, p);
+                seg.der(u, dv);   // ds/du: ds = dv du
+                for (int c = 0; c < 3; c++) r[c] = p[c] - xi[c];
+                const double ir = rsqrt_nr(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+                const double f = g * kG3w[q] * (u1 - u0) * inv4pi * (ir * ir * ir);
+                acc[0] += f * (r[1] * dv[2] - r[2] * dv[1]);
+                acc[1] += f * (r[2] * dv[0] - r[0] * dv[2]);
+                acc[2] += f * (r[0] * dv[1] - r[1] * dv[0]);
+            }
+        }
+    }
+    for (int q = odd; q < Q; q += 2) {
+        const double *p = F.qp + 3 * (j * Q + q), *ch = F.qc + 3 * (j * Q + q);
+        double r[3];
+        for (int c = 0; c < 3; c++) r[c] = p[c] - xi[c];
+        const double rr = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+        const double f = inv4pi * alpha * alpha * alpha * glr_over_x3(alpha * rr);
+        acc[0] -= f * (r[1] * ch[2] - r[2] * ch[1]);
+        acc[1] -= f * (r[2] * ch[0] - r[0] * ch[2]);
+        acc[2] -= f * (r[0] * ch[1] - r[1] * ch[0]);
+    }
+    const double l2 = __shfl_xor(l, 2);
+    if (sub4 == 0) {
+        const double *sd = F.D + 3 * k, *s2 = F.S + 3 * k;
+        const double in = rsqrt_nr(sd[0] * sd[0] + sd[1] * sd[1] + sd[2] * sd[2]);
+        const double lg = log(2.0 * sqrt(l * l2) / la.a);
+        const double f = g * inv4pi * (lg - la.delta) * (in * in * in);
+        acc[0] += f * (sd[1] * s2[2] - sd[2] * s2[1]);
+        acc[1] += f * (sd[2] * s2[0] - sd[0] * s2[2]);
+        acc[2] += f * (sd[0] * s2[1] - sd[1] * s2[0]);
+    }
+#pragma unroll
+    for (int m = 1; m <= 2; m <<= 1)
+#pragma unroll
+        for (int c = 0; c < 3; c++) acc[c] += __shfl_xor(acc[c], m);
+}
+
+template <int ORDER>
+__global__ __launch_bounds__(256) void k_filament_direct(
+    const int *__restrict__ off, StagePos xs, double *__restrict__ xd, double *__restrict__ xn,
+    const double *__restrict__ shift, const double *__restrict__ gs, double *__restrict__ gd,
+    double *__restrict__ dtau, double *__restrict__ D, double *__restrict__ sdd,
+    double *__restrict__ qpos, double *__restrict__ qchg, double *__restrict__ ell,
+    int *__restrict__ status, double *__restrict__ gscratch, GLArgs gl, LocalArgs la,
+    double *__restrict__ vls, DirectOut dx) {
+    __shared__ FilLds<ORDER> F;
+    const int f = blockIdx.x, b0 = off[f], n = off[f + 1] - b0, Q = la.Q;   // n <= kDirectFil
+    const int tid = threadIdx.x;
+    const double g = gs[f];
+    for (int i = tid; i < 3 * n; i += blockDim.x) F.x[i] = xs[3 * b0 + i];
+    __syncthreads();
+    for (int k = tid; k < n; k += blockDim.x) {
+        const bool last = k + 1 == n;
+        const double *x0 = F.x + 3 * k, *x1 = F.x + (last ? 0 : 3 * (k + 1));
+        double e[3];
+        bool ok = true;
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            e[q] = x1[q] + (last && shift ? shift[3 * f + q] : 0.0);
+            F.xn[3 * k + q] = e[q];
+            ok = ok && isfinite(x0[q]);
+        }
+        const double d0 = e[0] - x0[0], d1 = e[1] - x0[1], d2 = e[2] - x0[2];
+        const double h = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+        ok = ok && isfinite(h) && h > 0.0;
+        if (!ok) atomicOr(status, 1);
+        F.h[k] = ok ? h : 1.0;
+    }
+    __syncthreads();
+    if constexpr (ORDER == 4) spline_cubic_fil(0, n, F.x, F.xn, F.h, F.D, gscratch);
+    else spline_quintic_fil(0, n, F.x, F.xn, F.h, F.D, F.S, gscratch + (size_t)36 * b0);
+    __syncthreads();
+    for (int k = tid; k < n; k += blockDim.x)
+        geometry_seg<ORDER>(k, k + 1 == n ? 0 : k + 1, g, Q, gl, F.x, F.xn, F.h, F.D, F.qp, F.qc,
+                            F.S, F.ell);
+    __syncthreads();
+    for (int t0 = 0; t0 < 4 * n; t0 += blockDim.x) {   // whole wavefronts: the lanes exchange
+        const int kk = (t0 + tid) >> 2, k = kk < n ? kk : n - 1;
+        double acc[3];
+        local_self_quad<ORDER>(k, k == 0 ? n - 1 : k - 1, k + 1 == n ? 0 : k + 1, g, la, F, acc);
+        const int c = tid & 3;
+        if (kk < n && c < 3) vls[3 * (b0 + k) + c] = c == 0 ? acc[0] : (c == 1 ? acc[1] : acc[2]);
+    }
+    const int nq = n * Q, q0 = b0 * Q, w = dx.w;
+    const float iw = 1.0f / (float)w;
+    // several at a time: one wavefront per SIMD here, so independent chains
+    // are what hides the latency of each
+#pragma unroll 4
+    for (int t = tid; t < nq * 3 * w; t += blockDim.x) {
+        const int pa = (int)(((float)t + 0.5f) * iw);   // t / w: exact for t < 2^15
+        dx.ker[(size_t)q0 * 3 * w + t] = direct_value(F.qp[pa], t - pa * w, dx);
+    }
+    for (int t = tid; t < nq; t += blockDim.x)
+        direct_point(q0 + t, b0 + t / Q, F.qp + 3 * t, F.qc + 3 * t, dx);
+    for (int j = tid >> 6; j * kPiece < n; j += blockDim.x >> 6)
+        direct_piece(dx.piece + dx.pfirst[f] + j, F.qp + 3 * j * kPiece * Q, q0 + j * kPiece * Q,
+                     min(kPiece, n - j * kPiece) * Q, dx.L);
+    for (int k = tid; k < n; k += blockDim.x) {
+        direct_node(b0 + k, b0 + (k == 0 ? n - 1 : k - 1), F.x + 3 * k, dx);
+        dtau[b0 + k] = F.h[k];
+        ell[b0 + k] = F.ell[k];
+    }
+    for (int i = tid; i < 3 * n; i += blockDim.x) {
+        xd[3 * b0 + i] = F.x[i];
+        xn[3 * b0 + i] = F.xn[i];
+        D[3 * b0 + i] = F.D[i];
+        sdd[3 * b0 + i] = F.S[i];
+    }
+    for (int i = tid; i < 3 * nq; i += blockDim.x) {
+        qpos[3 * q0 + i] = F.qp[i];
+        qchg[3 * q0 + i] = F.qc[i];
+    }
+    if (tid == 0) gd[f] = g;
 }
 
 // ------------------------------------------------------------------ launch
@@ -600,26 +779,40 @@ static LocalArgs local_args(bs_plan_t p, int mode, double sign) {
 constexpr int64_t kFilamentSplitNodes = 16384;
 constexpr int64_t kFilamentSplitFils = 1024;
 
-void launch_filaments(bs_plan_t p, const double *xyz, const double *gamma) {
+void launch_filaments(bs_plan_t p, const double *xyz, const double *kstage, double c,
+                      const double *gamma) {
     if (p->N == 0) return;
     GLRule r = gl_rule(p->Q);
     GLArgs g;
     for (int i = 0; i < kMaxQ; i++) { g.h[i] = r.h[i]; g.w[i] = r.w[i]; }
     const LocalArgs la = local_args(p, LS_VLOCAL | LS_VSELF | LS_ASSIGN, 1.0);
-    const bool split = p->N >= kFilamentSplitNodes &&
+    const StagePos xs{xyz, kstage, c};
+    const int *off = (const int *)p->d_off.p;
+    const double *shift = p->nper ? (const double *)p->d_shift.p : nullptr;
+    double *xd = (double *)p->d_x.p, *xn = (double *)p->d_xn.p, *gd = (double *)p->d_gamma.p,
+           *dtau = (double *)p->d_dtau.p, *D = (double *)p->d_D.p, *sdd = (double *)p->d_sdd.p,
+           *qpos = (double *)p->d_qpos.p, *qchg = (double *)p->d_qchg.p,
+           *ell = (double *)p->d_ell.p, *tmp = (double *)p->spline_tmp.p,
+           *vls = (double *)p->d_vls.p;
+    int *status = (int *)p->d_status.p;
+    const dim3 grid((unsigned)p->nfil);
+    const bool quintic = p->order == 6;
+    if (p->direct && p->max_fil_nodes <= kDirectFil) {
+        auto kern = quintic ? k_filament_direct<6> : k_filament_direct<4>;
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, p->stream, off, xs, xd, xn, shift, gamma, gd,
+                           dtau, D, sdd, qpos, qchg, ell, status, tmp, g, la, vls, direct_out(p));
+        return;
+    }
+    const bool split = !p->direct && p->N >= kFilamentSplitNodes &&
                        (p->nfil > kFilamentSplitFils || p->N > kFilamentSplitFils * p->nfil);
-    auto kern = p->order == 6 ? (split ? k_filament<6, false> : k_filament<6, true>)
-                              : (split ? k_filament<4, false> : k_filament<4, true>);
-    hipLaunchKernelGGL(kern, dim3((unsigned)p->nfil), dim3(p->order == 6 ? 64 : 128), 0,
-                       p->stream, (int)p->nfil, (const int *)p->d_off.p, xyz,
-                       (double *)p->d_x.p, (double *)p->d_xn.p,
-                       p->nper ? (const double *)p->d_shift.p : nullptr, gamma,
-                       (double *)p->d_gamma.p,
-                       (double *)p->d_dtau.p, (double *)p->d_D.p, (double *)p->d_sdd.p,
-                       (double *)p->d_qpos.p, (double *)p->d_qchg.p, (double *)p->d_ell.p,
-                       (int *)p->d_status.p, (double *)p->spline_tmp.p, g, la,
-                       (double *)p->d_vls.p, bin_keys(p));
-    if (split) launch_local_self(p, LS_VLOCAL | LS_VSELF | LS_ASSIGN, 1.0, (double *)p->d_vls.p);
+    auto kern = p->direct ? (quintic ? k_filament<6, true, false> : k_filament<4, true, false>)
+                : split   ? (quintic ? k_filament<6, false, true> : k_filament<4, false, true>)
+                          : (quintic ? k_filament<6, true, true> : k_filament<4, true, true>);
+    hipLaunchKernelGGL(kern, grid, dim3(quintic ? 64 : 128), 0, p->stream, (int)p->nfil, off, xs, xd,
+                       xn, shift, gamma, gd, dtau, D, sdd, qpos, qchg, ell, status, tmp, g, la, vls,
+                       bin_keys(p));
+    if (p->direct) launch_direct_gather(p);
+    if (split) launch_local_self(p, LS_VLOCAL | LS_VSELF | LS_ASSIGN, 1.0, vls);
 }
 
 void launch_spline_data(bs_plan_t p, const double *data, double *Dout, double *Sout) {

@@ -53,22 +53,6 @@ namespace bs {
 // run on one XCD), so neighbouring tiles, which share candidate bins and the
 // cache lines of their grid rows, go through the same L2.
 //
-template <typename R> struct Mfma4;
-template <> struct Mfma4<double> {
-    typedef double V __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ V op(double a, double b, V c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ constexpr int row(int k4, int v) { return k4 + 4 * v; }
-};
-template <> struct Mfma4<float> {
-    typedef float V __attribute__((ext_vector_type(4)));
-    static __device__ __forceinline__ V op(float a, float b, V c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ constexpr int row(int k4, int v) { return 4 * k4 + v; }
-};
-
 template <typename R, int W, int TT, int WAVES, bool MMA>
 __global__ __launch_bounds__(64 * WAVES) void k_spread(int n, int NT, int nbv, int per_xcd,
                                                        const int *__restrict__ start,
@@ -400,6 +384,10 @@ static void spread_tt(bs_plan_t p) {
 }
 
 void launch_spread(bs_plan_t p) {
+    if (p->direct) {
+        launch_spread_direct(p);
+        return;
+    }
     if (p->fp32) {
         if (p->T == 8) spread_tt<float, 8>(p); else spread_tt<float, 4>(p);
     } else {
@@ -533,7 +521,7 @@ void launch_modes(bs_plan_t p, double *out) {
 template <typename R, int W, int G, bool IL>
 __global__ __launch_bounds__(256) void k_interp(int N, int per_xcd,
                                                 const double4 *__restrict__ tgt,
-                                                double inv_h, int n, double zeta, double inv_den,
+                                                double inv_h, int n, KbPhi kb,
                                                 const R *__restrict__ grid,
                                                 const double *__restrict__ base,
                                                 double *__restrict__ out) {
@@ -552,7 +540,7 @@ __global__ __launch_bounds__(256) void k_interp(int N, int per_xcd,
     R phi = (R)0;
     if (lane < 3 * W) {
         const int a = lane / W, k = lane % W;
-        phi = (R)kb_phi((k - f[a]) / half, zeta, inv_den);
+        phi = kb_value<R>((k - f[a]) / half, kb);
     }
     R pz[W];
     int iz[W];
@@ -621,15 +609,14 @@ static void interp_r(bs_plan_t p, const double *base, double *out) {
     const int N = (int)p->N;
     const int nblk = ceil_div((int64_t)N * kInterpLanes, 256), per = ceil_div(nblk, 8);
     dim3 grid(8 * per), block(256);
-    const double L = p->prm.L, inv_h = p->n / L, zeta = p->prm.zeta;
-    const double inv_den = 1.0 / (-expm1(-2.0 * zeta));
+    const double L = p->prm.L, inv_h = p->n / L;
     const double4 *tgt = (const double4 *)p->nd_rec.p;
     const R *g = (const R *)p->grid.p;
     const bool il = grid_interleaved(p);
 #define INTERP_CASE(WW) \
     case WW: \
-        if (il) hipLaunchKernelGGL((k_interp<R, WW, kInterpLanes, true>), grid, block, 0, p->stream, N, per, tgt, inv_h, p->n, zeta, inv_den, g, base, out); \
-        else hipLaunchKernelGGL((k_interp<R, WW, kInterpLanes, false>), grid, block, 0, p->stream, N, per, tgt, inv_h, p->n, zeta, inv_den, g, base, out); \
+        if (il) hipLaunchKernelGGL((k_interp<R, WW, kInterpLanes, true>), grid, block, 0, p->stream, N, per, tgt, inv_h, p->n, p->kb, g, base, out); \
+        else hipLaunchKernelGGL((k_interp<R, WW, kInterpLanes, false>), grid, block, 0, p->stream, N, per, tgt, inv_h, p->n, p->kb, g, base, out); \
         break;
     switch (p->prm.w) {
         INTERP_CASE(4) INTERP_CASE(5) INTERP_CASE(6) INTERP_CASE(7) INTERP_CASE(8)

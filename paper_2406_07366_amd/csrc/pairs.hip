@@ -19,64 +19,11 @@
 
 #include "bs_internal.h"
 #include "bs_device.h"
-#include "erfcx_fit.h"
+#include "direct.h"
 
 namespace bs {
 
-// g_sr(x) = erfc(x) + (2/sqrt(pi)) x exp(-x^2) = exp(-x^2) (erfcx(x) +
-// (2/sqrt(pi)) x): one exponential, with erfcx = P(Z) / (4 + x),
-// Z = (4 - x) / (4 + x), from its fitted polynomial (float64: relative
-// error 3e-15 for x = alpha r below the beta of every tolerance in Table 1,
-// 7e-14 where the term is below 1e-15 of its value at r = 0; float32:
-// 4e-7, below the float32 rounding of exp(-x^2) for x near beta)
-// float64: the polynomials' coefficients come as a kernel argument, so that they
-// sit in scalar registers: as literals they took 130 moves per target and 50
-// vector registers.  exp(y), y <= 0: y = n ln 2 + r, |r| <= ln 2 / 2, Taylor
-// polynomial of degree 13 (remainder below 5e-18).
-constexpr int kExpDeg = 13;
-struct ShortFit {
-    double p[kErfcxDeg + 1];
-    double e[kExpDeg + 1];   // 1 / k!
-    double log2e, ln2_hi, ln2_lo;
-};
-// scalars of the cell list, formed once on the host
-struct PairGeom {
-    double L, invL, rc2, rm, alpha;
-    double fx, fy;          // cells per length along x and along y, z
-    float ry, ratio;        // r_c in y cells with the margin, x cells per y cell
-    int ncx, ncy;
-};
-static ShortFit short_fit() {
-    ShortFit F;
-    for (int k = 0; k <= kErfcxDeg; k++) F.p[k] = kErfcxP[k];
-    double f = 1.0;
-    for (int k = 0; k <= kExpDeg; k++) {
-        if (k > 1) f *= k;
-        F.e[k] = 1.0 / f;
-    }
-    F.log2e = 1.44269504088896340735992468100189214;   // 1 / ln 2
-    F.ln2_hi = 0.693147180559945309417232121458176568; // ln 2 rounded, and the rest
-    F.ln2_lo = 2.31904681384629955842017e-17;
-    return F;
-}
-template <bool PSI>
-__device__ __forceinline__ double g_short64(double x, const ShortFit &F) {
-    constexpr double two_over_sqrtpi = 1.12837916709551257389615890312154517;
-    const double inv = rcp_nr(kErfcxShift + x);
-    const double z = (kErfcxShift - x) * inv;
-    double p = F.p[kErfcxDeg];
-#pragma unroll
-    for (int k = kErfcxDeg - 1; k >= 0; k--)
-        p = fma(p, z, F.p[k]);
-    const double y = -x * x, n = rint(y * F.log2e);
-    const double r = fma(-n, F.ln2_lo, fma(-n, F.ln2_hi, y));
-    double e = F.e[kExpDeg];
-#pragma unroll
-    for (int k = kExpDeg - 1; k >= 0; k--) e = fma(e, r, k < 2 ? 1.0 : (k == 2 ? 0.5 : F.e[k]));
-    e = ldexp(e, (int)n);
-    // psi: erfc(x) = exp(-x^2) erfcx(x)
-    return PSI ? e * (p * inv) : e * fma(p, inv, two_over_sqrtpi * x);
-}
+// float32 form of the short-range factor (pairs64.h)
 __device__ __forceinline__ float g_short(float x) {
     constexpr float two_over_sqrtpi = 1.12837916709551257389615890312154517f;
     const float inv = __builtin_amdgcn_rcpf((float)kErfcxShift + x);
@@ -272,7 +219,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // which the edges leave room.  One cell when fewer fit, and larger cells when
 // there would be more than one per point (their counting sort would cost more
 // than the tests they save).  float32 keeps ncell^3.
-constexpr float kRowMargin = 1e-4f;
 void pair_cells(bs_plan_t p, int64_t Nq, int *ncx, int *ncy) {
     *ncx = *ncy = p->nc;
     if (p->fp32) return;
@@ -283,57 +229,62 @@ void pair_cells(bs_plan_t p, int64_t Nq, int *ncx, int *ncy) {
     *ncx = *ncy == 1 ? 1 : (int)std::floor(std::min(3.0 * q, 1.5 * ny));
 }
 
-// accepted candidates queued per wavefront (a ring of two steps' worth)
-constexpr int kQueue = 128;
-// candidates per chunk (start marks in LDS, one byte each)
-constexpr int kMarkCap = 1024;
+PairGeom pair_geom(bs_plan_t p) {
+    const double L = p->prm.L, rc = p->prm.rcut;
+    PairGeom G;
+    G.L = L; G.invL = 1.0 / L; G.rc2 = rc * rc; G.rm = rc * (1.0 + 1e-9); G.alpha = p->prm.alpha;
+    G.fx = p->ncx / L; G.fy = p->ncy / L;
+    G.ry = (float)(rc * G.fy) + kRowMargin;
+    G.ratio = (float)p->ncx / (float)p->ncy;
+    G.ncx = p->ncx; G.ncy = p->ncy;
+    return G;
+}
+
+ShortFit short_fit() {
+    ShortFit F;
+    for (int k = 0; k <= kErfcxDeg; k++) F.p[k] = kErfcxP[k];
+    double f = 1.0;
+    for (int k = 0; k <= kExpDeg; k++) {
+        if (k > 1) f *= k;
+        F.e[k] = 1.0 / f;
+    }
+    F.log2e = 1.44269504088896340735992468100189214;   // 1 / ln 2
+    F.ln2_hi = 0.693147180559945309417232121458176568; // ln 2 rounded, and the rest
+    F.ln2_lo = 2.31904681384629955842017e-17;
+    return F;
+}
 
 // One wavefront (four on small inputs) per target node.  Lane r < 25 holds
 // row (iy, iz) of cells, cut along x to the cells that meet the sphere around
 // the target (so ~44 % of the candidates lie within r_c, against 31 % for the
 // 4 x 4 x 4 cells of edge 2 r_c / 3 near it); lane 32 + r the part of that row
-// beyond the periodic boundary.  A row's cells are one range of points, and
-// the ranges are enumerated as one flattened range: a mark at each range's
-// start, so that a candidate's range is the number of marks up to it (one
-// ballot and a bit count per 64 candidates).  The separations of the points within r_c
-// are queued in LDS and their exp / polynomial terms evaluated 64 at a time,
-// so that the costly part runs with every lane busy.  Bound by vector issue
-// (~560 instructions per target of ~230 candidates and ~100 terms on the 1e6-node
-// tangle: 2.42 -> 1.20 ms alone, 243 -> 121 us on 1e5 nodes; before, the cells
-// of edge 2 r_c / 3, target set-up by divisions and a map of every candidate
-// in LDS took ~950).  The partial sums are combined in a fixed order (deterministic).
+// beyond the periodic boundary.  A row's cells are one range of points
+// (PairScan).  The separations of the points within r_c are queued in LDS and
+// their exp / polynomial terms evaluated 64 at a time, so that the costly part
+// runs with every lane busy.  Bound by vector issue (~560 instructions per
+// target of ~230 candidates and ~100 terms on the 1e6-node tangle: 2.42 -> 1.20 ms
+// alone, 243 -> 121 us on 1e5 nodes; before, the cells of edge 2 r_c / 3, target
+// set-up by divisions and a map of every candidate in LDS took ~950).  The
+// partial sums are combined in a fixed order (deterministic).
 template <bool PSI, int WPN>
 __global__ __launch_bounds__(256) void k_pairs64(
     int N, int per_xcd, PairGeom G, const double4 *__restrict__ tgt, const int *__restrict__ cstart,
     const double4 *__restrict__ spos, const double4 *__restrict__ schg, ShortFit fit,
     const double *__restrict__ base, double *__restrict__ out) {
     static_assert(WPN == 1 || WPN == 4, "1 or 4 wavefronts per target");
-    __shared__ double red[4][3];
-    __shared__ __attribute__((aligned(16))) unsigned char mark_s[4][kMarkCap];
-    __shared__ int delta_s[4][64];
-    __shared__ double qbuf[4][3][kQueue];
-    __shared__ int qpid[4][kQueue];
+    __shared__ PairLds lds;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // targets in cell order, consecutive workgroups of them on one XCD (see
-    // k_pairs); WPN = 4: one target, its candidate steps dealt round-robin
+    // k_pairs)
     const int blk = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
     const int t = WPN == 1 ? blk * 4 + wave : blk;
-    const int part = WPN == 1 ? 0 : wave;
     if (t >= N) return;   // whole wavefronts (WPN = 1) or the whole workgroup
-    const double4 tg = tgt[t];   // wrapped position; node and its predecessor
-    const int o = __double2loint(tg.w);
-    const double od = (double)o, pd = (double)__double2hiint(tg.w);
-    const double w0 = tg.x, w1 = tg.y, w2 = tg.z;
-    unsigned char *mark = mark_s[wave];
-    static_assert(kMarkCap == 64 * 16, "a lane clears 16 marks");
-    *(uint4 *)(mark + 16 * lane) = make_uint4(0, 0, 0, 0);
-    int cs = 0, cn = 0;
-    bool inside = false;   // the sphere lies inside the box (wavefront-uniform)
-    const double L = G.L, invL = G.invL, rc2 = G.rc2, alpha = G.alpha;
+    PairScan<PSI, WPN> P(lds, tgt[t], G, spos, schg, fit);
     const int ncx = G.ncx, ncy = G.ncy;
+    int cs = 0, cn = 0;
     if (ncy >= 5) {
         const int r = lane & 31, iz = (r * 13) >> 6, iy = r - 5 * iz;   // r / 5 for r < 32
-        const float cx = (float)(w0 * G.fx), cy = (float)(w1 * G.fy), cz = (float)(w2 * G.fy);
+        const float cx = (float)(P.w0 * G.fx), cy = (float)(P.w1 * G.fy), cz = (float)(P.w2 * G.fy);
         const float ry = G.ry;
         int jy = (int)floorf(cy - ry) + iy, jz = (int)floorf(cz - ry) + iz;
         // distance from the target to the row's extent in y and z
@@ -356,110 +307,24 @@ __global__ __launch_bounds__(256) void k_pairs64(
                 cn = cstart[row + b + 1] - cs;
             }
         }
-        const double rm = G.rm;
-        inside = w0 >= rm && w1 >= rm && w2 >= rm && w0 + rm < L && w1 + rm < L && w2 + rm < L;
     } else if (lane == 0) {
         cn = cstart[ncx * ncy * ncy];
     }
-    const int incl = wave_incl_sum(cn);
-    const int total = __builtin_amdgcn_readlane(incl, 63);
-    const int excl = incl - cn;
-    double acc0 = 0, acc1 = 0, acc2 = 0;
-    int *qp = qpid[wave], *delta = delta_s[wave];
-    double *qx = qbuf[wave][0], *qy = qbuf[wave][1], *qz = qbuf[wave][2];
-    // the ranges in order: point = candidate + delta[range]
-    {
-        const unsigned long long m = __ballot(cn > 0);
-        if (cn > 0) delta[__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                                    __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = cs - excl;
-    }
-    // ring of accepted candidates, positions [head, tail)
-    // (wavefront-uniform); the terms of n <= 64 queued ones, one per lane
-    int head = 0, tail = 0;
-    auto drain = [&](int n) {
-        if (lane < n) {
-            const int sl = (head + lane) & (kQueue - 1);
-            const double4 q = schg[qp[sl]];
-            const double fx = qx[sl], fy = qy[sl], fz = qz[sl];
-            const double r2 = fx * fx + fy * fy + fz * fz;
-            const double ir = rsqrt_nr(r2);
-            const double g = g_short64<PSI>(alpha * (r2 * ir), fit);
-            if (PSI) {
-                const double f = g * ir;
-                acc0 += f * q.x; acc1 += f * q.y; acc2 += f * q.z;
-            } else {
-                const double f = g * (ir * ir * ir);
-                acc0 += f * (fy * q.z - fz * q.y);
-                acc1 += f * (fz * q.x - fx * q.z);
-                acc2 += f * (fx * q.y - fy * q.x);
-            }
-        }
-        head += n;
-    };
-    int seen = -1;   // ranges begun before the step, minus one
-    for (int c0 = 0; c0 < total; c0 += kMarkCap) {
-        const int cend = min(total, c0 + kMarkCap);
-        const bool mine = cn > 0 && excl >= c0 && excl < cend;
-        if (mine) mark[excl - c0] = 1;
-        wave_lds_sync();
-        // 64 candidates a step: separation (minimum image), the node's two
-        // adjacent segments excluded, those within r_c queued in order
-        for (int qb = c0, st = 0; qb < cend; qb += 64, st++) {
-            const int q = qb + lane;
-            const bool mk = mark[q - c0] != 0;
-            const unsigned long long mm = __ballot(mk);
-            const int rg = seen + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mm >> 32),
-                                    __builtin_amdgcn_mbcnt_lo((unsigned)mm, 0u)) + (mk ? 1 : 0);
-            seen += __popcll(mm);
-            if (WPN > 1 && (st & (WPN - 1)) != part) continue;
-            const bool in = q < cend;
-            const int p = in ? q + delta[rg] : 0;
-            const double4 sp = spos[p];
-            double rx = sp.x - w0, ry = sp.y - w1, rz = sp.z - w2;
-            if (!inside) {
-                rx -= L * rint(rx * invL);
-                ry -= L * rint(ry * invL);
-                rz -= L * rint(rz * invL);
-            }
-            const double r2 = rx * rx + ry * ry + rz * rz;
-            const bool ok = in && sp.w != od && sp.w != pd && r2 < rc2 && r2 != 0.0;
-            const unsigned long long m = __ballot(ok);
-            if (ok) {
-                const int sl = (tail + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                       __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))) & (kQueue - 1);
-                qx[sl] = rx; qy[sl] = ry; qz[sl] = rz; qp[sl] = p;
-            }
-            tail += __popcll(m);
-            if (tail - head >= 64) {
-                wave_lds_sync();
-                drain(64);
-                wave_lds_sync();   // slots read before the next step writes them
-            }
-        }
-        wave_lds_sync();   // marks read before they are cleared
-        if (mine) mark[excl - c0] = 0;
-    }
-    wave_lds_sync();
-    drain(tail - head);   // fewer than 64 left
-    acc0 = wave_total63(acc0);
-    acc1 = wave_total63(acc1);
-    acc2 = wave_total63(acc2);
-    if (WPN > 1) {
-        if (lane == 63) { red[wave][0] = acc0; red[wave][1] = acc1; red[wave][2] = acc2; }
-        __syncthreads();
-        if (wave != 0) return;
-        acc0 = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
-        acc1 = (red[0][1] + red[1][1]) + (red[2][1] + red[3][1]);
-        acc2 = (red[0][2] + red[1][2]) + (red[2][2] + red[3][2]);
-    }
-    if (lane == 63) {
-        const double inv4pi = 1.0 / (4.0 * kPi);
-        const double *b = base ? base : out;
-        const double b0 = b[3 * o], b1 = b[3 * o + 1], b2 = b[3 * o + 2];
-        out[3 * o] = b0 + acc0 * inv4pi;
-        out[3 * o + 1] = b1 + acc1 * inv4pi;
-        out[3 * o + 2] = b2 + acc2 * inv4pi;
-    }
+    P.ranges(cs, cn);
+    P.store(lds, base, out);
+}
+
+// The direct path (points and targets in index order, ranges from the pieces
+// of filaments near the target): WPN wavefronts per target.
+template <bool PSI, int WPN>
+__global__ __launch_bounds__(256) void k_pairs_direct(int N, PairGeom G, PieceList pl,
+                                                      const double4 *__restrict__ tgt,
+                                                      const double4 *__restrict__ spos,
+                                                      const double4 *__restrict__ schg, ShortFit fit,
+                                                      const double *__restrict__ base,
+                                                      double *__restrict__ out) {
+    __shared__ PairLds lds;
+    pairs_direct<PSI, WPN>(blockIdx.x, N, G, pl, tgt, spos, schg, fit, base, out, lds);
 }
 
 // targets below this count get four wavefronts each (latency hiding on
@@ -485,12 +350,14 @@ static void pairs_psi(bs_plan_t p, const double *base, double *out, bool alone) 
                            off, fil, cs, sp, (const float *)p->pq_chg.p, base, out);
     } else {
         auto kern = split ? k_pairs64<PSI, 4> : k_pairs64<PSI, 1>;
-        PairGeom G;
-        G.L = L; G.invL = 1.0 / L; G.rc2 = rc * rc; G.rm = rc * (1.0 + 1e-9); G.alpha = alpha;
-        G.fx = p->ncx / L; G.fy = p->ncy / L;
-        G.ry = (float)(rc * G.fy) + kRowMargin;
-        G.ratio = (float)p->ncx / (float)p->ncy;
-        G.ncx = p->ncx; G.ncy = p->ncy;
+        const PairGeom G = pair_geom(p);
+        if (p->direct) {
+            auto kern = alone ? k_pairs_direct<PSI, 4> : k_pairs_direct<PSI, 1>;
+            hipLaunchKernelGGL(kern, dim3(alone ? N : ceil_div(N, 4)), block, 0, p->stream, N,
+                               G, piece_list(p), (const double4 *)p->nd_rec.p, sp,
+                               (const double4 *)p->pq_chg.p, short_fit(), base, out);
+            return;
+        }
         hipLaunchKernelGGL(kern, grid, block, 0, p->stream, N, per, G, (const double4 *)p->nd_rec.p, cs, sp, (const double4 *)p->pq_chg.p,
                            short_fit(), base, out);
     }
