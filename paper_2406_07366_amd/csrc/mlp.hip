@@ -18,10 +18,14 @@
 // holds rows 4(l/16)..4(l/16)+3 of column l%16) is exactly the B-operand
 // layout of the next layer, so activations never leave registers in the
 // forward pass.  Backward: dH^T = W^T dZ^T by MFMA in the same orientation;
-// dW = dZ^T H by MFMA after a transpose of both 16-sample tiles through LDS.
-// Weight gradients are summed per workgroup (one wavefront, plain adds) and
-// the workgroup partials are added in a fixed order by a second kernel.
+// dW = dZ^T H by MFMA over a workgroup's samples, both factors transposed
+// through LDS, each wavefront owning a share of the output blocks in registers.
+// The workgroup partials are added in a fixed order by a second kernel, which
+// writes the gradient (or takes the Adam step).
+#include <algorithm>
+
 #include "bs_internal.h"
+#include "bs_device.h"
 
 namespace bs {
 
@@ -35,6 +39,10 @@ constexpr int kW1p = 0, kW2 = kW1p + 64 * 16, kW3 = kW2 + 64 * 64, kW4p = kW3 + 
 constexpr int kWpad = kW4p + 16 * 64;        // 10240 bf16 weights
 constexpr int kB1 = 0, kB2 = 64, kB3 = 128, kB4p = 192, kBpad = 208;   // fp32 biases
 constexpr int kGpad = kWpad + kBpad;         // padded gradient length (fp32)
+// the same image in LDS, rows padded by 4 elements against bank conflicts
+constexpr int kLd1 = 20, kLd = 68;
+constexpr int kL1 = 0, kL2 = kL1 + 64 * kLd1, kL3 = kL2 + 64 * kLd, kL4 = kL3 + 64 * kLd;
+constexpr int kLpad = kL4 + 16 * kLd;
 
 __device__ __forceinline__ unsigned short f2bf(float f) {
     unsigned int u = __float_as_uint(f);
@@ -90,14 +98,12 @@ __device__ __forceinline__ f32x4 mfma16(typename Prec<F>::Op a, typename Prec<F>
 }
 
 // A operand: 16x16 tile of a row-major matrix M (row stride ld), rows r0..,
-// columns c0..: lane l reads M[r0 + l%16][c0 + 4(l/16) .. +3].
+// columns c0..: lane l reads M[r0 + l%16][c0 + 4(l/16) .. +3] (M and ld
+// multiples of 4 elements: one 8- or 16-byte read).
 template <bool F>
 __device__ __forceinline__ typename Prec<F>::Op load_a(const typename Prec<F>::W *M, int ld,
                                                        int r0, int c0, int l) {
-    const typename Prec<F>::W *p = M + (r0 + (l & 15)) * ld + c0 + 4 * (l >> 4);
-    typename Prec<F>::Op v;
-    for (int r = 0; r < 4; r++) Prec<F>::set(v, r, p[r]);
-    return v;
+    return *(const typename Prec<F>::Op *)(M + (r0 + (l & 15)) * ld + c0 + 4 * (l >> 4));
 }
 // A operand of the transpose: A[i][k] = M[k][i], i.e. lane l reads
 // M[c0 + 4(l/16) + j][r0 + l%16], j = 0..3.
@@ -160,7 +166,7 @@ __device__ __forceinline__ void mlp_tile_forward(const typename Prec<F>::W *W, c
     for (int ob = 0; ob < 4; ob++) {
         f32x4 acc;
         for (int r = 0; r < 4; r++) acc[r] = b[kB1 + 16 * ob + 4 * g + r];
-        acc = mfma16<F>(load_a<F>(W + kW1p, 16, 16 * ob, 0, l), f.x, acc);
+        acc = mfma16<F>(load_a<F>(W + kL1, kLd1, 16 * ob, 0, l), f.x, acc);
         f.z1[ob] = acc;
     }
     for (int ob = 0; ob < 4; ob++) {
@@ -171,7 +177,7 @@ __device__ __forceinline__ void mlp_tile_forward(const typename Prec<F>::W *W, c
     for (int ob = 0; ob < 4; ob++) {
         f32x4 acc;
         for (int r = 0; r < 4; r++) acc[r] = b[kB2 + 16 * ob + 4 * g + r];
-        for (int kb = 0; kb < 4; kb++) acc = mfma16<F>(load_a<F>(W + kW2, 64, 16 * ob, 16 * kb, l), h[kb], acc);
+        for (int kb = 0; kb < 4; kb++) acc = mfma16<F>(load_a<F>(W + kL2, kLd, 16 * ob, 16 * kb, l), h[kb], acc);
         f.z2[ob] = acc;
     }
     for (int ob = 0; ob < 4; ob++) {
@@ -182,7 +188,7 @@ __device__ __forceinline__ void mlp_tile_forward(const typename Prec<F>::W *W, c
     for (int ob = 0; ob < 4; ob++) {
         f32x4 acc;
         for (int r = 0; r < 4; r++) acc[r] = b[kB3 + 16 * ob + 4 * g + r];
-        for (int kb = 0; kb < 4; kb++) acc = mfma16<F>(load_a<F>(W + kW3, 64, 16 * ob, 16 * kb, l), h[kb], acc);
+        for (int kb = 0; kb < 4; kb++) acc = mfma16<F>(load_a<F>(W + kL3, kLd, 16 * ob, 16 * kb, l), h[kb], acc);
         f.z3[ob] = acc;
     }
     for (int ob = 0; ob < 4; ob++) {
@@ -192,14 +198,27 @@ __device__ __forceinline__ void mlp_tile_forward(const typename Prec<F>::W *W, c
     }
     f32x4 acc;
     for (int r = 0; r < 4; r++) acc[r] = b[kB4p + 4 * g + r];
-    for (int kb = 0; kb < 4; kb++) acc = mfma16<F>(load_a<F>(W + kW4p, 64, 0, 16 * kb, l), h[kb], acc);
+    for (int kb = 0; kb < 4; kb++) acc = mfma16<F>(load_a<F>(W + kL4, kLd, 0, 16 * kb, l), h[kb], acc);
     f.y = acc;
 }
 
+// weights (16 bytes at a time; rows of 16 in W1p, of 64 in the others) and
+// biases into LDS
 template <typename WT>
-__device__ void load_weights_lds(const WT *__restrict__ wg, const float *__restrict__ bg,
-                                 WT *W, float *b) {
-    for (int i = threadIdx.x; i < kWpad; i += blockDim.x) W[i] = wg[i];
+__device__ __forceinline__ void load_weights_lds(const WT *__restrict__ wg,
+                                                 const float *__restrict__ bg, WT *W, float *b) {
+    typedef WT V4 __attribute__((ext_vector_type(4)));
+    constexpr int E = 16 / (int)sizeof(WT);   // elements per 16 bytes
+    struct V16 { V4 v[E / 4]; };
+    const V16 *src = (const V16 *)wg;
+    for (int i = threadIdx.x; i < kWpad / E; i += blockDim.x) {
+        const int e = i * E;
+        const V16 v = src[i];
+        const int at = e < kW2 ? (e >> 4) * kLd1 + (e & 15)
+                               : kL2 + ((e - kW2) >> 6) * kLd + ((e - kW2) & 63);
+#pragma unroll
+        for (int k = 0; k < E / 4; k++) *(V4 *)(W + at + 4 * k) = v.v[k];
+    }
     for (int i = threadIdx.x; i < kBpad; i += blockDim.x) b[i] = bg[i];
 }
 
@@ -215,7 +234,7 @@ __global__ __launch_bounds__(256) void k_mlp_infer(int64_t B, const int *__restr
                                                    const float *__restrict__ bg,
                                                    float *__restrict__ Y) {
     typedef typename Prec<F>::Op Op;
-    __shared__ typename Prec<F>::W W[kWpad];
+    __shared__ __attribute__((aligned(16))) typename Prec<F>::W W[kLpad];
     __shared__ float b[kBpad];
     if (Bdev) B = *Bdev;
     // a workgroup without a tile returns before staging the weights (the
@@ -230,12 +249,12 @@ __global__ __launch_bounds__(256) void k_mlp_infer(int64_t B, const int *__restr
     f32x4 C1[4], C2[4], C3[4], C4;
 #pragma unroll
     for (int ob = 0; ob < 4; ob++) {
-        A1[ob] = load_a<F>(W + kW1p, 16, 16 * ob, 0, l);
-        A4[ob] = load_a<F>(W + kW4p, 64, 0, 16 * ob, l);
+        A1[ob] = load_a<F>(W + kL1, kLd1, 16 * ob, 0, l);
+        A4[ob] = load_a<F>(W + kL4, kLd, 0, 16 * ob, l);
 #pragma unroll
         for (int kb = 0; kb < 4; kb++) {
-            A2[ob][kb] = load_a<F>(W + kW2, 64, 16 * ob, 16 * kb, l);
-            A3[ob][kb] = load_a<F>(W + kW3, 64, 16 * ob, 16 * kb, l);
+            A2[ob][kb] = load_a<F>(W + kL2, kLd, 16 * ob, 16 * kb, l);
+            A3[ob][kb] = load_a<F>(W + kL3, kLd, 16 * ob, 16 * kb, l);
         }
 #pragma unroll
         for (int r = 0; r < 4; r++) {
@@ -285,190 +304,299 @@ __global__ __launch_bounds__(256) void k_mlp_infer(int64_t B, const int *__restr
 }
 
 // ------------------------------------------------------------- training
-// adds dZ^T H for one 16-sample tile into the LDS gradient accumulator G
-// (out x in, row stride kin): Tz holds dZ [16][kout] and Th holds H [16][kin]
-// in the instance's precision.
+// A workgroup of NW wavefronts takes 16 NW samples at a time, each wavefront
+// the forward and backward chains of 16.  Both factors of a layer's dW = dZ^T H
+// go through LDS transposed ([feature][sample], so that an operand is one
+// read), and the wavefronts share the products by output blocks, which they
+// accumulate in registers over all the workgroup's samples.  Bias gradients are
+// summed per lane and reduced once.  Bound by latency at the training batch of
+// 8192 samples (128 workgroups): 14 us, and 4 for the reduction (one wavefront per
+// workgroup with its gradient in LDS, bias sums by shuffles and unaligned operand
+// reads took 56, the reduction over 512 partials 32, a fold and two copies 14).
+template <bool F> constexpr int train_waves() { return F ? 2 : 4; }
+template <bool F> constexpr int tile_ld() { return 16 * train_waves<F>() + 4; }
+
+// store a D-layout block (features 16 ob + 4 g + r of sample l % 16 of the
+// wavefront) into a [feature][sample] tile
 template <bool F>
-__device__ __forceinline__ void acc_dw(const typename Prec<F>::W *Tz, int kout,
-                                       const typename Prec<F>::W *Th, int kin, float *G, int l) {
-    const int g = l >> 4;
-    for (int ob = 0; ob < kout / 16; ob++)
-        for (int ib = 0; ib < kin / 16; ib++) {
-            typename Prec<F>::Op a, bb;
-            for (int r = 0; r < 4; r++) {
-                Prec<F>::set(a, r, Tz[(4 * g + r) * kout + 16 * ob + (l & 15)]);
-                Prec<F>::set(bb, r, Th[(4 * g + r) * kin + 16 * ib + (l & 15)]);
-            }
-            f32x4 d = {0.f, 0.f, 0.f, 0.f};
-            d = mfma16<F>(a, bb, d);
-            for (int r = 0; r < 4; r++) G[(16 * ob + 4 * g + r) * kin + 16 * ib + (l & 15)] += d[r];
-        }
+__device__ __forceinline__ void store_tile(typename Prec<F>::W *T, int ob, f32x4 v, int s, int g) {
+#pragma unroll
+    for (int r = 0; r < 4; r++) T[(16 * ob + 4 * g + r) * tile_ld<F>() + s] = Prec<F>::store(v[r]);
 }
 
-// store a D-layout block (features 16*ob + 4g + r of sample l%16) into a
-// [16][k] tile
+// acc += block (ob, ib) of dZ^T H over the workgroup's samples
 template <bool F>
-__device__ __forceinline__ void store_tile(typename Prec<F>::W *T, int k, int ob, f32x4 v, int l) {
-    const int g = l >> 4;
-    for (int r = 0; r < 4; r++) T[(l & 15) * k + 16 * ob + 4 * g + r] = Prec<F>::store(v[r]);
+__device__ __forceinline__ f32x4 acc_dw(const typename Prec<F>::W *Tz, int ob,
+                                        const typename Prec<F>::W *Th, int ib, f32x4 acc, int l) {
+#pragma unroll
+    for (int st = 0; st < train_waves<F>(); st++)
+        acc = mfma16<F>(load_a<F>(Tz, tile_ld<F>(), 16 * ob, 16 * st, l),
+                        load_a<F>(Th, tile_ld<F>(), 16 * ib, 16 * st, l), acc);
+    return acc;
 }
 
-// bias gradient: sum over the 16 samples (lanes sharing l/16)
-__device__ __forceinline__ void acc_db(f32x4 v, float *G, int base, int ob, int l) {
-    for (int r = 0; r < 4; r++) {
-        float s = v[r];
-        for (int m = 1; m < 16; m <<= 1) s += __shfl_xor(s, m, 16);
-        if ((l & 15) == 0) G[base + 16 * ob + 4 * (l >> 4) + r] += s;
-    }
-}
-
-template <bool F>
-__device__ __forceinline__ void hidden_back(const typename Prec<F>::W *W, float *G, int woff,
-                                            int boff, const f32x4 (&zp)[4], f32x4 (&dz)[4],
-                                            typename Prec<F>::W *Tz, typename Prec<F>::W *Th,
-                                            bool valid, int l) {
-    for (int ob = 0; ob < 4; ob++) {
-        f32x4 h = zp[ob];
-        for (int r = 0; r < 4; r++) h[r] = valid ? silu(h[r]) : 0.f;
-        store_tile<F>(Th, 64, ob, h, l);
-        store_tile<F>(Tz, 64, ob, dz[ob], l);
-    }
-    __syncthreads();
-    acc_dw<F>(Tz, 64, Th, 64, G + woff, l);
-    for (int ob = 0; ob < 4; ob++) acc_db(dz[ob], G, kWpad + boff, ob, l);
-    __syncthreads();
-    typename Prec<F>::Op dzb[4];
-    for (int ob = 0; ob < 4; ob++) dzb[ob] = to_op<F>(dz[ob]);
-    for (int ob = 0; ob < 4; ob++) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int kb = 0; kb < 4; kb++)
-            acc = mfma16<F>(load_at<F>(W + woff, 64, 16 * ob, 16 * kb, l), dzb[kb], acc);
-        for (int r = 0; r < 4; r++) acc[r] *= dsilu(zp[ob][r]);
-        dz[ob] = acc;
-    }
+// sum of a lane's value over its row of 16 lanes, in the row's last lane
+__device__ __forceinline__ float row_sum15(float v) {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x118, 0xf, 0xf, true));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x114, 0xf, 0xf, true));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x112, 0xf, 0xf, true));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x111, 0xf, 0xf, true));
+    return v;
 }
 
 template <bool F>
-__global__ __launch_bounds__(64) void k_mlp_train(int64_t B, const float *__restrict__ X,
-                                                  const float *__restrict__ T, float scale,
-                                                  const typename Prec<F>::W *__restrict__ wg,
-                                                  const float *__restrict__ bg,
-                                                  float *__restrict__ partial,
-                                                  float *__restrict__ loss_partial) {
+__global__ __launch_bounds__(64 * train_waves<F>()) void k_mlp_train(
+    int64_t B, const float *__restrict__ X, const float *__restrict__ T, float scale,
+    const typename Prec<F>::W *__restrict__ wg, const float *__restrict__ bg,
+    float *__restrict__ partial, float *__restrict__ loss_partial) {
     typedef typename Prec<F>::W WT;
-    __shared__ WT W[kWpad];
-    __shared__ float b[kBpad];
-    __shared__ float G[kGpad];
-    __shared__ WT Tz[16 * 64], Th[16 * 64];
+    constexpr int NW = train_waves<F>(), PB = 4 / NW;   // output blocks of a row per wavefront
+    __shared__ __attribute__((aligned(16))) WT W[kLpad];
+    __shared__ __attribute__((aligned(16))) WT Tz[64 * tile_ld<F>()], Th[64 * tile_ld<F>()];
+    __shared__ float b[kBpad], dbs[NW][kBpad];
     load_weights_lds(wg, bg, W, b);
-    for (int i = threadIdx.x; i < kGpad; i += blockDim.x) G[i] = 0.f;
     __syncthreads();
-    const int l = threadIdx.x, g = l >> 4;
-    const int64_t ntiles = (B + 15) / 16;
+    const int l = threadIdx.x & 63, wave = threadIdx.x >> 6, g = l >> 4, ts = 16 * wave + (l & 15);
+    const int64_t ntiles = (B + 16 * NW - 1) / (16 * NW);
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    // dW blocks: layers 3, 2: rows ob = wave PB + p; layer 4: columns; layer 1: rows
+    f32x4 g3[PB][4], g2[PB][4], g4[PB], g1[PB], db1[4], db2[4], db3[4], db4 = zero;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        db1[i] = db2[i] = db3[i] = zero;
+#pragma unroll
+        for (int p = 0; p < PB; p++) g3[p][i] = g2[p][i] = zero;
+    }
+#pragma unroll
+    for (int p = 0; p < PB; p++) g4[p] = g1[p] = zero;
     float lsum = 0.f;
-    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        Fwd<F> f;
-        mlp_tile_forward<F>(W, b, X, B, 16 * t, l, f);
-        const int64_t s = 16 * t + (l & 15);
-        const bool valid = s < B;
-        // dZ4 = (y - t) * scale on rows 0..2
-        f32x4 dz4 = {0.f, 0.f, 0.f, 0.f};
-        if (g == 0 && valid)
-            for (int r = 0; r < 3; r++) {
-                float d = f.y[r] - T[3 * s + r];
-                lsum += 0.5f * d * d * scale;
-                dz4[r] = d * scale;
-            }
-        // layer 4: dW4 (16 x 64) += dZ4^T H3
-        typename Prec<F>::Op dz4b = to_op<F>(dz4);
+    // dZ of the layer below: (W^T dZ) * silu'(z)
+    auto back = [&](int woff, int nk, const f32x4 (&zp)[4], f32x4 (&dz)[4]) {
+        typename Prec<F>::Op dzb[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            if (k < nk) dzb[k] = to_op<F>(dz[k]);
+#pragma unroll
         for (int ob = 0; ob < 4; ob++) {
-            f32x4 h = f.z3[ob];
-            for (int r = 0; r < 4; r++) h[r] = valid ? silu(h[r]) : 0.f;
-            store_tile<F>(Th, 64, ob, h, l);
-        }
-        store_tile<F>(Tz, 16, 0, dz4, l);
-        __syncthreads();
-        acc_dw<F>(Tz, 16, Th, 64, G + kW4p, l);
-        acc_db(dz4, G, kWpad + kB4p, 0, l);
-        __syncthreads();
-        // dH3 = W4^T dZ4 ; dZ3 = dH3 * silu'(z3)
-        f32x4 dz[4];
-        for (int ob = 0; ob < 4; ob++) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-            acc = mfma16<F>(load_at<F>(W + kW4p, 64, 16 * ob, 0, l), dz4b, acc);
-            for (int r = 0; r < 4; r++) acc[r] *= dsilu(f.z3[ob][r]);
+            f32x4 acc = zero;
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+                if (k < nk) acc = mfma16<F>(load_at<F>(W + woff, kLd, 16 * ob, 16 * k, l), dzb[k], acc);
+#pragma unroll
+            for (int r = 0; r < 4; r++) acc[r] *= dsilu(zp[ob][r]);
             dz[ob] = acc;
         }
-        // layers 3 and 2: dW += dZ^T H(prev); dZ(prev) = (W^T dZ) * silu'(z(prev))
-        hidden_back<F>(W, G, kW3, kB3, f.z2, dz, Tz, Th, valid, l);
-        hidden_back<F>(W, G, kW2, kB2, f.z1, dz, Tz, Th, valid, l);
-        // layer 1: dW1p (64 x 16) += dZ1^T Xp
-        for (int r = 0; r < 4; r++) Th[(l & 15) * 16 + 4 * g + r] = (WT)f.x[r];
-        for (int ob = 0; ob < 4; ob++) store_tile<F>(Tz, 64, ob, dz[ob], l);
+    };
+    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        Fwd<F> f;
+        const int64_t s0 = 16 * NW * t + 16 * wave, s = s0 + (l & 15);
+        mlp_tile_forward<F>(W, b, X, B, s0, l, f);
+        const bool valid = s < B;
+        auto store_h = [&](const f32x4 (&z)[4]) {
+#pragma unroll
+            for (int ob = 0; ob < 4; ob++) {
+                f32x4 h = z[ob];
+#pragma unroll
+                for (int r = 0; r < 4; r++) h[r] = valid ? silu(h[r]) : 0.f;
+                store_tile<F>(Th, ob, h, ts, g);
+            }
+        };
+        // dZ4 = (y - t) * scale on rows 0..2
+        f32x4 dz[4] = {zero, zero, zero, zero};
+        if (g == 0 && valid)
+#pragma unroll
+            for (int r = 0; r < 3; r++) {
+                const float d = f.y[r] - T[3 * s + r];
+                lsum += 0.5f * d * d * scale;
+                dz[0][r] = d * scale;
+            }
+        db4 += dz[0];
+        store_h(f.z3);
+        store_tile<F>(Tz, 0, dz[0], ts, g);
         __syncthreads();
-        acc_dw<F>(Tz, 64, Th, 16, G + kW1p, l);
-        for (int ob = 0; ob < 4; ob++) acc_db(dz[ob], G, kWpad + kB1, ob, l);
+#pragma unroll
+        for (int p = 0; p < PB; p++) g4[p] = acc_dw<F>(Tz, 0, Th, wave * PB + p, g4[p], l);
+        back(kL4, 1, f.z3, dz);
+        __syncthreads();
+        auto layer = [&](const f32x4 (&z)[4], f32x4 (&db)[4], f32x4 (&gw)[PB][4]) {
+            store_h(z);
+#pragma unroll
+            for (int ob = 0; ob < 4; ob++) {
+                db[ob] += dz[ob];
+                store_tile<F>(Tz, ob, dz[ob], ts, g);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int p = 0; p < PB; p++)
+#pragma unroll
+                for (int ib = 0; ib < 4; ib++)
+                    gw[p][ib] = acc_dw<F>(Tz, wave * PB + p, Th, ib, gw[p][ib], l);
+        };
+        layer(f.z2, db3, g3);
+        back(kL3, 4, f.z2, dz);
+        __syncthreads();
+        layer(f.z1, db2, g2);
+        back(kL2, 4, f.z1, dz);
+        __syncthreads();
+        // layer 1: dW1p (64 x 16) += dZ1^T Xp
+#pragma unroll
+        for (int r = 0; r < 4; r++) Th[(4 * g + r) * tile_ld<F>() + ts] = (WT)f.x[r];
+#pragma unroll
+        for (int ob = 0; ob < 4; ob++) {
+            db1[ob] += dz[ob];
+            store_tile<F>(Tz, ob, dz[ob], ts, g);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < PB; p++) g1[p] = acc_dw<F>(Tz, wave * PB + p, Th, 0, g1[p], l);
         __syncthreads();
     }
-    float* out = partial + (size_t)blockIdx.x * kGpad;
-    for (int i = threadIdx.x; i < kGpad; i += blockDim.x) out[i] = G[i];
+    // element r of a block: row 4 g + r, column l % 16
+    float *out = partial + (size_t)blockIdx.x * kGpad;
+    const int c = l & 15;
+#pragma unroll
+    for (int p = 0; p < PB; p++) {
+        const int ob = wave * PB + p;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int row = 16 * ob + 4 * g + r;
+            out[kW1p + row * 16 + c] = g1[p][r];
+            out[kW4p + (4 * g + r) * 64 + 16 * ob + c] = g4[p][r];
+#pragma unroll
+            for (int ib = 0; ib < 4; ib++) {
+                out[kW2 + row * 64 + 16 * ib + c] = g2[p][ib][r];
+                out[kW3 + row * 64 + 16 * ib + c] = g3[p][ib][r];
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+#pragma unroll
+        for (int ob = 0; ob < 4; ob++) {
+            const float v1 = row_sum15(db1[ob][r]), v2 = row_sum15(db2[ob][r]),
+                        v3 = row_sum15(db3[ob][r]);
+            if (c == 15) {
+                dbs[wave][kB1 + 16 * ob + 4 * g + r] = v1;
+                dbs[wave][kB2 + 16 * ob + 4 * g + r] = v2;
+                dbs[wave][kB3 + 16 * ob + 4 * g + r] = v3;
+            }
+        }
+        const float v4 = row_sum15(db4[r]);
+        if (c == 15) dbs[wave][kB4p + 4 * g + r] = v4;
+    }
     for (int m = 1; m < 64; m <<= 1) lsum += __shfl_xor(lsum, m, 64);
-    if (threadIdx.x == 0) loss_partial[blockIdx.x] = lsum;
+    if (l == 0) b[wave] = lsum;   // the biases are no longer read
+    __syncthreads();
+    for (int i = threadIdx.x; i < kBpad; i += blockDim.x) {
+        float v = dbs[0][i];
+        for (int w = 1; w < NW; w++) v += dbs[w][i];
+        out[kWpad + i] = v;
+    }
+    if (threadIdx.x == 0) {
+        float v = b[0];
+        for (int w = 1; w < NW; w++) v += b[w];
+        loss_partial[blockIdx.x] = v;
+    }
 }
 
 // Sum of the workgroup partials in a fixed order: block j < kGpad / 64 owns
 // 64 consecutive entries of the padded gradient image; its 4 thread groups
-// sum 4 contiguous quarters of the partials (coalesced rows) and the quarter
-// sums are added in order.  The extra last block sums the loss partials
-// (fixed per-thread strides, then a fixed tree).
+// sum 4 contiguous quarters of the partials (coalesced rows, eight loads in
+// flight) and the quarter sums are added in order.  The entries of the master
+// layout go to grad (W1's two copies of a column added), or, with ADAM, into
+// the Adam step: moments, parameters and the kernels' padded images.  The extra
+// last block sums the loss partials (fixed per-thread strides, then a fixed
+// tree).
 constexpr int kRedCols = 64;
 constexpr int kRedBlocks = (kGpad + kRedCols - 1) / kRedCols;
+static_assert(kGpad == kRedCols * kRedBlocks - 48, "the last block is cut short");
 
-__global__ __launch_bounds__(256) void k_mlp_reduce_pad(int nb, const float *__restrict__ partial,
-                                                       const float *__restrict__ loss_partial,
-                                                       float *__restrict__ gpad,
-                                                       float *__restrict__ loss) {
+struct AdamArgs {
+    float *P, *m, *v, *wf, *bg;
+    unsigned short *wg;
+    float lr, b1, b2, eps, c1, c2;
+};
+
+// master index of padded entry i, or -1 (padding, and W1's second copy)
+__device__ __forceinline__ int master_index(int i) {
+    if (i < kW2) return (i & 15) < 8 ? (i >> 4) * 8 + (i & 15) : -1;
+    if (i < kW3) return 576 + (i - kW2);
+    if (i < kW4p) return 4736 + (i - kW3);
+    if (i < kWpad) return i - kW4p < 192 ? 8896 + (i - kW4p) : -1;
+    const int j = i - kWpad;
+    if (j < kB2) return 512 + j;
+    if (j < kB3) return 4672 + (j - kB2);
+    if (j < kB4p) return 8832 + (j - kB3);
+    return j - kB4p < 3 ? 9088 + (j - kB4p) : -1;
+}
+
+__device__ __forceinline__ void sum_loss(int nb, const float *__restrict__ loss_partial, float *sh,
+                                         float *__restrict__ loss) {
+    const int t = threadIdx.x;
+    float s = 0.f;
+    for (int k = t; k < nb; k += 256) s += loss_partial[k];
+    sh[t] = s;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if (t < o) sh[t] += sh[t + o];
+        __syncthreads();
+    }
+    if (t == 0) *loss = sh[0];
+}
+
+__global__ __launch_bounds__(256) void k_mlp_loss(int nb, const float *__restrict__ loss_partial,
+                                                  float *__restrict__ loss) {
     __shared__ float sh[256];
+    sum_loss(nb, loss_partial, sh, loss);
+}
+
+template <bool ADAM>
+__global__ __launch_bounds__(256) void k_mlp_reduce(int nb, const float *__restrict__ partial,
+                                                   const float *__restrict__ loss_partial,
+                                                   float *__restrict__ grad,
+                                                   float *__restrict__ loss, AdamArgs A) {
+    __shared__ float sh[256], tot[64];
     const int t = threadIdx.x;
     if (blockIdx.x == kRedBlocks) {
-        float s = 0.f;
-        for (int k = t; k < nb; k += 256) s += loss_partial[k];
-        sh[t] = s;
-        __syncthreads();
-        for (int o = 128; o > 0; o >>= 1) {
-            if (t < o) sh[t] += sh[t + o];
-            __syncthreads();
-        }
-        if (t == 0) *loss = sh[0];
+        if (loss) sum_loss(nb, loss_partial, sh, loss);
         return;
     }
     const int c = t % kRedCols, g = t / kRedCols;
     const int i = blockIdx.x * kRedCols + c;
     const int q = (nb + 3) / 4, k0 = g * q, k1 = k0 + q < nb ? k0 + q : nb;
     float s = 0.f;
-    if (i < kGpad)
+    if (i < kGpad) {
+#pragma unroll 8
         for (int k = k0; k < k1; k++) s += partial[(size_t)k * kGpad + i];
+    }
     sh[t] = s;
     __syncthreads();
-    if (g == 0 && i < kGpad) gpad[i] = (sh[c] + sh[64 + c]) + (sh[128 + c] + sh[192 + c]);
-}
-
-// fold the padded gradient image back to the master layout
-__global__ void k_mlp_fold(const float *__restrict__ gp, float *__restrict__ grad) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kNP) return;
-    float v;
-    if (i < 512) {                               // W1[o][c]: both copies of column c
-        int o = i / 8, c = i % 8;
-        v = gp[kW1p + o * 16 + c] + gp[kW1p + o * 16 + 8 + c];
-    } else if (i < 576) v = gp[kWpad + kB1 + (i - 512)];
-    else if (i < 4672) v = gp[kW2 + (i - 576)];
-    else if (i < 4736) v = gp[kWpad + kB2 + (i - 4672)];
-    else if (i < 8832) v = gp[kW3 + (i - 4736)];
-    else if (i < 8896) v = gp[kWpad + kB3 + (i - 8832)];
-    else if (i < 9088) v = gp[kW4p + (i - 8896)];    // rows 0..2 of W4p
-    else v = gp[kWpad + kB4p + (i - 9088)];
-    grad[i] = v;
+    if (g == 0) tot[c] = (sh[c] + sh[64 + c]) + (sh[128 + c] + sh[192 + c]);
+    __syncthreads();
+    if (g != 0 || i >= kGpad) return;
+    const int j = master_index(i);
+    if (j < 0) return;
+    const float v = i < kW2 ? tot[c] + tot[c + 8] : tot[c];
+    if constexpr (!ADAM) {
+        grad[j] = v;
+    } else {
+        const float mi = A.b1 * A.m[j] + (1.f - A.b1) * v;
+        const float vi = A.b2 * A.v[j] + (1.f - A.b2) * v * v;
+        A.m[j] = mi;
+        A.v[j] = vi;
+        const float p = A.P[j] - A.lr * (mi / A.c1) / (sqrtf(vi / A.c2) + A.eps);
+        A.P[j] = p;
+        if (i < kWpad) {
+            A.wg[i] = f2bf(p);
+            A.wf[i] = p;
+            if (i < kW2) {
+                A.wg[i + 8] = f2bf(p);
+                A.wf[i + 8] = p;
+            }
+        } else {
+            A.bg[i - kWpad] = p;
+        }
+    }
 }
 
 // master FP32 -> padded BF16 weights (and the same image in FP32, for the
@@ -495,19 +623,6 @@ __global__ void k_mlp_pack(const float *__restrict__ P, unsigned short *__restri
     }
 }
 
-__global__ void k_adam(int n, float *__restrict__ P, const float *__restrict__ G,
-                       float *__restrict__ m, float *__restrict__ v, float lr, float b1, float b2,
-                       float eps, float c1, float c2) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float g = G[i];
-    float mi = b1 * m[i] + (1.f - b1) * g;
-    float vi = b2 * v[i] + (1.f - b2) * g * g;
-    m[i] = mi;
-    v[i] = vi;
-    P[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
 }  // namespace bs
 
 // ------------------------------------------------------------------ C ABI
@@ -515,13 +630,13 @@ using namespace bs;
 
 struct bs_mlp_s {
     hipStream_t stream = nullptr;
-    float *P = nullptr, *m = nullptr, *v = nullptr, *G = nullptr;
+    float *P = nullptr, *m = nullptr, *v = nullptr;
     unsigned short *wg = nullptr;
     float *wf = nullptr;     // FP32 image of the padded weights (debug mode)
     float *bg = nullptr;
     int fp32 = 0;            // 1: FP32 weights and activations (debug mode)
-    float *partial = nullptr, *loss_partial = nullptr, *loss = nullptr, *gpad = nullptr;
-    int nb = 512;
+    float *partial = nullptr, *loss_partial = nullptr;
+    int nb = 256;            // workgroups of a training pass, at most (one per CU)
     int64_t step = 0;
     std::string err;
 };
@@ -553,11 +668,10 @@ int bs_mlp_create(const float *params_host, void *hip_stream, bs_mlp_t *out) {
     hipError_t e = hipSuccess;
     auto al = [&](void **p, size_t bytes) { if (e == hipSuccess) e = hipMalloc(p, bytes); };
     al((void **)&M->P, kNP * 4); al((void **)&M->m, kNP * 4); al((void **)&M->v, kNP * 4);
-    al((void **)&M->G, kNP * 4); al((void **)&M->wg, kWpad * 2); al((void **)&M->bg, kBpad * 4);
+    al((void **)&M->wg, kWpad * 2); al((void **)&M->bg, kBpad * 4);
     al((void **)&M->wf, kWpad * 4);
     al((void **)&M->partial, (size_t)M->nb * kGpad * 4);
-    al((void **)&M->loss_partial, M->nb * 4); al((void **)&M->loss, 4);
-    al((void **)&M->gpad, kGpad * 4);
+    al((void **)&M->loss_partial, M->nb * 4);
     if (e != hipSuccess) { bs_mlp_destroy(M); return BS_ENOMEM; }
     (void)hipMemcpy(M->P, params_host, kNP * 4, hipMemcpyHostToDevice);
     (void)hipMemset(M->m, 0, kNP * 4);
@@ -582,46 +696,49 @@ int bs_mlp_forward(bs_mlp_t M, int64_t B, const float *X, float *Y) {
     return hipGetLastError() == hipSuccess ? BS_OK : BS_EDEVICE;
 }
 
-static int mlp_grad(bs_mlp_t M, int64_t B, const float *X, const float *T) {
-    int64_t tiles = (B + 15) / 16;
-    int blocks = (int)std::min<int64_t>(tiles, M->nb);
+// the workgroup partials of the loss and its gradient; their number
+static int mlp_partials(bs_mlp_t M, int64_t B, const float *X, const float *T) {
+    const int waves = M->fp32 ? train_waves<true>() : train_waves<false>();
+    const int64_t tiles = (B + 16 * waves - 1) / (16 * waves);
+    const int blocks = (int)std::min<int64_t>(tiles, M->nb);
     if (M->fp32)
-        hipLaunchKernelGGL(k_mlp_train<true>, dim3(blocks), dim3(64), 0, M->stream, B, X, T,
+        hipLaunchKernelGGL(k_mlp_train<true>, dim3(blocks), dim3(64 * waves), 0, M->stream, B, X, T,
                            1.0f / (float)B, (const float *)M->wf, M->bg, M->partial,
                            M->loss_partial);
     else
-        hipLaunchKernelGGL(k_mlp_train<false>, dim3(blocks), dim3(64), 0, M->stream, B, X, T,
-                           1.0f / (float)B, (const unsigned short *)M->wg, M->bg, M->partial,
+        hipLaunchKernelGGL(k_mlp_train<false>, dim3(blocks), dim3(64 * waves), 0, M->stream, B, X,
+                           T, 1.0f / (float)B, (const unsigned short *)M->wg, M->bg, M->partial,
                            M->loss_partial);
-    hipLaunchKernelGGL(k_mlp_reduce_pad, dim3(kRedBlocks + 1), dim3(256), 0, M->stream, blocks,
-                       M->partial, M->loss_partial, M->gpad, M->loss);
-    hipLaunchKernelGGL(k_mlp_fold, dim3(ceil_div(kNP, 256)), dim3(256), 0, M->stream, M->gpad,
-                       M->G);
-    return hipGetLastError() == hipSuccess ? BS_OK : BS_EDEVICE;
+    return blocks;
 }
 
 int bs_mlp_loss_grad(bs_mlp_t M, int64_t B, const float *X, const float *T, float *loss_dev,
                      float *grad_dev) {
     if (!M || B <= 0 || !X || !T) return BS_EINVAL;
-    int rc = mlp_grad(M, B, X, T);
-    if (rc) return rc;
-    if (loss_dev) (void)hipMemcpyAsync(loss_dev, M->loss, 4, hipMemcpyDeviceToDevice, M->stream);
-    if (grad_dev) (void)hipMemcpyAsync(grad_dev, M->G, kNP * 4, hipMemcpyDeviceToDevice, M->stream);
+    if (!loss_dev && !grad_dev) return BS_OK;
+    const int blocks = mlp_partials(M, B, X, T);
+    AdamArgs A{};
+    if (grad_dev)
+        hipLaunchKernelGGL(k_mlp_reduce<false>, dim3(kRedBlocks + 1), dim3(256), 0, M->stream,
+                           blocks, M->partial, M->loss_partial, grad_dev, loss_dev, A);
+    else
+        hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(256), 0, M->stream, blocks, M->loss_partial,
+                           loss_dev);
     return hipGetLastError() == hipSuccess ? BS_OK : BS_EDEVICE;
 }
 
 int bs_mlp_adam_step(bs_mlp_t M, int64_t B, const float *X, const float *T, float lr,
                      float beta1, float beta2, float eps, float *loss_dev) {
     if (!M || B <= 0 || !X || !T) return BS_EINVAL;
-    int rc = mlp_grad(M, B, X, T);
-    if (rc) return rc;
+    const int blocks = mlp_partials(M, B, X, T);
     M->step++;
-    float c1 = 1.f - powf(beta1, (float)M->step), c2 = 1.f - powf(beta2, (float)M->step);
-    hipLaunchKernelGGL(k_adam, dim3(ceil_div(kNP, 256)), dim3(256), 0, M->stream, kNP, M->P, M->G,
-                       M->m, M->v, lr, beta1, beta2, eps, c1, c2);
-    hipLaunchKernelGGL(k_mlp_pack, dim3(ceil_div(kWpad, 256)), dim3(256), 0, M->stream, M->P,
-                       M->wg, M->wf, M->bg);
-    if (loss_dev) (void)hipMemcpyAsync(loss_dev, M->loss, 4, hipMemcpyDeviceToDevice, M->stream);
+    AdamArgs A;
+    A.P = M->P; A.m = M->m; A.v = M->v; A.wf = M->wf; A.bg = M->bg; A.wg = M->wg;
+    A.lr = lr; A.b1 = beta1; A.b2 = beta2; A.eps = eps;
+    A.c1 = 1.f - powf(beta1, (float)M->step);
+    A.c2 = 1.f - powf(beta2, (float)M->step);
+    hipLaunchKernelGGL(k_mlp_reduce<true>, dim3(kRedBlocks + 1), dim3(256), 0, M->stream, blocks,
+                       M->partial, M->loss_partial, (float *)nullptr, loss_dev, A);
     return hipGetLastError() == hipSuccess ? BS_OK : BS_EDEVICE;
 }
 
@@ -641,8 +758,7 @@ int bs_mlp_get_params(bs_mlp_t M, float *params_host) {
 int bs_mlp_destroy(bs_mlp_t M) {
     if (!M) return BS_OK;
     (void)hipStreamSynchronize(M->stream);
-    void *all[] = {M->P, M->m, M->v, M->G, M->wg, M->wf, M->bg, M->partial, M->loss_partial,
-                   M->loss, M->gpad};
+    void *all[] = {M->P, M->m, M->v, M->wg, M->wf, M->bg, M->partial, M->loss_partial};
     for (void *p : all)
         if (p) (void)hipFree(p);
     delete M;
