@@ -762,16 +762,14 @@ int bs_energy(bs_plan_t P, double *E_out, double *psi_out) {
     int rc = long_range(P, 1, nullptr, psi);
     if (rc) return rc;
     launch_pairs(P, 1, nullptr, psi, true);
-    const int nb = 512;
-    double *partial = (double *)P->red_tmp.p;   // nb + 1 doubles
-    launch_energy(P, psi, partial, nb);
+    if (!P->h_energy && (rc = check_hip(P, hipHostMalloc((void **)&P->h_energy, sizeof(double),
+                                                         hipHostMallocMapped), "hipHostMalloc")))
+        return rc;
+    launch_energy(P, psi, (double *)P->red_tmp.p, P->h_energy);
     if ((rc = launch_status(P, "energy kernels"))) return rc;
-    if (E_out) {
-        if ((rc = check_hip(P, hipMemcpyAsync(E_out, partial + nb, sizeof(double),
-                                              hipMemcpyDeviceToHost, P->stream), "copy E")))
-            return rc;
-    }
-    return check_hip(P, hipStreamSynchronize(P->stream), "sync");
+    if ((rc = check_hip(P, hipStreamSynchronize(P->stream), "sync"))) return rc;
+    if (E_out) *E_out = *(volatile double *)P->h_energy;
+    return BS_OK;
 }
 
 int bs_vorticity_modes(bs_plan_t P, double *out) {
@@ -958,6 +956,7 @@ int bs_destroy(bs_plan_t P) {
         (void)hipStreamSynchronize(P->side);
         (void)hipStreamDestroy(P->side);
     }
+    if (P->h_energy) (void)hipHostFree(P->h_energy);
     if (P->ev_fork) (void)hipEventDestroy(P->ev_fork);
     if (P->ev_join) (void)hipEventDestroy(P->ev_join);
     if (P->ev_ns) (void)hipEventDestroy(P->ev_ns);

@@ -154,6 +154,7 @@ struct bs_plan_s {
     double *g_v = nullptr;
     // terms (for velocity terms / energy)
     bs::DBuf tmp3;                             // f64 [N][3]
+    double *h_energy = nullptr;                // pinned host memory, written by the device
     bs::DBuf e_D, e_S;                         // f64 [N][3]: spline of psi (energy)
     bs::DBuf d_vls;                            // f64 [N][3]: local - self velocity
     // per-stage timing (diagnostics)
@@ -253,7 +254,8 @@ void mlp_forward_device(bs_mlp_t m, const int *Bdev, int64_t Bmax, const float *
 hipStream_t mlp_stream(bs_mlp_t m);
 
 // pairs.hip (with the short-range sums): the energy line integral
-void launch_energy(bs_plan_t p, const double *psi, double *partial, int nblocks);
+// (into *e, host memory mapped on the device; partial: 512 doubles)
+void launch_energy(bs_plan_t p, const double *psi, double *partial, double *e);
 
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 

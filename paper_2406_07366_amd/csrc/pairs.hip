@@ -409,29 +409,42 @@ __global__ void k_energy_partial(int N, int Q, const double *__restrict__ psi,
     if (threadIdx.x == 0) partial[blockIdx.x] = sh[0];
 }
 
-__global__ void k_energy_final(int nb, double scale, const double *__restrict__ partial,
-                               double *__restrict__ e) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int b = 0; b < nb; b++) s += partial[b];
-        *e = s * scale;
+// one workgroup: thread t adds partials t, t + 256, ... and a fixed tree adds the
+// threads (one thread adding all 512 took 28 us); the sum goes to host memory
+// that the device maps
+__global__ __launch_bounds__(kRedBlock) void k_energy_final(int nb, double scale,
+                                                            const double *__restrict__ partial,
+                                                            double *__restrict__ e) {
+    __shared__ double sh[kRedBlock];
+    double s = 0.0;
+    for (int b = threadIdx.x; b < nb; b += kRedBlock) s += partial[b];
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int o = kRedBlock / 2; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        *e = sh[0] * scale;
+        __threadfence_system();
     }
 }
 
-void launch_energy(bs_plan_t p, const double *psi, double *partial, int nblocks) {
+void launch_energy(bs_plan_t p, const double *psi, double *partial, double *e) {
     double L = p->prm.L;
     double *eD = (double *)p->e_D.p, *eS = (double *)p->e_S.p;
     launch_spline_data(p, psi, eD, eS);
     GLRule r = gl_rule(p->Q);
     GLNodes g;
     for (int i = 0; i < kEnergyMaxQ; i++) g.h[i] = r.h[i];
+    const int nblocks = std::min(512, ceil_div(p->N, kRedBlock));
     auto kern = p->order == 6 ? k_energy_partial<6> : k_energy_partial<4>;
     hipLaunchKernelGGL(kern, dim3(nblocks), dim3(kRedBlock), 0, p->stream, (int)p->N, p->Q, psi,
                        (const double *)eD, (const double *)eS, (const double *)p->d_dtau.p,
                        (const int *)p->d_off.p, (const int *)p->d_fil.p,
                        (const double *)p->d_qchg.p, g, partial);
-    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(64), 0, p->stream, nblocks,
-                       1.0 / (2.0 * L * L * L), partial, partial + nblocks);
+    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kRedBlock), 0, p->stream, nblocks,
+                       1.0 / (2.0 * L * L * L), (const double *)partial, e);
 }
 
 }  // namespace bs
