@@ -328,7 +328,7 @@ __device__ __forceinline__ void fft_pass(int nseq, int pitch, C *buf, const C *t
             else dft_any<R>(v[it], sgn);
         }
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int it = 0; it < IPT; it++) {
         if (act[it]) {
@@ -341,7 +341,7 @@ __device__ __forceinline__ void fft_pass(int nseq, int pitch, C *buf, const C *t
             }
         }
     }
-    __syncthreads();
+    lds_barrier();
 }
 
 // tw: the twiddle table in LDS (n entries); passes P, P+1, ... of the plan
@@ -371,25 +371,6 @@ __device__ __forceinline__ void fft_run(int nseq, int pitch, C *buf, const C *tw
 template <typename C>
 __device__ __forceinline__ void stage_twiddles(C *dst, const C *__restrict__ src, int ntab) {
     for (int i = threadIdx.x; i < ntab; i += blockDim.x) dst[i] = src[i];
-}
-
-// cnt items into LDS: store(i, load(i)), with up to B loads of each thread in
-// flight before their LDS stores (a plain loop would wait for every load)
-template <int B, typename Load, typename Store>
-__device__ __forceinline__ void gather_lds(int cnt, Load &load, Store &store) {
-    for (int i0 = threadIdx.x; i0 < cnt; i0 += B * blockDim.x) {
-        decltype(load(0)) v[B];
-#pragma unroll
-        for (int b = 0; b < B; b++) {
-            const int i = i0 + b * (int)blockDim.x;
-            if (i < cnt) v[b] = load(i);
-        }
-#pragma unroll
-        for (int b = 0; b < B; b++) {
-            const int i = i0 + b * (int)blockDim.x;
-            if (i < cnt) store(i, v[b]);
-        }
-    }
 }
 
 constexpr int kFftMaxThreads = 512;
@@ -497,24 +478,26 @@ __global__ __launch_bounds__(kFftMaxThreads) void k_fft_x_inv(int K1, int per,
     if (bid >= n * (n / Y)) return;
     const int z = bid / (n / Y), y0 = (bid - z * (n / Y)) * Y;
     const int pitch = lds_pitch<true>(n, NSEQ);
-    // the runs of modes 0..K (index i = (k 3 + c) Y + yy), then the twiddle
-    // table, in one batched copy; spectrum of (c, yy) at spec[(c Y + yy) K1]
-    const int nin = 3 * Y * K1;
-    auto gl = [&](int i) {
-        if (i >= nin) return tw[i - nin];
-        const int yy = i % Y, kc = i / Y, c = kc % 3, k = kc / 3;
-        return A[(size_t)k * nrows + ((size_t)c * n + z) * n + y0 + yy];
-    };
-    auto gs = [&](int i, C v) {
-        if (i < nin) {
-            const int yy = i % Y, kc = i / Y, c = kc % 3, k = kc / 3;
-            spec[(c * Y + yy) * K1 + k] = v;
-        } else {
-            twl[i - nin] = v;
-        }
-    };
-    gather_lds<8>(nin + n, gl, gs);
-    __syncthreads();
+    // the runs of modes 0..K, all of a thread's loads issued together with a
+    // fixed stride (as in k_fft_y_inv: 1.77 -> 1.61 ms at 512^3 in float64,
+    // 1.00 -> 0.91 in float32; twiddles from global memory instead of LDS took
+    // 1.91); spectrum of (c, yy) at spec[(c Y + yy) K1]
+    constexpr int NT = fft_threads(N, NSEQ), KS = NT / (3 * Y), PF = (n / 2 + KS - 1) / KS;
+    const int k0 = threadIdx.x / (3 * Y), r0 = threadIdx.x % (3 * Y), c0 = r0 / Y;
+    typedef R V2 __attribute__((ext_vector_type(2)));
+    V2 pf[PF];
+    const C *src = A + ((size_t)c0 * n + z) * n + y0 + (r0 - c0 * Y);
+    static_for<0, PF>([&](auto I) {
+        constexpr int b = decltype(I)::value;
+        pf[b] = *(const V2 *)&src[(size_t)min(k0 + b * KS, K1 - 1) * nrows];
+    });
+    stage_twiddles(twl, tw, n);
+    if (k0 < KS)   // (the rest of a thread count that 3 Y does not divide loads nothing new)
+        static_for<0, PF>([&](auto I) {
+            constexpr int b = decltype(I)::value;
+            if (k0 + b * KS < K1) spec[r0 * K1 + k0 + b * KS] = C{pf[b].x, pf[b].y};
+        });
+    lds_barrier();
     auto herm = [&](int c, int yy, int e) {
         const C *sp = spec + (c * Y + yy) * K1;
         C v = C{(R)0, (R)0};
@@ -552,9 +535,9 @@ __global__ __launch_bounds__(kFftMaxThreads) void k_fft_x_inv(int K1, int per,
     fft_run<true, N, IPT>(NSEQ, pitch, buf, twl, (R)1, load, lstore);
     typedef typename std::conditional<sizeof(R) == 8, double2, float4>::type V;
     constexpr int PER = 16 / (int)sizeof(R), NV = 3 * n * Y / PER;
-    const V *src = (const V *)outl;
+    const V *rows = (const V *)outl;
     V *dst = (V *)(grid + (size_t)3 * n * ((size_t)z * n + y0));
-    for (int i = threadIdx.x; i < NV; i += blockDim.x) dst[i] = src[i];
+    for (int i = threadIdx.x; i < NV; i += blockDim.x) dst[i] = rows[i];
 }
 
 // y forward: run_len sequences q = (3 kx + c) n + z0 + s (contiguous in A);
@@ -588,8 +571,12 @@ __global__ __launch_bounds__(kFftMaxThreads) void k_fft_y_fwd(int K, int per,
     }
 }
 
-// y inverse: the B runs of run_len sequences into LDS (modes |my| > K zero),
-// inverse FFT along y, whole sequences out to A
+// y inverse: the B runs of 8 sequences into LDS (modes |my| > K zero),
+// inverse FFT along y, whole sequences out to A.  All of a thread's loads are
+// issued together with fixed strides, before the twiddle table's (batches of 8
+// with the table among them: 0.94 ms at 512^3 in float64 against 0.68).
+// Measured slower: a workgroup striding over tiles with the next one's loads
+// in flight (0.82).
 template <typename R, int N>
 __global__ __launch_bounds__(kFftMaxThreads) void k_fft_y_inv(int K, int per,
                                                             const typename Cx<R>::T *__restrict__ B,
@@ -597,34 +584,34 @@ __global__ __launch_bounds__(kFftMaxThreads) void k_fft_y_inv(int K, int per,
                                                             typename Cx<R>::T *__restrict__ A) {
     typedef typename Cx<R>::T C;
     extern __shared__ unsigned char smem[];
-    constexpr int n = N, SEQ = y_inv_seqs<C>();
-    constexpr int IPT = fft_ipt(N, SEQ);
-    const int K1 = K + 1;
+    constexpr int n = N, SEQ = y_inv_seqs<C>(), NT = fft_threads(N, SEQ);
+    // thread (ky, s): modes ky, ky + KS, ... of sequence s
+    constexpr int IPT = fft_ipt(N, SEQ), KS = NT / SEQ, PF = (n + KS - 1) / KS;
+    static_assert(NT % SEQ == 0, "every thread loads");
+    const int K1 = K + 1, NY = 2 * K + 1;
     C *twl = (C *)smem, *buf = twl + n;
     const int bid = xcd_block(per);
     if (bid >= 3 * n / SEQ * K1) return;
     const size_t q0 = (size_t)bid * SEQ, kxc = q0 / n;
-    const int z0 = (int)(q0 % n);
     const int pitch = lds_pitch<true>(n, SEQ);
-    // the runs of modes |my| <= K (the rest zero), then the twiddle table, in
-    // one batched copy
-    const int nin = SEQ * n;
-    auto gl = [&](int i) {
-        C v = C{(R)0, (R)0};
-        if (i < nin) {
-            const int e = i / SEQ, my = e <= n / 2 ? e : e - n;
-            if (my >= -K && my <= K) v = B[((size_t)(my + K) * 3 * K1 + kxc) * n + z0 + i % SEQ];
-        } else {
-            v = tw[i - nin];
-        }
-        return v;
-    };
-    auto gs = [&](int i, C v) {
-        if (i < nin) buf[lds_at<true>(i % SEQ, i / SEQ, pitch)] = v;
-        else twl[i - nin] = v;
-    };
-    gather_lds<8>(nin + n, gl, gs);
-    __syncthreads();
+    const int k0 = threadIdx.x / SEQ, s0 = threadIdx.x % SEQ;
+    // (a plain vector type: the compiler keeps arrays of double2 in scratch)
+    typedef R V2 __attribute__((ext_vector_type(2)));
+    V2 pf[PF];
+    const C *src = B + kxc * n + (q0 % n) + s0;
+    static_for<0, PF>([&](auto I) {   // (clamped: loads without branches)
+        constexpr int b = decltype(I)::value;
+        pf[b] = *(const V2 *)&src[(size_t)min(k0 + b * KS, NY - 1) * 3 * K1 * n];
+    });
+    stage_twiddles(twl, tw, n);
+    static_for<0, PF>([&](auto I) {
+        constexpr int b = decltype(I)::value;
+        const int my = k0 + b * KS - K;
+        if (my <= K) buf[lds_at<true>(s0, my < 0 ? my + n : my, pitch)] = C{pf[b].x, pf[b].y};
+    });
+    for (int i = threadIdx.x; i < SEQ * (n - NY); i += NT)
+        buf[lds_at<true>(i % SEQ, K1 + i / SEQ, pitch)] = C{(R)0, (R)0};
+    lds_barrier();
     auto load = [&](int s, int e) { return buf[lds_at<true>(s, e, pitch)]; };
     auto store = [&](int s, int e, C v) { A[(q0 + s) * n + e] = v; };
     fft_run<true, N, IPT>(SEQ, pitch, buf, twl, (R)1, load, store);
