@@ -46,7 +46,11 @@ struct ScanSet {
     const int *in[3];
     int *out[3];
     int n[3], blk[4];
+    const int *lim;   // when set: the arrays' sizes, decided on the device (at most n)
 };
+__device__ __forceinline__ int scan_size(const ScanSet &S, int a) {
+    return S.lim ? S.lim[a] : S.n[a];
+}
 
 __device__ __forceinline__ int scan_array(const ScanSet &S) {
     return (int)blockIdx.x >= S.blk[2] ? 2 : ((int)blockIdx.x >= S.blk[1] ? 1 : 0);
@@ -54,7 +58,8 @@ __device__ __forceinline__ int scan_array(const ScanSet &S) {
 
 __global__ void k_scan_reduce(ScanSet S, int *__restrict__ sums) {
     __shared__ int sh[kScanBlock];
-    const int a = scan_array(S), n = S.n[a];
+    const int a = scan_array(S), n = scan_size(S, a);
+    if (((int)blockIdx.x - S.blk[a]) * kScanTile >= n) return;
     const int *in = S.in[a];
     int base = ((int)blockIdx.x - S.blk[a]) * kScanTile + threadIdx.x * kScanItems;
     int s = 0;
@@ -68,7 +73,7 @@ __global__ void k_scan_reduce(ScanSet S, int *__restrict__ sums) {
 // one workgroup per array; out[n] = total
 __global__ void k_scan_sums(ScanSet S, int *__restrict__ sums) {
     __shared__ int sh[kScanBlock];
-    const int a = blockIdx.x, nb = S.blk[a + 1] - S.blk[a];
+    const int a = blockIdx.x, n = scan_size(S, a), nb = (n + kScanTile - 1) / kScanTile;
     // nb <= kScanTile
     int *sa = sums + S.blk[a];
     int base = threadIdx.x * kScanItems;
@@ -83,12 +88,13 @@ __global__ void k_scan_sums(ScanSet S, int *__restrict__ sums) {
         if (base + k < nb) sa[base + k] = ex;
         ex += v[k];
     }
-    if (threadIdx.x == 0) S.out[a][S.n[a]] = tot;
+    if (threadIdx.x == 0) S.out[a][n] = tot;
 }
 
 __global__ void k_scan_apply(ScanSet S, const int *__restrict__ sums) {
     __shared__ int sh[kScanBlock];
-    const int a = scan_array(S), n = S.n[a];
+    const int a = scan_array(S), n = scan_size(S, a);
+    if (((int)blockIdx.x - S.blk[a]) * kScanTile >= n) return;
     const int *in = S.in[a];
     int *out = S.out[a];
     int base = ((int)blockIdx.x - S.blk[a]) * kScanTile + threadIdx.x * kScanItems;
@@ -105,9 +111,10 @@ __global__ void k_scan_apply(ScanSet S, const int *__restrict__ sums) {
     }
 }
 
-static void scan_arrays(bs_plan_t p, int na, const int *const *in, int *const *out, const int *n,
-                        int *sums) {
+void scan_arrays(bs_plan_t p, int na, const int *const *in, int *const *out, const int *n,
+                 int *sums, const int *lim) {
     ScanSet S{};
+    S.lim = lim;
     for (int a = 0; a < 3; a++) {
         if (a < na) { S.in[a] = in[a]; S.out[a] = out[a]; S.n[a] = n[a]; }
         S.blk[a + 1] = S.blk[a] + (a < na ? ceil_div(n[a], kScanTile) : 0);
@@ -118,11 +125,11 @@ static void scan_arrays(bs_plan_t p, int na, const int *const *in, int *const *o
     hipLaunchKernelGGL(k_scan_apply, g, b, 0, p->stream, S, (const int *)sums);
 }
 
-// out[0..n-1] = exclusive scan of in, out[n] = total.  in and out may not
-// alias.  Requires n <= kScanTile^2 (4.2 M bins); sums: kScanTile ints of
+// out[0..n-1] = exclusive scan of in, out[n] = total (n: S.lim's, if set).  in
+// and out may not alias.  Requires n <= kScanTile^2 (4.2 M bins); sums: kScanTile ints of
 // scratch, private to the stream.
 void exclusive_scan(bs_plan_t p, const int *in, int *out, int n, int *sums) {
-    scan_arrays(p, 1, &in, &out, &n, sums);
+    scan_arrays(p, 1, &in, &out, &n, sums, nullptr);
 }
 
 // Bins are ordered by original index (k_sort_all); a bin too large for LDS
@@ -385,7 +392,7 @@ void build_bins(bs_plan_t p) {
     if (maxb <= kScanSmall) {
         hipLaunchKernelGGL(k_scan_small, dim3(3), dim3(1024), 0, p->stream, S);
     } else {
-        scan_arrays(p, 3, S.cnt, S.start, S.nbins, (int *)p->red_tmp.p);
+        scan_arrays(p, 3, S.cnt, S.start, S.nbins, (int *)p->red_tmp.p, nullptr);
     }
     hipLaunchKernelGGL(k_scatter_all, dim3(ceil_div(2 * (int64_t)M + N, bs)), dim3(bs), 0, p->stream, S);
     hipLaunchKernelGGL(k_sort_all, dim3(S.ngrp[0] + S.ngrp[1] + S.ngrp[2]), dim3(64), 0, p->stream, S);

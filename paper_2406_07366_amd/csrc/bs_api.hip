@@ -507,7 +507,7 @@ static int set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, cons
             P->ns_ncmax = ncmax < 3 ? 3 : (ncmax > 128 ? 128 : ncmax);
             const size_t nb3 = (size_t)P->ns_ncmax * P->ns_ncmax * P->ns_ncmax;
             if ((rc = ensure<double>(P, P->ns_red, 2 * 1024 + 1)) ||
-                (rc = ensure<int>(P, P->ns_nc, 2)) || (rc = ensure<int>(P, P->ns_ckey, N)) ||
+                (rc = ensure<int>(P, P->ns_nc, 4)) || (rc = ensure<int>(P, P->ns_ckey, N)) ||
                 (rc = ensure<int>(P, P->ns_ccnt, 2 * nb3 + 1)) ||
                 (rc = ensure<int>(P, P->ns_cstart, 2 * nb3 + 1)) ||
                 (rc = ensure<int>(P, P->ns_cfill, 2 * nb3 + 1)) || (rc = ensure<int>(P, P->ns_cperm, N)) ||
@@ -517,6 +517,7 @@ static int set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, cons
                 (rc = ensure<double4>(P, P->ns_segA, N)) || (rc = ensure<double4>(P, P->ns_segB, N)) ||
                 (rc = ensure<float4>(P, P->ns_segM, N)) ||
                 (rc = ensure<float4>(P, P->ns_segH, N)) ||
+                (rc = ensure<float4>(P, P->ns_segP, N)) ||
                 (rc = ensure<int2>(P, P->ns_slots, mp)) || (rc = ensure<int>(P, P->ns_cnt, N + 1)) ||
                 (rc = ensure<int>(P, P->ns_start, N + 1)) || (rc = ensure<int2>(P, P->ns_pairs, mp)) ||
                 (rc = ensure<int>(P, P->ns_pnode, mp)) || (rc = ensure<double>(P, P->ns_pout, 3 * mp)))
@@ -975,7 +976,7 @@ int bs_destroy(bs_plan_t P) {
                    &P->nd_key, &P->nd_cnt, &P->nd_start, &P->nd_fill, &P->nd_perm, &P->nd_rec,
                    &P->scan_tmp, &P->red_tmp, &P->spline_tmp, &P->tmp3, &P->e_D, &P->e_S, &P->d_vls, &P->ns_red, &P->ns_nc, &P->ns_ckey,
                    &P->ns_ccnt, &P->ns_cstart, &P->ns_cfill, &P->ns_cperm, &P->ns_tkey, &P->ns_tcnt,
-                   &P->ns_tstart, &P->ns_tfill, &P->ns_tperm, &P->ns_segA, &P->ns_segB, &P->ns_segM, &P->ns_segH, &P->ns_slots,
+                   &P->ns_tstart, &P->ns_tfill, &P->ns_tperm, &P->ns_segA, &P->ns_segB, &P->ns_segM, &P->ns_segH, &P->ns_segP, &P->ns_slots,
                    &P->ns_cnt, &P->ns_start, &P->ns_pairs, &P->ns_pnode, &P->ns_pout,
                    &P->ns_X, &P->ns_Y, &P->ns_fallback, &P->ns_learn, &P->ns_fblist, &P->ns_vs, &P->rk_k,
                    &P->d_piece, &P->d_pfirst};

@@ -126,12 +126,12 @@ struct bs_plan_s {
     // near-singular pairs
     int ns_max_per_node = 64;                  // near-singular segments per target, at most
     int ns_ncmax = 3;                          // bound on the segment cell grid per axis
-    bs::DBuf ns_red, ns_nc;                    // f64 [1 + blocks] max reach, int32 cells per axis
+    bs::DBuf ns_red, ns_nc;                    // f64 [1 + blocks] max reach, int32 [4] cells
     bs::DBuf ns_ckey, ns_ccnt, ns_cstart, ns_cfill, ns_cperm;   // segments by midpoint cell
     bs::DBuf ns_tkey, ns_tcnt, ns_tstart, ns_tfill, ns_tperm;   // targets by node cell
     bs::DBuf ns_segA, ns_segB;                 // double4 [N] cell-ordered end points
-    bs::DBuf ns_segM, ns_segH;                 // float4 [N] flag-test capsules (midpoint,
-                                               // eta ell; half chord, periods)
+    bs::DBuf ns_segM, ns_segH, ns_segP;        // float4 [N] flag-test capsules (midpoint,
+                                               // eta ell; half chord, periods), spheres
     bs::DBuf ns_slots;                         // int2 [N][max_per_node] per-node flag output
     bs::DBuf ns_cnt, ns_start, ns_pairs, ns_pnode, ns_pout;
     // learned correction
@@ -185,6 +185,9 @@ void launch_local_self(bs_plan_t p, int mode, double sign, double *out);
 
 // binning.hip
 void exclusive_scan(bs_plan_t p, const int *in, int *out, int n, int *sums);
+// up to three arrays side by side; lim: their sizes on the device (NULL: n)
+void scan_arrays(bs_plan_t p, int na, const int *const *in, int *const *out, const int *n,
+                 int *sums, const int *lim);
 void build_bins(bs_plan_t p);
 // what the per-filament kernel needs to key and count the three bin sorts
 // (quadrature points by spread tile and by pair cell, nodes by pair cell);

@@ -9,8 +9,9 @@
 //
 // Passes (no host synchronisation):
 //   search  segments binned by chord midpoint, targets by node cell; one
-//           workgroup per target cell tests the window's segments and writes
-//           each node's flagged pairs in a fixed order; compacted pair list;
+//           wavefront per target cell culls the window's segments against the
+//           cell, tests its targets and writes each node's flagged pairs in a
+//           fixed order; compacted pair list;
 //   integrate  one thread per pair, float64, by one of
 //           - graded panels: closest point of the segment to the target by
 //             Newton steps, 10-point (cubic) or 12-point (quintic)
@@ -85,7 +86,10 @@ __global__ void k_ns_reach(int N, const double *__restrict__ x, const double *__
 // ones (its cells are at least as large as any reach): a target cell scans
 // the 4 x 4 x 4 B-cells from the B-cell of its lower corner minus one B edge.
 // nc_A < 3: one A-cell holds every segment (and grid B is empty); nc_B < 4:
-// one B-cell.  ncp[0] = nc_A, ncp[1] = nc_B.
+// one B-cell.  ncp[0] = nc_A, ncp[1] = nc_B; the bins of the segments, nc_A^3 +
+// nc_B^3, and of the targets, nc_A^3, in ncp[2], ncp[3] (the kernels below clear
+// and scan those, not all that the arrays hold: 39304 + 8000 of 2 x 2e6 on the
+// 1e6-node tangle).
 __global__ void k_ns_cells(const double *__restrict__ pmax, const double *__restrict__ psum,
                            int nparts, int N, double L, int ncmax, double *__restrict__ maxreach,
                            int *__restrict__ ncp) {
@@ -118,6 +122,8 @@ __global__ void k_ns_cells(const double *__restrict__ pmax, const double *__rest
         *maxreach = m;
         ncp[0] = na;
         ncp[1] = nb;
+        ncp[2] = na * na * na + nb * nb * nb;
+        ncp[3] = na * na * na;
     }
 }
 
@@ -129,6 +135,17 @@ __device__ __forceinline__ int cell_of(double v, double L, int nc) {
 __global__ void k_ns_zero(int n, int *__restrict__ a, int *__restrict__ b) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) { a[i] = 0; b[i] = 0; }
+}
+
+// bin counts and fill counters of the segments (a, b) and the targets (c, d)
+__global__ void k_ns_zero_bins(const int *__restrict__ ncp, int *__restrict__ a,
+                               int *__restrict__ b, int *__restrict__ c, int *__restrict__ d) {
+    const int ns = ncp[2], nt = ncp[3];   // nt < ns
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i <= ns; i += gridDim.x * blockDim.x) {
+        a[i] = 0;
+        b[i] = 0;
+        if (i <= nt) { c[i] = 0; d[i] = 0; }
+    }
 }
 
 // segment key: A-cell of the chord midpoint (short segments) or nc_A^3 +
@@ -214,12 +231,15 @@ __device__ __forceinline__ int pack_periods(const int *k) {
 // cell-ordered copies of each segment's end points, weight ell and index,
 // and the float32 capsule of the flag test: chord midpoint moved into the
 // box and eta ell (segM), half chord and the midpoint's packed period
-// indices (segH)
+// indices (segH); the sphere that the capsule lies in, midpoint and radius
+// |half chord| + eta ell + 1e-5 L (segP: the margin covers the float32
+// rounding of both points; infinite beyond the clamped period range)
 __global__ void k_ns_gather(int N, const int *__restrict__ perm, const double *__restrict__ x,
                             const double *__restrict__ xn,
                             const double *__restrict__ ell, double eta, double L,
                             double4 *__restrict__ segA, double4 *__restrict__ segB,
-                            float4 *__restrict__ segM, float4 *__restrict__ segH) {
+                            float4 *__restrict__ segM, float4 *__restrict__ segH,
+                            float4 *__restrict__ segP) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= N) return;
     const int j = perm[p];
@@ -234,10 +254,14 @@ __global__ void k_ns_gather(int N, const int *__restrict__ perm, const double *_
     // a midpoint beyond the clamped period range gets a negative eta ell,
     // which sends every test against it to the float64 decision
     const bool clamped = abs(k[0]) == 511 || abs(k[1]) == 511 || abs(k[2]) == 511;
-    segM[p] = make_float4((float)m[0], (float)m[1], (float)m[2],
-                          clamped ? -1.f : (float)(eta * ell[j]));
-    segH[p] = make_float4((float)h[0], (float)h[1], (float)h[2],
-                          __int_as_float(pack_periods(k)));
+    const float hx = (float)h[0], hy = (float)h[1], hz = (float)h[2], rl = (float)(eta * ell[j]);
+    segM[p] = make_float4((float)m[0], (float)m[1], (float)m[2], clamped ? -1.f : rl);
+    segH[p] = make_float4(hx, hy, hz, __int_as_float(pack_periods(k)));
+    // (a negative or NaN eta ell passes every target on to the capsule test)
+    segP[p] = make_float4((float)m[0], (float)m[1], (float)m[2],
+                          !clamped && rl >= 0.f
+                              ? sqrtf(hx * hx + hy * hy + hz * hz) + rl + (float)(1e-5 * L)
+                              : INFINITY);
 }
 
 // chord distance from x to segment A->B with A, B shifted by the minimum
@@ -264,7 +288,7 @@ struct NsArgs {
     const double *x;
     const int *off, *fil, *ncp, *cstart, *segj;
     const double4 *segA, *segB;
-    const float4 *segM, *segH;
+    const float4 *segM, *segH, *segP;
 };
 
 // Target of a flag test: the node, its previous node (the two adjacent
@@ -365,275 +389,212 @@ __device__ __forceinline__ bool ns_test(const NsArgs &a, const NsTarget &T, floa
     return true;
 }
 
-// Necessary condition for ns_test to accept: a target within eta ell of
-// the chord lies within eta ell + |half chord| of the chord midpoint's
-// nearest image.  The staged midpoint m is that image for every target of
-// the cell (section below), r2m = (|h| + eta ell + 1e-5 L)^2 (the margin
-// covers the float32 rounding of both points), infinite for records that
-// every target passes.
-__device__ __forceinline__ bool ns_pretest(const float *xf, float4 M4, float r2m) {
-    const float d0 = xf[0] - M4.x, d1 = xf[1] - M4.y, d2 = xf[2] - M4.z;
-    return fmaf(d2, d2, fmaf(d1, d1, d0 * d0)) < r2m;
-}
-
-// Lanes 0..26 of a wavefront: start and size of one of the 27 cells around
-// cell (c0x, c0y, c0z) (lane 0: the single cell when nc < 3); returns the
-// lane's exclusive prefix of the sizes and the total in *total.
-__device__ __forceinline__ int ns_window(const NsArgs &a, int nc, const int *c0, int lane,
-                                         int *cs, int *cn, int *total) {
-    const int ncell = nc >= 3 ? 27 : 1;
-    *cs = 0; *cn = 0;
-    if (lane < ncell) {
-        int cidx = 0;
-        if (nc >= 3) {
-            const int dd[3] = {lane % 3 - 1, (lane / 3) % 3 - 1, lane / 9 - 1};
-            int c[3];
-            for (int q = 0; q < 3; q++) {
-                int v = c0[q] + dd[q];
-                c[q] = v < 0 ? v + nc : (v >= nc ? v - nc : v);
-            }
-            cidx = (c[2] * nc + c[1]) * nc + c[0];
+// Range r of a target cell's window in cell order, as its first cell and its
+// length in cells.  The window's rows of cells along x are contiguous there
+// apart from the wrap, so each is one or two ranges: 0 .. 17, the 3 x 3 rows of
+// A-cells around cell (cx, cy, cz); 18 .. 49, the 4 x 4 rows of B-cells from the
+// B-cell of its lower corner minus one B edge (or the single cell of either).
+__device__ __forceinline__ void ns_range(const NsArgs &a, int nc, int ncb, const int *c0, int r,
+                                         int *first, int *len) {
+    const bool A = r < 18;
+    const int row = (A ? r : r - 18) >> 1, half = r & 1, n = A ? nc : ncb, w = A ? 3 : 4;
+    *first = *len = 0;
+    if (r >= 50) return;
+    if (n < w) {   // one cell
+        *first = A ? 0 : nc * nc * nc;
+        *len = r == 0 || r == 18 ? 1 : 0;
+        return;
+    }
+    int b[3];
+    for (int q = 0; q < 3; q++) {
+        if (A) {
+            b[q] = c0[q] - 1;
+        } else {
+            const double ha = a.L / nc, hb = a.L / ncb;
+            b[q] = (int)floor((c0[q] * ha - hb) / hb) % n;
         }
-        *cs = a.cstart[cidx];
-        *cn = a.cstart[cidx + 1] - *cs;
+        if (b[q] < 0) b[q] += n;
     }
-    int incl = *cn;
-    for (int d = 1; d < 64; d <<= 1) {
-        const int v = __shfl_up(incl, d);
-        if (lane >= d) incl += v;
-    }
-    *total = __shfl(incl, 63);
-    return incl - *cn;
+    int y = b[1] + row % w, z = b[2] + row / w;
+    if (y >= n) y -= n;
+    if (z >= n) z -= n;
+    const int n0 = b[0] + w <= n ? w : n - b[0];   // cells before the wrap
+    *first = (A ? 0 : nc * nc * nc) + (z * n + y) * n + (half ? 0 : b[0]);
+    *len = half ? w - n0 : n0;
 }
 
-// Used when fewer than 3 cells fit along an axis (one cell holds every
-// segment): one wavefront per target, 64 candidates per step, flagged ones
-// ranked with a ballot and written in candidate order to the target's
-// max_per_node slots.
-__global__ __launch_bounds__(256) void k_ns_flag(NsArgs a, int *__restrict__ cnt,
-                                                 int2 *__restrict__ slots,
-                                                 int *__restrict__ status) {
-    if (*a.ncp >= 3) return;
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = gid & 63;
+// Search of the window, one wavefront at a time.  A wavefront takes targets of
+// one cell, at most 64, one per lane, and the segments of the window's rows of
+// cells in three steps:
+// - cull: 64 segments per step, one per lane, are kept when their sphere (segP)
+//   reaches the cell's box, for all targets at once (of ~800 segments per cell
+//   of the 1e6-node tangle, a quarter);
+// - sphere: the kept ones, up to 256, stay in registers, and each target in
+//   turn, its position in scalar registers, is tested against them;
+// - capsule: the (target, segment) pairs that pass, queued target by target and
+//   in candidate order, take the capsule test 64 at a time, whatever target
+//   they belong to.
+// Each target's pairs are written in candidate order to its max_per_node slots.
+// Before, a workgroup per cell staged every segment of the window and tested
+// every target against all of them, with a capsule queue for each target that
+// was rarely half full: 1.53 ms on the 1e6-node tangle against 0.50.
+//
+// A cell's targets are cut into pieces of 64 (of tper in the case of one cell,
+// whose segments all go to the capsule test); a piece belongs to the wavefront
+// whose range of tper consecutive targets, in cell order, holds its first.
+constexpr int kNsChunk = 256;
+struct NsLds {
+    float4 c[kNsChunk];        // kept segments: midpoint at its image nearest the cell's
+    int p[kNsChunk];           // centre, sphere radius squared; index in cell order
+    float4 tx[64];             // targets: position, periods
+    int2 ti[64];               // and node, previous node
+    int off[64], st[64];       // ranges: first candidate number, first segment
+    int tk[64];                // pairs of each target so far
+    unsigned short q[kNsChunk + 64];   // queue: 256 target + segment
+};
+
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_ns_flag(
+    NsArgs a, int per, int tper, const int *__restrict__ tkey, const int *__restrict__ tstart,
+    const int *__restrict__ tperm, int *__restrict__ cnt, int2 *__restrict__ slots,
+    int *__restrict__ status) {
+    __shared__ NsLds S;
+    const int lane = threadIdx.x, w = xcd_block(per), nc = a.ncp[0], ncb = a.ncp[1];
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int t = gid >> 6; t < a.N; t += (gridDim.x * blockDim.x) >> 6) {
-        const NsTarget T = ns_target(a, t);
-        const int zero[3] = {0, 0, 0};
-        int cs, cn, total;
-        ns_window(a, 1, zero, lane, &cs, &cn, &total);
-        const int s0 = __shfl(cs, 0);
-        int2 *out = slots + (size_t)T.o * a.max_per_node;
-        int k = 0;
-        for (int q0 = 0; q0 < total; q0 += 64) {
-            const int q = q0 + lane;
-            int sg = 0, sh = 0;
-            const bool flag =
-                q < total && ns_test(a, T, a.segM[s0 + q], a.segH[s0 + q], s0 + q, &sg, &sh);
-            const unsigned long long m = __ballot(flag);
-            if (flag) {
-                const int slot = k + __popcll(m & below);
-                if (slot < a.max_per_node) out[slot] = make_int2(sg, sh);
-            }
-            k += __popcll(m);
+    const float Lf = (float)a.L, iLf = (float)(1.0 / a.L);
+    const float half = (float)(0.5 * a.L / nc);
+    const int piece = nc < 3 ? tper : 64;
+    const int w0 = (int)min((int64_t)w * tper, (int64_t)a.N), w1 = min(w0 + tper, a.N);
+    for (int pos = w0; pos < w1;) {
+        const int C = tkey[tperm[pos]], cs = tstart[C], ce = tstart[C + 1];
+        const int t0 = cs + (pos - cs + piece - 1) / piece * piece;   // first piece from pos on
+        if (t0 >= min(ce, w1)) {
+            pos = min(ce, w1);
+            continue;
         }
-        if (lane == 0) {
-            if (k > a.max_per_node) atomicOr(status, 2);
-            cnt[T.o] = k < a.max_per_node ? k : a.max_per_node;
-        }
-    }
-}
-
-// One workgroup per cell of targets (nc >= 3).  The segment records of the
-// 27 cells around it (cell order, then segment order) are staged in LDS in
-// chunks of kNsStage and shared by every target of the cell; wavefront w
-// takes targets w, w + 4, ...  and scans each chunk 64 candidates per step.
-// Flagged candidates are ranked with a ballot, so each target's pairs are
-// written in candidate order to its max_per_node slots.  Targets are taken
-// 256 at a time (their running counts live in LDS).  A cheap sphere test
-// (ns_pretest) runs first on every candidate; the ~3 % that pass it are
-// queued per wavefront, in candidate order, and the capsule test runs on
-// the queue 64 at a time, so the order of each target's pairs is that of
-// the full scan.  Records of 40 B (two float4 capsules, the sphere radius
-// and the index), 512 at a time, and at most 96 VGPRs keep five wavefronts
-// per SIMD.
-constexpr int kNsStage = 512;
-
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_ns_flag_cells(NsArgs a, const int *__restrict__ tstart,
-                                                       const int *__restrict__ tperm,
-                                                       int *__restrict__ cnt,
-                                                       int2 *__restrict__ slots,
-                                                       int *__restrict__ status) {
-    __shared__ float4 sm[kNsStage], sh4[kNsStage];
-    __shared__ int sp[kNsStage];
-    __shared__ float sr2[kNsStage];
-    __shared__ short sq[4][128];   // per wavefront: queued candidates
-    // window: the 27 A-cells (entries 0..26), then the B-cells (27..90)
-    constexpr int kWin = 27 + 64;
-    __shared__ int cell_s[kWin], cell_o[kWin], tk[256], tot_a, tot_b;
-    __shared__ int t_o[256], t_ip[256], t_kp[256];   // targets of the group (kp bit 30: exact)
-    __shared__ float t_xf[3][256];
-    const int nc = a.ncp[0], ncb = a.ncp[1];
-    if (nc < 3) return;
-    const int nb3 = nc * nc * nc;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float Lf = (float)a.L, iLf = (float)(1.0 / a.L), band = (float)(1e-5 * a.L);
-    const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int C = blockIdx.x; C < nb3; C += gridDim.x) {
-        const int t0 = tstart[C], nt = tstart[C + 1] - t0;
-        if (nt == 0) continue;   // uniform over the workgroup
+        const int t1 = pos = min(t0 + piece, ce);
+        const int ng = t1 - t0;
+        NsTarget T{};
+        if (lane < ng) T = ns_target(a, tperm[t0 + lane]);
+        const unsigned long long exm = __ballot(T.exact);
         const int c0[3] = {C % nc, (C / nc) % nc, C / (nc * nc)};
         const float cc[3] = {(float)((c0[0] + 0.5) * a.L / nc), (float)((c0[1] + 0.5) * a.L / nc),
                              (float)((c0[2] + 0.5) * a.L / nc)};   // the cell's centre
-        if (wave == 0) {
-            int cs, cn, total;
-            const int excl = ns_window(a, nc, c0, lane, &cs, &cn, &total);
-            if (lane < 27) { cell_s[lane] = cs; cell_o[lane] = excl; }
-            if (lane == 0) tot_a = total;
-        } else if (wave == 1) {
-            // B-cells: 4 per axis from the B-cell of (lower corner - B edge),
-            // or the single B-cell
-            int cs = 0, cn = 0;
-            if (ncb >= 4 || lane == 0) {
-                int cidx = 0;
-                if (ncb >= 4) {
-                    const double ha = a.L / nc, hb = a.L / ncb;
-                    const int dd[3] = {lane & 3, (lane >> 2) & 3, lane >> 4};
-                    int c[3];
-                    for (int q = 0; q < 3; q++) {
-                        int v = (int)floor((c0[q] * ha - hb) / hb) + dd[q];
-                        v %= ncb;
-                        c[q] = v < 0 ? v + ncb : v;
-                    }
-                    cidx = (c[2] * ncb + c[1]) * ncb + c[0];
-                }
-                cidx += nb3;
-                cs = a.cstart[cidx];
-                cn = a.cstart[cidx + 1] - cs;
-            }
-            int incl = cn;
-            for (int d = 1; d < 64; d <<= 1) {
-                const int v = __shfl_up(incl, d);
-                if (lane >= d) incl += v;
-            }
-            cell_s[27 + lane] = cs;
-            cell_o[27 + lane] = incl - cn;   // relative; tot_a added below
-            if (lane == 63) tot_b = incl;
-        }
-        __syncthreads();
-        if (threadIdx.x < 64) cell_o[27 + threadIdx.x] += tot_a;
-        __syncthreads();
-        const int total = tot_a + tot_b;
-        for (int g0 = 0; g0 < nt; g0 += 256) {
-            const int ng = nt - g0 < 256 ? nt - g0 : 256;
-            // each target's flag-test data, once (one thread per target; the
-            // chunk loop below reads it from LDS)
-            for (int i = threadIdx.x; i < ng; i += blockDim.x) {
-                const NsTarget T = ns_target(a, tperm[t0 + g0 + i]);
-                tk[i] = 0;
-                t_o[i] = T.o;
-                t_ip[i] = T.ip;
-                t_kp[i] = T.kp | (T.exact ? 1 << 30 : 0);
-                t_xf[0][i] = T.xf[0]; t_xf[1][i] = T.xf[1]; t_xf[2][i] = T.xf[2];
-            }
-            for (int c0 = 0; c0 < total; c0 += kNsStage) {
-                const int cn = total - c0 < kNsStage ? total - c0 : kNsStage;
-                for (int i = threadIdx.x; i < cn; i += blockDim.x) {
-                    const int q = c0 + i;
-                    int c = 0;
-                    for (int step = 64; step > 0; step >>= 1) {
-                        const int tc = c + step;
-                        if (tc < kWin && cell_o[tc] <= q) c = tc;
-                    }
-                    const int p = cell_s[c] + (q - cell_o[c]);
-                    float4 M4 = a.segM[p], H4 = a.segH[p];
-                    // the midpoint's image nearest the cell's centre, with its
-                    // period indices moved by the same shift (the capsule
-                    // test's float decision and image shift are unchanged):
-                    // for every target of the cell that is the nearest image
-                    // when the window lies within 0.45 L of the cell
-                    // (window A: 2 h_A, five or more cells per axis; window
-                    // B: 3 h_B, eight or more).  Other records, and midpoints
-                    // beyond the clamped period range (negative eta ell, sent
-                    // to the float64 decision), pass every target.
-                    float r2m = INFINITY;
-                    if ((q < tot_a ? nc >= 5 : ncb >= 8) && M4.w >= 0.f) {
-                        int km = __float_as_int(H4.w);
-                        float m[3] = {M4.x, M4.y, M4.z};
+        int first, len;
+        ns_range(a, nc, ncb, c0, lane, &first, &len);
+        const int rs = a.cstart[first], rn = a.cstart[first + len] - rs;
+        const int incl = wave_incl_sum(rn);
+        S.off[lane] = incl - rn;
+        S.st[lane] = rs;
+        S.tk[lane] = 0;
+        S.tx[lane] = make_float4(T.xf[0], T.xf[1], T.xf[2], __int_as_float(T.kp));
+        S.ti[lane] = make_int2(T.o, T.ip);
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        const int tot_a = __builtin_amdgcn_readlane(incl, 17);
+        wave_lds_sync();
+
+        int ns = 0;   // kept segments of the chunk
+        for (int q0 = 0; q0 < total;) {
+            const int q = q0 + lane;
+            int r = 0;
+            for (int step = 32; step > 0; step >>= 1)
+                if (S.off[r + step] <= q) r += step;
+            const int p = q < total ? S.st[r] + (q - S.off[r]) : 0;
+            float4 c = a.segP[p];
+            // The midpoint's image nearest the cell's centre: for every target
+            // of the cell that is the nearest image when the window lies
+            // within 0.45 L of the cell (window A: 2 h_A, five or more cells
+            // per axis; window B: 3 h_B, eight or more).  Other segments pass
+            // every target.
+            const bool near = q < tot_a ? nc >= 5 : ncb >= 8;
+            c.w = near ? c.w * c.w : INFINITY;
+            float m[3] = {c.x, c.y, c.z}, d2 = 0.f;
 #pragma unroll
-                        for (int ax = 0; ax < 3; ax++) {
-                            const float sft = rintf((cc[ax] - m[ax]) * iLf);
-                            m[ax] = fmaf(Lf, sft, m[ax]);
-                            km -= (int)sft * (1 << (20 - 10 * ax));
-                        }
-                        M4.x = m[0]; M4.y = m[1]; M4.z = m[2];
-                        H4.w = __int_as_float(km);
-                        const float r = sqrtf(H4.x * H4.x + H4.y * H4.y + H4.z * H4.z) + M4.w + band;
-                        r2m = r * r;
-                    }
-                    sm[i] = M4;
-                    sh4[i] = H4;
-                    sp[i] = p;
-                    sr2[i] = r2m;
-                }
-                __syncthreads();
-                for (int ti = wave; ti < ng; ti += 4) {
-                    NsTarget T;
-                    T.o = t_o[ti];
-                    T.ip = t_ip[ti];
-                    T.kp = t_kp[ti] & ((1 << 30) - 1);
-                    T.exact = (t_kp[ti] >> 30) & 1;
-                    T.xf[0] = t_xf[0][ti]; T.xf[1] = t_xf[1][ti]; T.xf[2] = t_xf[2][ti];
-                    int2 *out = slots + (size_t)T.o * a.max_per_node;
-                    int k = tk[ti];
-                    short *qw = sq[wave];
-                    // capsule test on the first nq (<= 64) queued candidates
-                    auto drain = [&](int nq) {
-                        const int j = lane < nq ? qw[lane] : 0;
-                        int sg = 0, sh = 0;
-                        const bool flag =
-                            lane < nq && ns_test(a, T, sm[j], sh4[j], sp[j], &sg, &sh);
-                        const unsigned long long m = __ballot(flag);
-                        if (flag) {
-                            const int slot = k + __popcll(m & below);
-                            if (slot < a.max_per_node) out[slot] = make_int2(sg, sh);
-                        }
-                        k += __popcll(m);
-                    };
-                    // pre-test 64 candidates per step while any are left; drain
-                    // the queue when it holds 64, and to the end after the last
-                    int nq = 0;
-                    for (int j0 = 0;;) {
-                        if (j0 < cn) {
-                            const int j = j0 + lane;
-                            const bool pass =
-                                j < cn && (T.exact || ns_pretest(T.xf, sm[j], sr2[j]));
-                            const unsigned long long m = __ballot(pass);
-                            if (pass) qw[nq + __popcll(m & below)] = (short)j;
-                            nq += __popcll(m);
-                            j0 += 64;
-                        }
-                        const bool done = j0 >= cn;
-                        if (nq >= 64 || (done && nq > 0)) {
-                            const int d = nq < 64 ? nq : 64;
-                            drain(d);
-                            const short rest = lane < nq - d ? qw[d + lane] : (short)0;
-                            if (lane < nq - d) qw[lane] = rest;
-                            nq -= d;
-                        }
-                        if (done && nq == 0) break;
-                    }
-                    if (lane == 0) tk[ti] = k;
-                }
-                __syncthreads();
+            for (int ax = 0; ax < 3; ax++) {
+                m[ax] = fmaf(Lf, rintf((cc[ax] - m[ax]) * iLf), m[ax]);
+                const float d = fmaxf(fabsf(m[ax] - cc[ax]) - half, 0.f);
+                d2 = fmaf(d, d, d2);
             }
-            for (int i = threadIdx.x; i < ng; i += blockDim.x) {
-                const int o = t_o[i], k = tk[i];
-                if (k > a.max_per_node) atomicOr(status, 2);
-                cnt[o] = k < a.max_per_node ? k : a.max_per_node;
+            const bool keep = q < total && (exm || !(d2 >= c.w));
+            const unsigned long long km = __ballot(keep);
+            if (keep) {
+                const int j = ns + __popcll(km & below);
+                S.c[j] = make_float4(m[0], m[1], m[2], c.w);
+                S.p[j] = p;
             }
-            __syncthreads();
+            ns += __popcll(km);
+            q0 += 64;
+            if (ns == 0 || (ns <= kNsChunk - 64 && q0 < total)) continue;
+
+            // the chunk: sphere test of every target, capsule tests
+            wave_lds_sync();
+            float4 k4[kNsChunk / 64];
+#pragma unroll
+            for (int b = 0; b < kNsChunk / 64; b++) {
+                k4[b] = S.c[min(64 * b + lane, ns - 1)];
+                if (64 * b + lane >= ns) k4[b].w = -1.f;   // passes no target
+            }
+            int nq = 0;
+            for (int ti = 0; ti < ng; ti++) {
+                const float x0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(T.xf[0]), ti));
+                const float x1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(T.xf[1]), ti));
+                const float x2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(T.xf[2]), ti));
+                const bool exact = (exm >> ti) & 1ull;
+#pragma unroll
+                for (int b = 0; b < kNsChunk / 64; b++) {
+                    if (64 * b < ns) {
+                        const float d0 = x0 - k4[b].x, d1 = x1 - k4[b].y, d2 = x2 - k4[b].z;
+                        const bool pass = exact ? 64 * b + lane < ns
+                                                : fmaf(d2, d2, fmaf(d1, d1, d0 * d0)) < k4[b].w;
+                        const unsigned long long pm = __ballot(pass);
+                        if (pass)
+                            S.q[nq + __popcll(pm & below)] =
+                                (unsigned short)(ti * kNsChunk + 64 * b + lane);
+                        nq += __popcll(pm);
+                    }
+                }
+                // capsule tests: full groups of 64, the rest after the last target
+                int qh = 0;
+                for (; nq - qh >= 64 || (ti == ng - 1 && nq > qh); qh += 64) {
+                    wave_lds_sync();
+                    const bool act = qh + lane < nq;
+                    const int e = act ? S.q[qh + lane] : 0, et = e / kNsChunk;
+                    const int sp = S.p[e % kNsChunk], base = S.tk[et];
+                    const float4 tx = S.tx[et];
+                    const int2 ti2 = S.ti[et];
+                    const NsTarget X{ti2.x, ti2.y, __float_as_int(tx.w), (bool)((exm >> et) & 1ull),
+                                     {tx.x, tx.y, tx.z}};
+                    int sg = 0, sh = 0;
+                    const bool flag =
+                        act && ns_test(a, X, a.segM[sp], a.segH[sp], sp, &sg, &sh);
+                    // rank among the target's flagged entries of the group
+                    const int prev = __shfl_up(et, 1);
+                    const unsigned long long fm = __ballot(flag),
+                                             hm = __ballot(lane == 0 || et != prev);
+                    const int run = 63 - __clzll((long long)(hm & (below | (1ull << lane))));
+                    if (flag) {
+                        const int slot = base + __popcll(fm & below & (~0ull << run));
+                        if (slot < a.max_per_node)
+                            slots[(size_t)X.o * a.max_per_node + slot] = make_int2(sg, sh);
+                        atomicAdd(&S.tk[et], 1);
+                    }
+                }
+                if (qh) {   // the rest (fewer than 64) to the front
+                    wave_lds_sync();
+                    const unsigned short v = S.q[min(qh + lane, kNsChunk + 63)];
+                    wave_lds_sync();
+                    nq = max(nq - qh, 0);
+                    if (lane < nq) S.q[lane] = v;
+                }
+            }
+            ns = 0;
+            wave_lds_sync();
         }
+        if (lane < ng) {
+            const int k = S.tk[lane];
+            if (k > a.max_per_node) atomicOr(status, 2);
+            cnt[T.o] = k < a.max_per_node ? k : a.max_per_node;
+        }
+        wave_lds_sync();
     }
 }
 
@@ -1484,15 +1445,16 @@ void ns_build_pairs(bs_plan_t p) {
     int *tkey = (int *)p->ns_tkey.p, *tcnt = (int *)p->ns_tcnt.p, *tstart = (int *)p->ns_tstart.p;
     int *tfill = (int *)p->ns_tfill.p, *tperm = (int *)p->ns_tperm.p;
     // segment keys span both grids (nc_B <= nc_A <= ncmax)
-    hipLaunchKernelGGL(k_ns_zero, dim3(ceil_div(2 * nb3 + 1, bs)), dim3(bs), 0, p->stream,
-                       2 * nb3 + 1, ccnt, cfill);
-    hipLaunchKernelGGL(k_ns_zero, dim3(ceil_div(nb3 + 1, bs)), dim3(bs), 0, p->stream, nb3 + 1,
-                       tcnt, tfill);
+    const int nzero = ceil_div(2 * nb3 + 1, bs);
+    hipLaunchKernelGGL(k_ns_zero_bins, dim3(nzero < 512 ? nzero : 512), dim3(bs), 0, p->stream,
+                       (const int *)ncp, ccnt, cfill, tcnt, tfill);
     hipLaunchKernelGGL(k_ns_keys, dim3(ceil_div(N, bs)), dim3(bs), 0, p->stream, N, x, xn,
                        ell, p->prm.ns_eta, p->prm.L, (const int *)ncp, ckey, ccnt, tkey, tcnt);
     int *sums = (int *)p->scan_tmp.p;   // the search may run on the side stream
-    exclusive_scan(p, ccnt, cstart, 2 * nb3, sums);
-    exclusive_scan(p, tcnt, tstart, nb3, sums);
+    const int *const sin[2] = {ccnt, tcnt};
+    int *const sout[2] = {cstart, tstart};
+    const int sn[2] = {2 * nb3, nb3};
+    scan_arrays(p, 2, sin, sout, sn, sums, ncp + 2);
     hipLaunchKernelGGL(k_ns_scatter, dim3(ceil_div(N, bs)), dim3(bs), 0, p->stream, N,
                        (const int *)ckey, (const int *)cstart, cfill, cperm, (const int *)tkey,
                        (const int *)tstart, tfill, tperm);
@@ -1502,7 +1464,7 @@ void ns_build_pairs(bs_plan_t p) {
     hipLaunchKernelGGL(k_ns_gather, dim3(ceil_div(N, bs)), dim3(bs), 0, p->stream, N,
                        (const int *)cperm, x, xn, ell, p->prm.ns_eta, p->prm.L,
                        (double4 *)p->ns_segA.p, (double4 *)p->ns_segB.p,
-                       (float4 *)p->ns_segM.p, (float4 *)p->ns_segH.p);
+                       (float4 *)p->ns_segM.p, (float4 *)p->ns_segH.p, (float4 *)p->ns_segP.p);
     NsArgs a;
     a.N = N; a.max_per_node = p->ns_max_per_node;
     a.L = p->prm.L; a.eta = p->prm.ns_eta;
@@ -1510,20 +1472,16 @@ void ns_build_pairs(bs_plan_t p) {
     a.ncp = ncp; a.cstart = cstart;
     a.segA = (const double4 *)p->ns_segA.p; a.segB = (const double4 *)p->ns_segB.p;
     a.segM = (const float4 *)p->ns_segM.p; a.segH = (const float4 *)p->ns_segH.p;
+    a.segP = (const float4 *)p->ns_segP.p;
     a.segj = (const int *)cperm;
     int *cnt = (int *)p->ns_cnt.p, *start = (int *)p->ns_start.p;
-    // exactly one of the two does work, depending on the cell count.  The
-    // cells' target counts are uneven, so the cell kernel's workgroups stride
-    // over many more cells than fit at once (~1500 resident): 20000 of them
-    // balance the last rounds better than 8192 (1.58 -> 1.53 ms on the
-    // 1e6-node tangle), while one per cell pays for the many empty ones.
-    constexpr int kNsFlagBlocks = 20000;
-    hipLaunchKernelGGL(k_ns_flag_cells, dim3(nb3 < kNsFlagBlocks ? nb3 : kNsFlagBlocks), dim3(bs), 0, p->stream, a,
-                       (const int *)tstart, (const int *)tperm, cnt, (int2 *)p->ns_slots.p,
-                       (int *)p->d_status.p);
-    const int nwave = ceil_div((int64_t)N * 64, bs);
-    hipLaunchKernelGGL(k_ns_flag, dim3(nwave < 1024 ? nwave : 1024), dim3(bs), 0, p->stream, a,
-                       cnt, (int2 *)p->ns_slots.p, (int *)p->d_status.p);
+    // targets per wavefront: 16, fewer where that leaves under 8192 wavefronts
+    int tper = 1;
+    while (tper < 16 && (int64_t)tper * 8192 < N) tper *= 2;
+    const int per = ceil_div(ceil_div(N, tper), 8);
+    hipLaunchKernelGGL(k_ns_flag, dim3(8 * per), dim3(64), 0, p->stream, a, per, tper,
+                       (const int *)tkey, (const int *)tstart, (const int *)tperm, cnt,
+                       (int2 *)p->ns_slots.p, (int *)p->d_status.p);
     exclusive_scan(p, cnt, start, N, sums);
     hipLaunchKernelGGL(k_ns_compact, dim3(ceil_div((int64_t)N * kNsCompactLanes, bs)), dim3(bs),
                        0, p->stream, N, p->ns_max_per_node, (const int *)cnt, (const int *)start,
