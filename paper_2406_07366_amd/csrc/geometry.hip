@@ -600,7 +600,11 @@ __global__ __launch_bounds__(128) void k_filament(int nfil, const int *__restric
 // kernel values 4.3, records and stores 2 us; on the 64^3 ellipses it takes 16 us
 // where the kernel above and the gather took 15 + 6.5 and the sorts 14).
 // Four lanes per node share the local - self term; the kernel values of the
-// spread and the records of the pair sums are written here too.
+// spread and the records of the pair sums are written here too.  With parts > 1
+// workgroups per filament each solves the spline for itself and the rest is
+// shared out: the nodes' terms and arrays to the first, the points' to the others
+// (few filaments leave the chip idle: one 64-node ring 14.4 -> 10.1 us, the two
+// quintic rings of the leapfrog 20.0 -> 16.2, the 40 ellipses 14.8 -> 11.6).
 template <int ORDER>
 struct FilLds {
     static constexpr int M = kDirectFil;
@@ -684,10 +688,14 @@ __global__ __launch_bounds__(256) void k_filament_direct(
     double *__restrict__ dtau, double *__restrict__ D, double *__restrict__ sdd,
     double *__restrict__ qpos, double *__restrict__ qchg, double *__restrict__ ell,
     int *__restrict__ status, double *__restrict__ gscratch, GLArgs gl, LocalArgs la,
-    double *__restrict__ vls, DirectOut dx) {
+    double *__restrict__ vls, DirectOut dx, int parts) {
     __shared__ FilLds<ORDER> F;
-    const int f = blockIdx.x, b0 = off[f], n = off[f + 1] - b0, Q = la.Q;   // n <= kDirectFil
+    const int f = blockIdx.x / parts, part = blockIdx.x - f * parts, b0 = off[f], n = off[f + 1] - b0, Q = la.Q;   // n <= kDirectFil
     const int tid = threadIdx.x;
+    // this workgroup's share: the nodes, and part sub of nsub of the points (none
+    // if negative)
+    const bool nodes = part == 0;
+    const int sub = parts > 1 ? part - 1 : 0, nsub = parts > 1 ? parts - 1 : 1;
     const double g = gs[f];
     for (int i = tid; i < 3 * n; i += blockDim.x) F.x[i] = xs[3 * b0 + i];
     __syncthreads();
@@ -716,43 +724,46 @@ __global__ __launch_bounds__(256) void k_filament_direct(
         geometry_seg<ORDER>(k, k + 1 == n ? 0 : k + 1, g, Q, gl, F.x, F.xn, F.h, F.D, F.qp, F.qc,
                             F.S, F.ell);
     __syncthreads();
-    for (int t0 = 0; t0 < 4 * n; t0 += blockDim.x) {   // whole wavefronts: the lanes exchange
+    for (int t0 = 0; nodes && t0 < 4 * n; t0 += blockDim.x) {   // whole wavefronts: the lanes exchange
         const int kk = (t0 + tid) >> 2, k = kk < n ? kk : n - 1;
         double acc[3];
         local_self_quad<ORDER>(k, k == 0 ? n - 1 : k - 1, k + 1 == n ? 0 : k + 1, g, la, F, acc);
         const int c = tid & 3;
         if (kk < n && c < 3) vls[3 * (b0 + k) + c] = c == 0 ? acc[0] : (c == 1 ? acc[1] : acc[2]);
     }
-    const int nq = n * Q, q0 = b0 * Q, w = dx.w;
+    if (nodes) {
+        for (int k = tid; k < n; k += blockDim.x) {
+            direct_node(b0 + k, b0 + (k == 0 ? n - 1 : k - 1), F.x + 3 * k, dx);
+            dtau[b0 + k] = F.h[k];
+            ell[b0 + k] = F.ell[k];
+        }
+        for (int i = tid; i < 3 * n; i += blockDim.x) {
+            xd[3 * b0 + i] = F.x[i];
+            xn[3 * b0 + i] = F.xn[i];
+            D[3 * b0 + i] = F.D[i];
+            sdd[3 * b0 + i] = F.S[i];
+        }
+        if (tid == 0) gd[f] = g;
+    }
+    if (sub < 0) return;
+    const int nq = n * Q, q0 = b0 * Q, w = dx.w, t0 = sub * blockDim.x + tid, ts = nsub * blockDim.x;
     const float iw = 1.0f / (float)w;
     // several at a time: one wavefront per SIMD here, so independent chains
     // are what hides the latency of each
 #pragma unroll 4
-    for (int t = tid; t < nq * 3 * w; t += blockDim.x) {
+    for (int t = t0; t < nq * 3 * w; t += ts) {
         const int pa = (int)(((float)t + 0.5f) * iw);   // t / w: exact for t < 2^15
         dx.ker[(size_t)q0 * 3 * w + t] = direct_value(F.qp[pa], t - pa * w, dx);
     }
-    for (int t = tid; t < nq; t += blockDim.x)
+    for (int t = t0; t < nq; t += ts)
         direct_point(q0 + t, b0 + t / Q, F.qp + 3 * t, F.qc + 3 * t, dx);
-    for (int j = tid >> 6; j * kPiece < n; j += blockDim.x >> 6)
+    for (int j = t0 >> 6; j * kPiece < n; j += ts >> 6)
         direct_piece(dx.piece + dx.pfirst[f] + j, F.qp + 3 * j * kPiece * Q, q0 + j * kPiece * Q,
                      min(kPiece, n - j * kPiece) * Q, dx.L);
-    for (int k = tid; k < n; k += blockDim.x) {
-        direct_node(b0 + k, b0 + (k == 0 ? n - 1 : k - 1), F.x + 3 * k, dx);
-        dtau[b0 + k] = F.h[k];
-        ell[b0 + k] = F.ell[k];
-    }
-    for (int i = tid; i < 3 * n; i += blockDim.x) {
-        xd[3 * b0 + i] = F.x[i];
-        xn[3 * b0 + i] = F.xn[i];
-        D[3 * b0 + i] = F.D[i];
-        sdd[3 * b0 + i] = F.S[i];
-    }
-    for (int i = tid; i < 3 * nq; i += blockDim.x) {
+    for (int i = t0; i < 3 * nq; i += ts) {
         qpos[3 * q0 + i] = F.qp[i];
         qchg[3 * q0 + i] = F.qc[i];
     }
-    if (tid == 0) gd[f] = g;
 }
 
 // ------------------------------------------------------------------ launch
@@ -799,8 +810,14 @@ void launch_filaments(bs_plan_t p, const double *xyz, const double *kstage, doub
     const bool quintic = p->order == 6;
     if (p->direct && p->max_fil_nodes <= kDirectFil) {
         auto kern = quintic ? k_filament_direct<6> : k_filament_direct<4>;
-        hipLaunchKernelGGL(kern, grid, dim3(256), 0, p->stream, off, xs, xd, xn, shift, gamma, gd,
-                           dtau, D, sdd, qpos, qchg, ell, status, tmp, g, la, vls, direct_out(p));
+        // a workgroup per CU, up to four per filament (3: 10.3 us on one 64-node
+        // ring, 4: 10.1, 8: 10.0); a quintic system beyond the LDS has one copy,
+        // in global memory
+        const bool one = quintic && p->max_fil_nodes > kPcr5Lds;
+        const int parts = one ? 1 : (int)std::clamp<int64_t>(256 / p->nfil, 1, 4);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(p->nfil * parts)), dim3(256), 0, p->stream, off, xs,
+                           xd, xn, shift, gamma, gd, dtau, D, sdd, qpos, qchg, ell, status, tmp, g,
+                           la, vls, direct_out(p), parts);
         return;
     }
     const bool split = !p->direct && p->N >= kFilamentSplitNodes &&

@@ -40,6 +40,8 @@ CASES = [
     ("infinite", lambda: W.helices(48), 32, 8, 4, 2),
     ("most points", lambda: W.ellipses(64, 64, seed=7), 64, 8, 4, 2),
     ("nearly as many", lambda: W.ellipses(63, 65, seed=8), 64, 8, 4, 2),
+    ("two workgroups a filament", lambda: W.ellipses(100, 21, seed=10), 64, 8, 4, 2),
+    ("one workgroup a filament", lambda: W.ellipses(200, 13, seed=11), 64, 8, 6, 3),
     ("larger grid", lambda: W.ellipses(20, 50, seed=9), 128, 6, 6, 2),
 ]
 
