@@ -713,9 +713,8 @@ __device__ void ns_panel(const Seg &s, const double *x, double a, double b, cons
 }
 
 // Integral over u in [0,1] of (s(u) - x) x s'(u) / |s(u) - x|^3 for one
-// cubic segment: closest point by a coarse scan and Newton steps on
-// (s - x) . s' = 0, then Gauss-Legendre panels graded geometrically (ratio
-// 3) away from it.
+// segment: closest point by a coarse scan and Newton steps on (s - x) . s' = 0,
+// then Gauss-Legendre panels graded geometrically (ratio 3) away from it.
 template <int DEG = 5>
 __device__ __forceinline__ void seg_eval(const Seg &s, double u, double *p, double *d1) {
     for (int q = 0; q < 3; q++) {
@@ -757,36 +756,55 @@ __device__ double closest_u(const Seg &s, const double *xs) {
     return ub;
 }
 
+// half the distance C (closest point to target) in parameter units, d1 the
+// segment's derivative there: the centre panel [u - delta, u + delta] is finer
+// than the singularity's width
+__device__ __forceinline__ double ns_delta(const double *C, const double *d1) {
+    const double r2 = C[0] * C[0] + C[1] * C[1] + C[2] * C[2];
+    const double sp2 = d1[0] * d1[0] + d1[1] * d1[1] + d1[2] * d1[2];
+    const double delta = 0.5 * sqrt(r2 / sp2);
+    return delta < 1e-13 ? 1e-13 : delta;
+}
+// Panel k: 0 the centre panel, then those to its left up to 0, each ending at
+// three times the distance from ub at which it begins, then those to its right up
+// to 1 (clipped).  None when the distance is not a number.
+__device__ __forceinline__ int ns_panels(double ub, double delta) {
+    const double a0 = ub - delta < 0.0 ? 0.0 : ub - delta, b0 = ub + delta > 1.0 ? 1.0 : ub + delta;
+    int n = b0 > a0 ? 1 : 0;
+    for (double e = a0, w = delta; e > 0.0; w *= 3.0, n++) e = ub - 3.0 * w;
+    for (double e = b0, w = delta; e < 1.0; w *= 3.0, n++) e = ub + 3.0 * w;
+    return n;
+}
+__device__ __forceinline__ void ns_panel_bounds(double ub, double delta, int k, double *lo,
+                                                double *hi) {
+    *lo = fmax(ub - delta, 0.0);
+    *hi = fmin(ub + delta, 1.0);
+    double w = delta;
+    for (; k > 0 && *lo > 0.0; k--, w *= 3.0) {
+        *hi = *lo;
+        *lo = fmax(ub - 3.0 * w, 0.0);
+    }
+    if (k == 0) return;
+    *hi = fmin(ub + delta, 1.0);
+    for (w = delta; k > 0; k--, w *= 3.0) {
+        *lo = *hi;
+        *hi = fmin(ub + 3.0 * w, 1.0);
+    }
+}
+
 template <int DEG = 5>
 __device__ void ns_seg_integral(const Seg &s, const double *xs, const NsRule &R, double *acc) {
     const double ub = closest_u<DEG>(s, xs);
-    double P[3], d1[3];
-    seg_eval<DEG>(s, ub, P, d1);
-    const double r2 = (P[0] - xs[0]) * (P[0] - xs[0]) + (P[1] - xs[1]) * (P[1] - xs[1]) +
-                      (P[2] - xs[2]) * (P[2] - xs[2]);
-    const double sp2 = d1[0] * d1[0] + d1[1] * d1[1] + d1[2] * d1[2];
-    // half the distance in parameter units: the first panel pair is finer
-    // than the singularity's width
-    double delta = 0.5 * sqrt(r2 / sp2);
-    delta = delta < 1e-13 ? 1e-13 : delta;
+    double C[3], d1[3];
+    seg_eval<DEG>(s, ub, C, d1);
+    for (int q = 0; q < 3; q++) C[q] -= xs[q];
+    const double delta = ns_delta(C, d1);
+    const int n = ns_panels(ub, delta);
     acc[0] = acc[1] = acc[2] = 0.0;
-    double a0 = ub - delta < 0.0 ? 0.0 : ub - delta, b0 = ub + delta > 1.0 ? 1.0 : ub + delta;
-    if (b0 > a0) ns_panel<DEG>(s, xs, a0, b0, R, acc);
-    double edge = a0, width = delta;
-    while (edge > 0.0) {
-        double nxt = ub - 3.0 * width;
-        if (nxt < 0.0) nxt = 0.0;
-        ns_panel<DEG>(s, xs, nxt, edge, R, acc);
-        edge = nxt;
-        width *= 3.0;
-    }
-    edge = b0; width = delta;
-    while (edge < 1.0) {
-        double nxt = ub + 3.0 * width;
-        if (nxt > 1.0) nxt = 1.0;
-        ns_panel<DEG>(s, xs, edge, nxt, R, acc);
-        edge = nxt;
-        width *= 3.0;
+    for (int k = 0; k < n; k++) {
+        double lo, hi;
+        ns_panel_bounds(ub, delta, k, &lo, &hi);
+        ns_panel<DEG>(s, xs, lo, hi, R, acc);
     }
 }
 
@@ -811,27 +829,25 @@ __device__ __forceinline__ void unpack_shift(int sh, const double *x, double L, 
     for (int q = 0; q < 3; q++) xs[q] = x[q] + shv[q] * L;
 }
 
-// Exact segment integral minus its Q-point sum, for one (node, segment) pair
-// (DEG 3: cubic segments, S == NULL)
+// Exact segment integral minus its Q-point sum, for every pair (list ==
+// nullptr, count = total pairs) or the pairs listed (DEG 3: cubic segments, S ==
+// NULL).  A wavefront takes 64 pairs at a time, one per lane, for the closest
+// point and the panel count, and then their panels 64 at a time, one per lane,
+// whatever pair they belong to: the counts of a wavefront's pairs differ (2.5
+// on average over the capsule that flags a pair, 5.3 at the most among 64).
+// The segment, moved so that the target is the origin, waits in LDS; each
+// pair's panels are summed in their order by its lane.
+// Float64 arithmetic bounds it; with a pair per lane for the panels too it
+// took 1.22 ms for the 1.1e7 pairs of the 1e6-node tangle, now 0.93.
 template <int DEG>
-__device__ void ns_pair(int o, int sg, int sh, const int *off, const int *fil, const double *x,
-                        const double *xn, const double *D, const double *S, const double *dtau, const double *gamma,
-                        const double *qpos, const double *qchg, int Q, double L,
-                        const NsRule &R, double *out) {
-    double xs[3];
-    unpack_shift(sh, x + 3 * o, L, xs);
-    Seg s = load_seg(sg, off, fil, x, xn, D, S, dtau);
-    double acc[3], qs[3];
-    ns_seg_integral<DEG>(s, xs, R, acc);
-    ns_qsum(sg, xs, qpos, qchg, Q, qs);
-    const double g4 = gamma[fil[sg]] / (4.0 * kPi);
-    for (int q = 0; q < 3; q++) out[q] = g4 * acc[q] - qs[q] / (4.0 * kPi);
-}
+struct NsIntLds {
+    double c[(DEG + 1) * 3][64], ub[64], dl[64];
+    double part[3][64];
+    unsigned char own[64];
+};
 
-// every pair (list == nullptr, count = total pairs), or the pairs listed.
-// Held to 128 VGPRs (four wavefronts per SIMD instead of three at 158, no
-// spills: 1.32 -> 1.27 ms for the 1.1e7 pairs of the 1e6-node tangle)
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_ns_integrate(
+template <int DEG>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DEG == 3 ? 4 : 3))) void k_ns_integrate(
     const int *__restrict__ count, const int *__restrict__ list, const int *__restrict__ pnode,
     const int2 *__restrict__ pairs, const int *__restrict__ off, const int *__restrict__ fil,
     const double *__restrict__ x, const double *__restrict__ xn, const double *__restrict__ D,
@@ -839,21 +855,67 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const double *__restrict__ gamma, const double *__restrict__ qpos,
     const double *__restrict__ qchg, int Q, double L, NsRule R, double *__restrict__ pout,
     const int *__restrict__ skip) {
+    __shared__ NsIntLds<DEG> W;
     if (skip && *skip) return;
-    const int P = *count;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < P; i += gridDim.x * blockDim.x) {
-        const int p = list ? list[i] : i;
-        int2 pr = pairs[p];
-        double out[3];
-        if (S)
-            ns_pair<5>(pnode[p], pr.x, pr.y, off, fil, x, xn, D, S, dtau, gamma, qpos, qchg, Q, L,
-                       R, out);
-        else
-            ns_pair<3>(pnode[p], pr.x, pr.y, off, fil, x, xn, D, S, dtau, gamma, qpos, qchg, Q, L,
-                       R, out);
-        pout[3 * (size_t)p] = out[0];
-        pout[3 * (size_t)p + 1] = out[1];
-        pout[3 * (size_t)p + 2] = out[2];
+    const int P = *count, lane = threadIdx.x;
+    constexpr double zero[3] = {0.0, 0.0, 0.0};
+    auto coef = [](Seg &s, int k, int q) -> double & {
+        return k == 0 ? s.c0[q] : k == 1 ? s.c1[q] : k == 2 ? s.c2[q] : k == 3 ? s.c3[q] : k == 4 ? s.c4[q] : s.c5[q];
+    };
+    for (int64_t i0 = (int64_t)blockIdx.x * 64; i0 < P; i0 += (int64_t)gridDim.x * 64) {
+        const bool act = i0 + lane < P;
+        int p = 0, np = 0;
+        double qs[3] = {0.0, 0.0, 0.0}, acc[3] = {0.0, 0.0, 0.0}, g4 = 0.0;
+        if (act) {
+            p = list ? list[i0 + lane] : (int)(i0 + lane);
+            const int2 pr = pairs[p];
+            double xs[3];
+            unpack_shift(pr.y, x + 3 * pnode[p], L, xs);
+            Seg s = load_seg(pr.x, off, fil, x, xn, D, S, dtau);
+            ns_qsum(pr.x, xs, qpos, qchg, Q, qs);
+            g4 = gamma[fil[pr.x]] / (4.0 * kPi);
+            for (int q = 0; q < 3; q++) s.c0[q] -= xs[q];
+            const double ub = closest_u<DEG>(s, zero);
+            double C[3], d1[3];
+            seg_eval<DEG>(s, ub, C, d1);
+            const double dl = ns_delta(C, d1);
+            np = ns_panels(ub, dl);
+#pragma unroll
+            for (int k = 0; k <= DEG; k++)
+#pragma unroll
+                for (int q = 0; q < 3; q++) W.c[3 * k + q][lane] = coef(s, k, q);
+            W.ub[lane] = ub;
+            W.dl[lane] = dl;
+        }
+        const int incl = wave_incl_sum(np), first = incl - np;
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        for (int r0 = 0; r0 < total; r0 += 64) {
+            const int a = max(first, r0), b = min(incl, r0 + 64);   // own panels of the round
+            for (int k = a; k < b; k++) W.own[k - r0] = (unsigned char)lane;
+            wave_lds_sync();
+            // (lanes beyond the last panel repeat it)
+            const int t = min(r0 + lane, total - 1);
+            const int e = W.own[t - r0], k = t - __shfl(first, e);
+            Seg s;
+#pragma unroll
+            for (int m = 0; m <= DEG; m++)
+#pragma unroll
+                for (int q = 0; q < 3; q++) coef(s, m, q) = W.c[3 * m + q][e];
+            if constexpr (DEG == 3)
+                for (int q = 0; q < 3; q++) s.c4[q] = s.c5[q] = 0.0;
+            seg_derivs(s);
+            double lo, hi, v[3] = {0.0, 0.0, 0.0};
+            ns_panel_bounds(W.ub[e], W.dl[e], k, &lo, &hi);
+            ns_panel<DEG>(s, zero, lo, hi, R, v);
+            for (int q = 0; q < 3; q++) W.part[q][lane] = v[q];
+            wave_lds_sync();
+            for (int m = a; m < b; m++)
+                for (int q = 0; q < 3; q++) acc[q] += W.part[q][m - r0];
+            wave_lds_sync();
+        }
+        if (act)
+            for (int q = 0; q < 3; q++)
+                pout[3 * (size_t)p + q] = g4 * acc[q] - qs[q] / (4.0 * kPi);
     }
 }
 
@@ -1492,22 +1554,23 @@ void ns_rule(NsRule *R);
 
 // the graded-panel integrator on every pair (list == nullptr) or on the
 // listed ones; nothing when *skip is set.  The pair count is known on the
-// device only: the grid strides over it with many more workgroups than fit
-// at once (1024 resident at four wavefronts per SIMD), so that the last
-// round does not leave most CUs idle (1024 workgroups: 1.48 ms for the
-// 1.1e7 pairs of the 1e6-node tangle at three wavefronts per SIMD; 12288:
-// 1.36 ms)
-constexpr int kNsIntegrateBlocks = 12288;
+// device only: the grid strides over it with many more workgroups (of one
+// wavefront) than fit at once, so that the last round does not leave most CUs
+// idle: enough for 16 pairs per node, up to 49152
+constexpr int kNsIntegrateBlocks = 49152;
 
 static void adaptive_pairs(bs_plan_t p, const int *count, const int *list,
                            const int *skip = nullptr) {
     NsRule R;
     ns_rule(&R);
-    hipLaunchKernelGGL(k_ns_integrate, dim3(kNsIntegrateBlocks), dim3(256), 0, p->stream,
+    const bool quintic = p->order == 6;
+    auto kern = quintic ? k_ns_integrate<5> : k_ns_integrate<3>;
+    const int nblk = (int)std::clamp<int64_t>(p->N / 4, 64, kNsIntegrateBlocks);
+    hipLaunchKernelGGL(kern, dim3(nblk), dim3(64), 0, p->stream,
                        count, list, (const int *)p->ns_pnode.p, (const int2 *)p->ns_pairs.p,
                        (const int *)p->d_off.p, (const int *)p->d_fil.p,
                        (const double *)p->d_x.p, (const double *)p->d_xn.p,
-                       (const double *)p->d_D.p, p->order == 6 ? (const double *)p->d_sdd.p : nullptr,
+                       (const double *)p->d_D.p, quintic ? (const double *)p->d_sdd.p : nullptr,
                        (const double *)p->d_dtau.p, (const double *)p->d_gamma.p,
                        (const double *)p->d_qpos.p, (const double *)p->d_qchg.p, p->Q,
                        p->prm.L, R, (double *)p->ns_pout.p, skip);

@@ -99,3 +99,31 @@ def test_search_flags_the_pairs_of_a_full_count(B, name):
         dv = plan.velocity_terms()["ns"].cpu().numpy()
         ref, cnt = O.Oracle(fs).ns_correction(eta=eta)
         assert int(cnt.sum()) == want and rel_l2(dv, ref) < 1e-10
+
+
+def close_rings(gap, n):
+    """Two coaxial rings of n nodes a gap apart, the second turned by a third
+    of a segment (targets over the inside of segments), and a third ring far
+    from both."""
+    t = 2 * np.pi * np.arange(n) / n
+    fs = W.ellipses(nfil=3, n_per=n, seed=9)
+    ring = lambda z, s: np.stack([1.0 + 0.5 * np.cos(t + s), 2.0 + 0.5 * np.sin(t + s), z + 0 * t], 1)
+    fs.xyz = np.concatenate([ring(3.0, 0.0), ring(3.0 + gap, 2 * np.pi / (3 * n)), ring(5.5, 0.1)])
+    fs.grid_n, fs.tol, fs.name = 64, 1e-6, f"rings of {n}, gap {gap}"
+    return fs
+
+
+@pytest.mark.parametrize("order", [4, 6])
+@pytest.mark.parametrize("gap,n", [(0.2, 6), (1e-2, 7), (1e-5, 11)])
+def test_integrals_with_few_and_many_panels(B, order, gap, n):
+    """From 2 panels a pair to over 20, pair counts that leave lanes idle: the
+    correction is the oracle's, to the 1e-10 of the panels' quadrature, or to
+    the float64 rounding of the distance in a pair's 1 / distance."""
+    fs = close_rings(gap, n)
+    plan = make_plan(B, fs, ns_mode=B.BS_NS_ADAPTIVE, spline_order=order)
+    dv = plan.velocity_terms()["ns"].cpu().numpy()
+    ref, cnt = O.Oracle(fs, order=order).ns_correction(eta=1.0)
+    assert plan.ns_counts()[0] == int(cnt.sum()) > 0
+    err = rel_l2(dv, ref)
+    print(f"  order {order} gap {gap}: {cnt.sum()} pairs, rel_l2 {err:.2e}")
+    assert err < max(1e-10, 1e-14 / gap)
