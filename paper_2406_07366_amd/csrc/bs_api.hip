@@ -473,6 +473,7 @@ static int set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, cons
     const size_t rs = P->real_size;
     if (!same) {
         P->have_filaments = false;
+        drop_graph(P);   // it holds the buffers that may move here, and their sizes
         if ((rc = ensure<int>(P, P->d_off, nfil + 1)) || (rc = ensure<int>(P, P->d_fil, N)) ||
             (rc = ensure<double>(P, P->d_gamma, nfil)) || (rc = ensure<double>(P, P->d_x, 3 * N)) ||
             (rc = ensure<double>(P, P->d_xn, 3 * N)) ||
@@ -851,7 +852,10 @@ int bs_rk4_step(bs_plan_t P, int64_t nfil, const int64_t *offsets, double *xyz,
 
 // ---------------------------------------------------------- graph replay
 static void drop_graph(bs_plan_t P) {
-    if (P->gexec) (void)hipGraphExecDestroy(P->gexec);
+    if (P->gexec) {
+        (void)hipStreamSynchronize(P->stream);   // a replay may still run
+        (void)hipGraphExecDestroy(P->gexec);
+    }
     if (P->graph) (void)hipGraphDestroy(P->graph);
     P->gexec = nullptr;
     P->graph = nullptr;
@@ -870,10 +874,14 @@ int bs_step(bs_plan_t P, int64_t nfil, const int64_t *offsets, const double *xyz
             const double *gamma, double *v_out) {
     if (!P) return set_error(nullptr, BS_EINVAL, "null plan");
     const bool same = P->gexec && P->have_filaments && P->g_xyz == xyz && P->g_gamma == gamma &&
-                      P->g_v == v_out && P->nfil == nfil && offsets &&
+                      P->g_v == v_out && P->g_fp32 == mlp_fp32(P->mlp) && P->nfil == nfil && offsets &&
                       std::equal(offsets, offsets + nfil + 1, P->off_host.begin());
-    if (P->use_graph && !P->prof && same)
-        return check_hip(P, hipGraphLaunch(P->gexec, P->stream), "hipGraphLaunch");
+    if (P->use_graph && !P->prof && same) {
+        // a pair search of an earlier bs_set_filaments may still read, on the
+        // side stream, what the replay rewrites
+        int rc = join_side(P);
+        return rc ? rc : check_hip(P, hipGraphLaunch(P->gexec, P->stream), "hipGraphLaunch");
+    }
     // eager step (also sizes every buffer and uploads the filament structure)
     int rc = bs_set_filaments(P, nfil, offsets, xyz, gamma);
     if (!rc) rc = bs_velocity(P, v_out);
@@ -900,6 +908,7 @@ int bs_step(bs_plan_t P, int64_t nfil, const int64_t *offsets, const double *xyz
     }
     P->graph = g;
     P->g_xyz = xyz; P->g_gamma = gamma; P->g_v = v_out;
+    P->g_fp32 = mlp_fp32(P->mlp);
     return BS_OK;
 }
 

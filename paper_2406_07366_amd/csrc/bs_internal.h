@@ -152,6 +152,7 @@ struct bs_plan_s {
     hipGraphExec_t gexec = nullptr;
     const double *g_xyz = nullptr, *g_gamma = nullptr;
     double *g_v = nullptr;
+    int g_fp32 = 0;                            // the network's precision when recorded
     // terms (for velocity terms / energy)
     bs::DBuf tmp3;                             // f64 [N][3]
     double *h_energy = nullptr;                // pinned host memory, written by the device
@@ -255,6 +256,7 @@ void launch_ns_mlp(bs_plan_t p, double *v, const double *base);
 void mlp_forward_device(bs_mlp_t m, const int *Bdev, int64_t Bmax, const float *X, float *Y,
                         hipStream_t stream);
 hipStream_t mlp_stream(bs_mlp_t m);
+int mlp_fp32(bs_mlp_t m);   // its debug mode (0 for no network)
 
 // pairs.hip (with the short-range sums): the energy line integral
 // (into *e, host memory mapped on the device; partial: 512 doubles)

@@ -643,6 +643,7 @@ struct bs_mlp_s {
 
 namespace bs {
 hipStream_t mlp_stream(bs_mlp_t M) { return M->stream; }
+int mlp_fp32(bs_mlp_t M) { return M ? M->fp32 : 0; }
 
 void mlp_forward_device(bs_mlp_t M, const int *Bdev, int64_t Bmax, const float *X, float *Y,
                         hipStream_t stream) {
