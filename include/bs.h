@@ -153,6 +153,12 @@ typedef struct {
  * rcut would exceed L/2), BS_EKB. */
 int bs_resolve_params(const bs_params *p, bs_params *out);
 
+/* Pure host call: the transforms that a plan of these parameters runs,
+ * BS_FFT_LIBRARY or BS_FFT_PRUNED (the resolved fft_mode does not tell them
+ * apart where BS_FFT_AUTO keeps its own transforms, see there), or the error
+ * of bs_resolve_params. */
+int bs_params_transforms(const bs_params *p);
+
 /* Create a plan on the current HIP device for one box period L, core a and
  * Delta (Sec. 2.3, eq:BS_local), Ewald parameters alpha, r_c (Sec. 3,
  * eq:ewald_velocity_splitting; Sec. 4 for beta) and NUFFT parameters sigma,

@@ -25,7 +25,7 @@ BS_FFT_AUTO, BS_FFT_LIBRARY, BS_FFT_PRUNED = 0, 1, 2
 _CODES = {0: "BS_OK", -1: "BS_EINVAL", -2: "BS_EMINIMG", -3: "BS_ETOL", -4: "BS_EKB",
           -5: "BS_ENOMEM", -6: "BS_EDEVICE", -7: "BS_ESTATE"}
 
-EXPORTED = ["bs_resolve_params", "bs_plan", "bs_set_filaments", "bs_set_periods", "bs_velocity",
+EXPORTED = ["bs_resolve_params", "bs_params_transforms", "bs_plan", "bs_set_filaments", "bs_set_periods", "bs_velocity",
             "bs_velocity_terms", "bs_energy", "bs_vorticity_modes", "bs_geometry",
             "bs_status", "bs_set_profiling", "bs_stage_times", "bs_get_params",
             "bs_destroy", "bs_last_error", "bs_mlp_nparams", "bs_mlp_create",
@@ -75,6 +75,7 @@ import torch  # noqa: E402,F401
 _lib = C.CDLL(LIB_PATH)
 _vp = C.c_void_p
 _lib.bs_resolve_params.argtypes = [C.POINTER(BsParams), C.POINTER(BsParams)]
+_lib.bs_params_transforms.argtypes = [C.POINTER(BsParams)]
 _lib.bs_plan.argtypes = [C.POINTER(BsParams), _vp, C.POINTER(_vp)]
 _lib.bs_set_filaments.argtypes = [_vp, C.c_int64, C.POINTER(C.c_int64), _vp, _vp]
 _lib.bs_set_periods.argtypes = [_vp, C.c_int64, _vp]
@@ -140,6 +141,15 @@ def resolve_params(p: BsParams) -> BsParams:
     out = BsParams()
     _check(_lib.bs_resolve_params(C.byref(p), C.byref(out)))
     return out
+
+
+def params_transforms(p: BsParams) -> int:
+    """BS_FFT_LIBRARY or BS_FFT_PRUNED: what a plan of these parameters runs
+    (host only)."""
+    rc = _lib.bs_params_transforms(C.byref(p))
+    if rc < 0:
+        _check(rc)
+    return rc
 
 
 def params_for(fs, precision=BS_FP64, **kw) -> BsParams:

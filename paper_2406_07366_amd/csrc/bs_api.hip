@@ -249,6 +249,20 @@ int resolve(const bs_params *in, bs_params *out) {
     return BS_OK;
 }
 
+// Whether a plan of parameters in (resolved: r) runs its own transforms.
+// BS_FFT_AUTO resolves to BS_FFT_LIBRARY on grids that are no power of two
+// (BS_FFT_PRUNED refuses them) and below 64; in float64 the plan still runs
+// its own transforms there where it has them: hipFFT's form all modes
+// and need a pass of the spectral operator (384^3: 5.69 ms against 1.91;
+// 160^3: 280 us, 162; 32^3: 20.5, 15).  In
+// float32 their rounding would change results, so those stay on hipFFT, as
+// does an explicit BS_FFT_LIBRARY, and 1024^3 in float64, which
+// BS_FFT_PRUNED refuses (its arrays would add 29 GB).
+static bool runs_pruned(const bs_params &in, const bs_params &r) {
+    return r.fft_mode == BS_FFT_PRUNED ||
+           (in.fft_mode == BS_FFT_AUTO && r.precision == BS_FP64 && pruned_auto64(r.grid_n));
+}
+
 void stage_collect(bs_plan_t p) {
     if (!p->prof) return;
     (void)hipStreamSynchronize(p->stream);
@@ -293,6 +307,13 @@ int bs_stage_times(bs_plan_t P, double *ms, int64_t *counts, int reset) {
 }
 
 int bs_resolve_params(const bs_params *p, bs_params *out) { return resolve(p, out); }
+
+int bs_params_transforms(const bs_params *p) {
+    bs_params r;
+    const int rc = resolve(p, &r);
+    if (rc) return rc;
+    return runs_pruned(*p, r) ? BS_FFT_PRUNED : BS_FFT_LIBRARY;
+}
 
 const char *bs_last_error(bs_plan_t plan) { return plan ? plan->err.c_str() : g_err.c_str(); }
 
@@ -366,15 +387,7 @@ int bs_plan(const bs_params *p, void *hip_stream, bs_plan_t *out) {
         hipfftSetStream(P->fft_inv, P->stream) != HIPFFT_SUCCESS)
         return fail(set_error(P, BS_EDEVICE, "hipfftSetStream failed"));
     // pruned transforms: twiddles exp(-+2 pi i k / n), k < n/2, from float64
-    // BS_FFT_AUTO resolves to BS_FFT_LIBRARY on grids that are no power of two
-    // (BS_FFT_PRUNED refuses them) and below 64; in float64 the plan still runs
-    // its own transforms there where it has them: hipFFT's form all modes
-    // and need a pass of the spectral operator (384^3: 5.69 ms against 1.91;
-    // 160^3: 280 us, 162; 32^3: 20.5, 15).  In
-    // float32 their rounding would change results, so those stay on hipFFT, as
-    // does an explicit BS_FFT_LIBRARY.
-    P->pruned = r.fft_mode == BS_FFT_PRUNED ||
-                (p->fft_mode == BS_FFT_AUTO && !P->fp32 && pruned_ops(P->n, false));
+    P->pruned = runs_pruned(*p, r);
     if (P->pruned) {
         P->fft_ops = pruned_ops(P->n, P->fp32);
         const size_t cs = 2 * P->real_size, K1 = r.K + 1, NY = 2 * r.K + 1;

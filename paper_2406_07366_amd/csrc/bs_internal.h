@@ -222,6 +222,9 @@ int fft_inverse(bs_plan_t p);
 // need no array between the x and y transforms
 constexpr int kFftXYMax = 64;
 bool pruned_fft_ok(int n, size_t csize);
+// grids on which BS_FFT_AUTO runs the own transforms in float64 although it
+// resolves to BS_FFT_LIBRARY
+bool pruned_auto64(int n);
 // the passes for a grid of n points per axis, NULL if there are none
 const FftOps *pruned_ops(int n, bool fp32);
 const FftOps *mixed_ops_a(int n);

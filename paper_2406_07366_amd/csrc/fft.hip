@@ -12,6 +12,16 @@ bool pruned_fft_ok(int n, size_t csize) {
            3 * fft_max_nj(n) <= kFftMaxThreads;
 }
 
+// 16, 32 and the sizes of fft_mixed_*.hip: multiples of 8 from 40 to 504 that are
+// not powers of two and have no prime factor above 7
+bool pruned_auto64(int n) {
+    if (n == 16 || n == 32) return true;
+    if (n < 40 || n > 504 || n % 8 != 0 || (n & (n - 1)) == 0) return false;
+    for (int f : {2, 3, 5, 7})
+        while (n % f == 0) n /= f;
+    return n == 1;
+}
+
 template <typename R>
 static const FftOps *ops_pow2(int n) {
     switch (n) {
@@ -21,7 +31,9 @@ static const FftOps *ops_pow2(int n) {
         case 128: return fft_ops_for<R, 128>();
         case 256: return fft_ops_for<R, 256>();
         case 512: return fft_ops_for<R, 512>();
-        case 1024: return fft_ops_for<R, 1024>();
+        case 1024:   // float64: refused by pruned_fft_ok
+            if constexpr (sizeof(R) == 4) return fft_ops_for<R, 1024>();
+            return nullptr;
         default: return nullptr;
     }
 }
