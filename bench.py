@@ -80,20 +80,16 @@ def count_pairs(plan, fs, Q, rc):
     return int(cnt.sum()) - 2 * Q * fs.n_nodes
 
 
-def pruned_transforms(prm):
-    """Whether the resolved plan uses the pruned transforms."""
-    return prm.fft_mode == 2
-
-
-def stage_bytes(prm, N, Nq, fp32):
-    """Algorithmic HBM bytes per launch of each stage (minimum traffic)."""
+def stage_bytes(prm, N, Nq, fp32, pruned):
+    """Algorithmic HBM bytes per launch of each stage (minimum traffic);
+    pruned: whether the plan runs its own transforms."""
     s = 4 if fp32 else 8
     n = prm.grid_n
     n3 = n ** 3
     w = prm.w
     out = {"spread": 3 * n3 * s + Nq * (16 + (3 * w + 4) * s),
            "interp": 3 * n3 * s + N * (24 + 48)}
-    if pruned_transforms(prm):
+    if pruned:
         K1, NY = prm.K + 1, 2 * prm.K + 1
         a = 3 * n * n * K1 * 2 * s          # x-transformed grid, modes 0..K
         b = 3 * NY * n * K1 * 2 * s         # after y, |my| <= K
@@ -186,7 +182,7 @@ def table1(args, torch, B, W):
             paper_us = C_fit * N * math.log10(N)
             line = {"table1": {"tol": tol, "beta": beta, "N": N, "grid_n": prm.grid_n,
                                "K": prm.K, "alpha": prm.alpha, "rcut": prm.rcut,
-                               "fft_mode": prm.fft_mode, "ms_per_eval": ms,
+                               "fft_mode": plan.transforms(), "ms_per_eval": ms,
                                "nodes_per_s": N / (ms * 1e-3), "rel_l2_vs_1e-14": err,
                                "paper_cpu_core_ms": paper_us * 1e-3}}
             print(json.dumps(line), flush=True)
@@ -360,7 +356,8 @@ def main():
     fs.tol = primary["tol"]   # the legs loop left the last leg's tolerance
     rp = B.resolve_params(B.params_for(fs, precision=primary["precision"]))
     Nq = N * prm["Q"]
-    sb = stage_bytes(rp, N, Nq, fp32)
+    pruned = primary["plan"].transforms() == B.BS_FFT_PRUNED
+    sb = stage_bytes(rp, N, Nq, fp32, pruned)
     st = primary["stages"]
     roof_all = {}
     for k, b in sb.items():
@@ -380,7 +377,7 @@ def main():
     def roof_entry(k):
         d = roof_all[k]
         srcname = SINGLE_KERNEL_STAGES[k]
-        if k == "spectral" and pruned_transforms(rp):
+        if k == "spectral" and pruned:
             srcname = "fft.hip"         # the spectral operator runs inside the z transform
         src = os.path.join(ROOT, "paper_2406_07366_amd", "csrc", srcname)
         traffic = read_traffic(os.path.join(

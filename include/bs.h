@@ -404,8 +404,15 @@ int bs_set_mlp(bs_plan_t plan, bs_mlp_t mlp, const float *err_table, int nbins);
  * the rest). */
 int bs_ns_counts(bs_plan_t plan, int64_t *npairs, int64_t *nfallback);
 
-/* Parameters actually used (all derived fields filled). */
+/* Parameters actually used (all derived fields filled).  A plan made again
+ * from them has fft_mode's resolved value as an explicit choice: where
+ * BS_FFT_AUTO keeps its own transforms (see there) set it back to BS_FFT_AUTO
+ * for the same transforms. */
 int bs_get_params(bs_plan_t plan, bs_params *resolved);
+
+/* The transforms this plan runs, BS_FFT_LIBRARY or BS_FFT_PRUNED (a negative
+ * code for a null plan); bs_vorticity_modes always takes hipFFT's. */
+int bs_plan_transforms(bs_plan_t plan);
 
 /* Release every device buffer and FFT plan; synchronises first. */
 int bs_destroy(bs_plan_t plan);

@@ -28,7 +28,7 @@ _CODES = {0: "BS_OK", -1: "BS_EINVAL", -2: "BS_EMINIMG", -3: "BS_ETOL", -4: "BS_
 EXPORTED = ["bs_resolve_params", "bs_params_transforms", "bs_plan", "bs_set_filaments", "bs_set_periods", "bs_velocity",
             "bs_velocity_terms", "bs_energy", "bs_vorticity_modes", "bs_geometry",
             "bs_status", "bs_set_profiling", "bs_stage_times", "bs_get_params",
-            "bs_destroy", "bs_last_error", "bs_mlp_nparams", "bs_mlp_create",
+            "bs_plan_transforms", "bs_destroy", "bs_last_error", "bs_mlp_nparams", "bs_mlp_create",
             "bs_mlp_forward", "bs_mlp_loss_grad", "bs_mlp_adam_step", "bs_mlp_get_params",
             "bs_mlp_set_fp32",
             "bs_mlp_destroy", "bs_ns_samples", "bs_ns_error_bins", "bs_ns_error_table",
@@ -86,6 +86,7 @@ _lib.bs_vorticity_modes.argtypes = [_vp, _vp]
 _lib.bs_geometry.argtypes = [_vp] + [_vp] * 5
 _lib.bs_status.argtypes = [_vp]
 _lib.bs_get_params.argtypes = [_vp, C.POINTER(BsParams)]
+_lib.bs_plan_transforms.argtypes = [_vp]
 _lib.bs_set_profiling.argtypes = [_vp, C.c_int]
 _lib.bs_stage_times.argtypes = [_vp, _vp, _vp, C.c_int]
 _lib.bs_destroy.argtypes = [_vp]
@@ -192,6 +193,10 @@ class Plan:
         out = BsParams()
         _check(_lib.bs_get_params(self._h, C.byref(out)), self._h)
         return out
+
+    def transforms(self) -> int:
+        """BS_FFT_LIBRARY or BS_FFT_PRUNED: the transforms this plan runs."""
+        return _lib.bs_plan_transforms(self._h)
 
     def set_filaments(self, offsets, xyz, gamma):
         torch = self._torch

@@ -972,6 +972,11 @@ int bs_get_params(bs_plan_t P, bs_params *resolved) {
     return BS_OK;
 }
 
+int bs_plan_transforms(bs_plan_t P) {
+    if (!P) return set_error(nullptr, BS_EINVAL, "null plan");
+    return P->pruned ? BS_FFT_PRUNED : BS_FFT_LIBRARY;
+}
+
 int bs_destroy(bs_plan_t P) {
     if (!P) return BS_OK;
     (void)hipStreamSynchronize(P->stream);
