@@ -167,8 +167,11 @@ int bs_params_transforms(const bs_params *p);
  *   hip_stream  a hipStream_t (NULL = the null stream); every later call
  *               enqueues on it;
  *   out         receives the handle (NULL on error).
- * Allocates the grids (3 [n]^3 reals and their spectra) and builds the FFT
- * plans; the plan owns them until bs_destroy.  Errors as
+ * Allocates the grids (3 [n]^3 reals and their spectra), builds the FFT
+ * plans and allocates one work area for them (the plan's own transforms use the
+ * spectra's memory and the work area, which they make larger only if hipFFT asks
+ * for less than 3 (2K+1) n (K+1) complex values); the plan owns them until
+ * bs_destroy.  Errors as
  * bs_resolve_params, plus BS_ENOMEM, BS_EDEVICE. */
 int bs_plan(const bs_params *p, void *hip_stream, bs_plan_t *out);
 

@@ -373,29 +373,35 @@ int bs_plan(const bs_params *p, void *hip_stream, bs_plan_t *out) {
     P->kb.inv_den = 1.0 / (-expm1(-2.0 * r.zeta));
     P->kb.edge = 2.0 * r.zeta * exp(-r.zeta) * P->kb.inv_den;
     // FFT plans: 3 transforms of n^3 (real) <-> n^2 (n/2+1) (complex)
+    // (one work area for both, which the pruned transforms use too)
     int dims[3] = {P->n, P->n, P->n};
-    size_t ws = 0;
-    if (hipfftCreate(&P->fft_fwd) != HIPFFT_SUCCESS || hipfftCreate(&P->fft_inv) != HIPFFT_SUCCESS)
+    size_t wsf = 0, wsi = 0;
+    if (hipfftCreate(&P->fft_fwd) != HIPFFT_SUCCESS || hipfftCreate(&P->fft_inv) != HIPFFT_SUCCESS ||
+        hipfftSetAutoAllocation(P->fft_fwd, 0) != HIPFFT_SUCCESS ||
+        hipfftSetAutoAllocation(P->fft_inv, 0) != HIPFFT_SUCCESS)
         return fail(set_error(P, BS_EDEVICE, "hipfftCreate failed"));
     hipfftType tf = P->fp32 ? HIPFFT_R2C : HIPFFT_D2Z, ti = P->fp32 ? HIPFFT_C2R : HIPFFT_Z2D;
     if (hipfftMakePlanMany(P->fft_fwd, 3, dims, nullptr, 1, (int)n3, nullptr, 1, (int)nc, tf, 3,
-                           &ws) != HIPFFT_SUCCESS ||
+                           &wsf) != HIPFFT_SUCCESS ||
         hipfftMakePlanMany(P->fft_inv, 3, dims, nullptr, 1, (int)nc, nullptr, 1, (int)n3, ti, 3,
-                           &ws) != HIPFFT_SUCCESS)
+                           &wsi) != HIPFFT_SUCCESS)
         return fail(set_error(P, BS_EDEVICE, "hipfftMakePlanMany failed"));
     if (hipfftSetStream(P->fft_fwd, P->stream) != HIPFFT_SUCCESS ||
         hipfftSetStream(P->fft_inv, P->stream) != HIPFFT_SUCCESS)
         return fail(set_error(P, BS_EDEVICE, "hipfftSetStream failed"));
-    // pruned transforms: twiddles exp(-+2 pi i k / n), k < n/2, from float64
     P->pruned = runs_pruned(*p, r);
+    const size_t cs = 2 * P->real_size, K1 = r.K + 1, NY = 2 * r.K + 1;
+    const size_t wsB = P->pruned ? 3 * NY * n * K1 * cs : 0;
+    if ((rc = ensure<char>(P, P->fftwork, std::max({wsf, wsi, wsB})))) return fail(rc);
+    if ((wsf && hipfftSetWorkArea(P->fft_fwd, P->fftwork.p) != HIPFFT_SUCCESS) ||
+        (wsi && hipfftSetWorkArea(P->fft_inv, P->fftwork.p) != HIPFFT_SUCCESS))
+        return fail(set_error(P, BS_EDEVICE, "hipfftSetWorkArea failed"));
+    // pruned transforms: twiddles exp(-+2 pi i k / n), k < n, from float64
     if (P->pruned) {
         P->fft_ops = pruned_ops(P->n, P->fp32);
-        const size_t cs = 2 * P->real_size, K1 = r.K + 1, NY = 2 * r.K + 1;
         pruned_batches(P->n, cs, &P->fft_rb, &P->fft_kb, &P->fft_kz);
-        if ((rc = ensure<char>(P, P->fft_tw, 2 * n * cs)) ||
-            (P->n > kFftXYMax && (rc = ensure<char>(P, P->fft_A, 3 * n * n * K1 * cs))) ||
-            (rc = ensure<char>(P, P->fft_B, 3 * NY * n * K1 * cs)))
-            return fail(rc);
+        // (A, 3 n^2 (K + 1) values, K + 1 <= n / 2, fits the spectrum's 3 n^2 (n / 2 + 1))
+        if ((rc = ensure<char>(P, P->fft_tw, 2 * n * cs))) return fail(rc);
         // [n] exp(-2 pi i k / n), then [n] exp(+2 pi i k / n)
         std::vector<double> tw(4 * n);
         for (size_t k = 0; k < n; k++) {
@@ -995,7 +1001,7 @@ int bs_destroy(bs_plan_t P) {
     }
     if (P->fft_fwd) hipfftDestroy(P->fft_fwd);
     if (P->fft_inv) hipfftDestroy(P->fft_inv);
-    DBuf *all[] = {&P->grid, &P->spec, &P->deconv, &P->fftwork, &P->fft_tw, &P->fft_A, &P->fft_B, &P->d_off, &P->d_fil,
+    DBuf *all[] = {&P->grid, &P->spec, &P->deconv, &P->fftwork, &P->fft_tw, &P->d_off, &P->d_fil,
                    &P->d_gamma, &P->d_x, &P->d_xn, &P->d_shift, &P->d_dtau, &P->d_D, &P->d_sdd, &P->d_ell,
                    &P->d_qpos, &P->d_qchg, &P->d_status, &P->sp_key, &P->sp_cnt, &P->sp_start,
                    &P->sp_fill, &P->sp_perm, &P->sp_base, &P->sp_ker, &P->sp_q, &P->pq_key,

@@ -75,13 +75,15 @@ struct bs_plan_s {
     bs::DBuf grid;          // [3][n][n][n] real
     bs::DBuf spec;          // [3][n][n][n/2+1] complex
     bs::DBuf deconv;        // [K+1] float64: 1 / F(m)^2 per axis
+    // pruned transforms: twiddles [n forward][n inverse]; their arrays A
+    // [3][n][n][K+1] (in spec) and B [3][2K+1][n][K+1] complex (in fftwork) share
+    // the memory of hipFFT's spectrum and work area, which only the calls that
+    // run hipFFT use, within the call; z-pass batch
     bs::DBuf fftwork;
-    // pruned transforms: twiddles [n forward][n
-    // inverse], A [3][n][n][K+1] and B [3][2K+1][n][K+1] complex; batch sizes
     bool pruned = false;
     const bs::FftOps *fft_ops = nullptr;
     int fft_rb = 1, fft_kb = 1, fft_kz = 1;
-    bs::DBuf fft_tw, fft_A, fft_B;
+    bs::DBuf fft_tw;
 
     // short-range cell lists: nodes (and float32 points) in nc^3 cells, points
     // in ncx x ncy x ncy (x fastest; set with the filaments, see pair_cells)

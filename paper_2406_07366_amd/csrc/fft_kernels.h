@@ -859,7 +859,7 @@ static void pruned_fwd(bs_plan_t p) {
         if (lds > 65536) allow_big_lds<k_fft_xy_fwd<R, N>>(p->device);
         const int per = ceil_div(3 * n, 8);
         hipLaunchKernelGGL((k_fft_xy_fwd<R, N>), dim3(8 * per), dim3(n * mnj), lds, p->stream,
-                           K, per, (const R *)p->grid.p, twf, (C *)p->fft_B.p);
+                           K, per, (const R *)p->grid.p, twf, (C *)p->fftwork.p);
     } else {
         constexpr int XR = x_rows<C>(), YS = y_seqs<C>();
         static_assert(fft_threads(N, XR / 2) <= kFftMaxThreads &&
@@ -872,9 +872,9 @@ static void pruned_fwd(bs_plan_t p) {
         if (ly > 65536) allow_big_lds<k_fft_y_fwd<R, N>>(p->device);
         hipLaunchKernelGGL((k_fft_x_fwd<R, N>), dim3(8 * px), dim3(fft_threads(N, XR / 2)),
                            lx, p->stream, nrows, K1, px, (const R *)p->grid.p, twf,
-                           (C *)p->fft_A.p);
+                           (C *)p->spec.p);
         hipLaunchKernelGGL((k_fft_y_fwd<R, N>), dim3(8 * py), dim3(fft_threads(N, YS)), ly,
-                           p->stream, K, py, (const C *)p->fft_A.p, twf, (C *)p->fft_B.p);
+                           p->stream, K, py, (const C *)p->spec.p, twf, (C *)p->fftwork.p);
     }
 }
 
@@ -896,7 +896,7 @@ static void pruned_spectral(bs_plan_t p, int psi) {
         hipLaunchKernelGGL((k_fft_z_spectral<R, N, IPT>), dim3(8 * pz),
                            dim3(ceil_div(3 * KZ * fft_max_nj(N), IPT)), lds, p->stream, K, KZ,
                            pz, psi, k0, inv4a2, 1.0 / (L * L * L), dec2, twf, twi,
-                           (C *)p->fft_B.p);
+                           (C *)p->fftwork.p);
     } else {
         constexpr int KZ = z_cols<C>();
         static_assert(fft_threads(N, 3 * KZ) <= kFftMaxThreads,
@@ -906,7 +906,7 @@ static void pruned_spectral(bs_plan_t p, int psi) {
         if (lds > 65536) allow_big_lds<k_fft_zt_spectral<R, N>>(p->device);
         hipLaunchKernelGGL((k_fft_zt_spectral<R, N>), dim3(8 * pz),
                            dim3(fft_threads(N, 3 * KZ)), lds, p->stream, K, pz, psi, k0, inv4a2,
-                           1.0 / (L * L * L), dec2, twf, (C *)p->fft_B.p);
+                           1.0 / (L * L * L), dec2, twf, (C *)p->fftwork.p);
     }
 }
 
@@ -921,7 +921,7 @@ static void pruned_inv(bs_plan_t p) {
         if (lds > 65536) allow_big_lds<k_fft_yx_inv<R, N>>(p->device);
         const int per = ceil_div(3 * n, 8);
         hipLaunchKernelGGL((k_fft_yx_inv<R, N>), dim3(8 * per), dim3(n * mnj), lds, p->stream,
-                           K, per, (const C *)p->fft_B.p, twi, (R *)p->grid.p);
+                           K, per, (const C *)p->fftwork.p, twi, (R *)p->grid.p);
     } else {
         constexpr int YS = y_inv_seqs<C>(), XY = xi_rows<C>(), XS = 3 * XY / 2;
         static_assert(fft_threads(N, YS) <= kFftMaxThreads &&
@@ -932,9 +932,9 @@ static void pruned_inv(bs_plan_t p) {
         if (ly > 65536) allow_big_lds<k_fft_y_inv<R, N>>(p->device);
         if (lx > 65536) allow_big_lds<k_fft_x_inv<R, N>>(p->device);
         hipLaunchKernelGGL((k_fft_y_inv<R, N>), dim3(8 * py), dim3(fft_threads(N, YS)), ly,
-                           p->stream, K, py, (const C *)p->fft_B.p, twi, (C *)p->fft_A.p);
+                           p->stream, K, py, (const C *)p->fftwork.p, twi, (C *)p->spec.p);
         hipLaunchKernelGGL((k_fft_x_inv<R, N>), dim3(8 * px), dim3(fft_threads(N, XS)),
-                           lx, p->stream, K1, px, (const C *)p->fft_A.p, twi, (R *)p->grid.p);
+                           lx, p->stream, K1, px, (const C *)p->spec.p, twi, (R *)p->grid.p);
     }
 }
 

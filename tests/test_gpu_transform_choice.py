@@ -62,3 +62,24 @@ def test_mixed_precision_and_other_sizes(B):
         plan = B.Plan(prm)
         assert plan.transforms() == want == B.params_transforms(prm)
         plan.close()
+
+
+def test_own_transforms_share_hipfft_memory(B):
+    """At 384^3 in float64, where hipFFT needs no work area, a plan with its own
+    transforms holds one array of 3 (2K+1) n (K+1) complex values more than one
+    without, and no second one of 3 n^2 (K+1) beside the spectrum."""
+    import torch
+    n, used = 384, {}
+    torch.zeros(1, device="cuda")
+    for mode in (B.BS_FFT_LIBRARY, B.BS_FFT_AUTO, B.BS_FFT_LIBRARY, B.BS_FFT_AUTO):
+        print(f"\n[case] plan at {n}, mode {mode}", flush=True)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        plan = B.Plan(B.make_params(L=6.0, a=1e-6, tol=1e-6, grid_n=n, fft_mode=mode))
+        torch.cuda.synchronize()
+        used[mode] = before - torch.cuda.mem_get_info()[0]
+        K = plan.params().K
+        plan.close()
+    extra = used[B.BS_FFT_AUTO] - used[B.BS_FFT_LIBRARY]
+    print(f"  {used}, extra {extra / 1e6:.0f} MB")
+    assert extra < 3 * (2 * K + 1) * n * (K + 1) * 16 + (64 << 20)
