@@ -132,10 +132,6 @@ void exclusive_scan(bs_plan_t p, const int *in, int *out, int n, int *sums) {
     scan_arrays(p, 1, &in, &out, &n, sums, nullptr);
 }
 
-// Bins are ordered by original index (k_sort_all); a bin too large for LDS
-// ranks into the key array, which is free once the scatter is done.
-constexpr int kSortLds = 2048;
-
 // ------------------------------------------------------- fused bin passes
 // The three sorts (quadrature points by spread tile, quadrature points by pair
 // cell, nodes by pair cell) run side by side: each pass below is one launch
@@ -143,7 +139,8 @@ constexpr int kSortLds = 2048;
 struct SortSet {
     int *key[3], *cnt[3], *start[3], *fill[3], *perm[3];
     int nbins[3], nitems[3];
-    int per[3], ngrp[3];   // bins per wavefront of the per-bin sort, wavefronts
+    int share[3], nwave[3];   // the per-bin sort: entries per wavefront, wavefronts
+    int *tmp[3];              // scratch of the array's size, free until the gather
 };
 
 
@@ -215,54 +212,114 @@ __global__ void k_scatter_all(SortSet S) {
     if (act) S.perm[a][S.start[a][k] + slot] = i;
 }
 
-// Orders every bin's entries by original index.  A wavefront takes per[a]
-// consecutive bins of set a, whose entries form one contiguous range: staged in
-// LDS with the bins' bounds, and each entry counts the smaller ones of its own
-// bin, so that the lanes stay busy whatever the bins hold (a wavefront per
-// bin left most lanes idle on bins of a few points: 298 -> 55 us for the 1e6-node
-// tangle's 8e5 bins).  A range beyond the LDS goes bin by bin.
-__global__ __launch_bounds__(64) void k_sort_all(SortSet S) {
-    int g = blockIdx.x, a = 0;
-    if (g >= S.ngrp[0]) { g -= S.ngrp[0]; a = 1; }
-    if (a == 1 && g >= S.ngrp[1]) { g -= S.ngrp[1]; a = 2; }
-    if (a == 2 && g >= S.ngrp[2]) return;
-    __shared__ int v[kSortLds], st[65];
-    const int lane = threadIdx.x, per = S.per[a], b0 = g * per;
-    const int nb = min(per, S.nbins[a] - b0);
-    const int *start = S.start[a];
-    int *perm = S.perm[a];
-    const int s0 = start[b0], e0 = start[b0 + nb], total = e0 - s0;
-    // the bins' counters are not read again: clear them for the next call
-    // (the per-filament kernel counts into them)
-    if (lane < nb) {
-        S.cnt[a][b0 + lane] = 0;
-        S.fill[a][b0 + lane] = 0;
-        st[lane] = start[b0 + lane] - s0;
-    } else {
-        st[lane] = total;
-    }
-    if (lane == 0) st[64] = total;
-    if (S.nbins[a] == 1) return;   // one bin: the scatter wrote the identity
-    if (total <= kSortLds) {
-        for (int i = lane; i < total; i += 64) v[i] = perm[s0 + i];
+// Orders every bin's entries by original index.  A wavefront takes the bins that
+// begin in its share of the array's entries, so that neither many empty bins nor a
+// few full ones, wherever they lie, leave work to one wavefront (groups of up to
+// 64 bins each, with the counting below for every bin, took 1.8 ms instead of 0.24
+// and 133 ms instead of 0.31 for clusters of 20000 and 1e5 nodes on 512^3; on the
+// 1e6-node tangle both take 0.40).  Those bins' entries form one contiguous range, of which
+// only the last bin may reach beyond the share.  Up to kSortLds entries: staged
+// in LDS, each counts the smaller ones of its own bin.  Beyond: so the bins but
+// the last, and the last one by digits (radix_sort_bin).  The other wavefronts
+// may be moving entries meanwhile, but only within their bins: a position's bin
+// can be read at any time.
+constexpr int kSortLds = 1024;
+
+// LDS of the per-bin sort: the staged entries, or the digits' counts
+struct SortLds {
+    int v[kSortLds];
+};
+
+// n distinct entries below 2^nbits at a, in ascending order, by one wavefront:
+// stable passes over eight bits at a time between a and t (n values of scratch).
+// Counting the smaller ones, as the bins in LDS do, took 1.5 s where 20000 nodes
+// fill a handful of bins, against 0.7 ms (all of the binning).
+__device__ __forceinline__ void radix_sort_bin(int *a, int *t, int n, int nbits, SortLds &S) {
+    const int lane = threadIdx.x & 63;
+    int *cnt = S.v;   // 256 counts, then the digits' next positions
+    int *src = a, *dst = t;
+    for (int sh = 0; sh < nbits; sh += 8) {
+        for (int i = lane; i < 256; i += 64) cnt[i] = 0;
         wave_lds_sync();
-        for (int i = lane; i < total; i += 64) {
-            int b = 0;   // the last bin that starts at or before i
-            if (nb > 1)
-                for (int step = 32; step > 0; step >>= 1)
-                    if (st[b + step] <= i) b += step;
-            const int lo = st[b], hi = st[b + 1], x = v[i];
-            int r = lo;
-#pragma unroll 8
-            for (int j = lo; j < hi; j++) r += (v[j] < x);
-            perm[s0 + r] = x;
+        for (int i = lane; i < n; i += 64) atomicAdd(&cnt[(src[i] >> sh) & 255], 1);
+        wave_lds_sync();
+        int c[4], s = 0;
+        for (int k = 0; k < 4; k++) { c[k] = cnt[4 * lane + k]; s += c[k]; }
+        int e = wave_incl_sum(s) - s;
+        for (int k = 0; k < 4; k++) { cnt[4 * lane + k] = e; e += c[k]; }
+        wave_lds_sync();
+        int next = lane < n ? src[lane] : 0;
+        for (int i0 = 0; i0 < n; i0 += 64) {
+            const int x = next, i = i0 + lane, d = (x >> sh) & 255;
+            const bool act = i < n;
+            if (i + 64 < n) next = src[i + 64];
+            // the lanes with the same digit
+            unsigned long long m = __ballot(act);
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                const unsigned long long bit = __ballot((d >> k) & 1);
+                m &= ((d >> k) & 1) ? bit : ~bit;
+            }
+            const int base = cnt[d];
+            wave_lds_sync();   // read before the group's last lane moves it on
+            const int r = bits_below(m);
+            if (act) {
+                dst[base + r] = x;
+                if (r + 1 == __popcll(m)) cnt[d] = base + r + 1;
+            }
+            wave_lds_sync();
         }
+        __threadfence();   // the pass's stores before the next one's loads
+        int *const p = src; src = dst; dst = p;
+    }
+    if (src != a) {
+        for (int i = lane; i < n; i += 64) a[i] = src[i];
+    }
+}
+
+// where the first bin that begins at or after position v of the entries begins
+__device__ __forceinline__ int sort_bound(const SortSet &S, int a, int v) {
+    if (v >= S.nitems[a]) return S.nitems[a];
+    const int b = S.key[a][S.perm[a][v]], s = S.start[a][b];
+    return s == v ? v : S.start[a][b + 1];
+}
+
+__global__ __launch_bounds__(64) void k_sort_all(SortSet S) {
+    int w = blockIdx.x, a = 0;
+    if (w >= S.nwave[0]) { w -= S.nwave[0]; a = 1; }
+    if (a == 1 && w >= S.nwave[1]) { w -= S.nwave[1]; a = 2; }
+    __shared__ SortLds L;
+    const int lane = threadIdx.x;
+    int *perm = S.perm[a], *cnt = S.cnt[a], *fill = S.fill[a];
+    const int *key = S.key[a], *start = S.start[a];
+    // the bins' counters are not read again: those of the bins that hold entries are
+    // cleared for the next call (the per-filament kernel counts into them)
+    if (S.nbins[a] == 1) {   // one bin: the scatter wrote the identity
+        if (lane == 0) cnt[0] = fill[0] = 0;
         return;
     }
-    for (int k = 0; k < nb; k++) {
-        const int s = start[b0 + k], n = start[b0 + k + 1] - s;
-        rank_sort_bin<kSortLds>(perm, S.key[a], s, n, v);
-        __syncthreads();   // the LDS is free for the next bin
+    const int s0 = sort_bound(S, a, w * S.share[a]);
+    int e0 = sort_bound(S, a, (w + 1) * S.share[a]);
+    if (s0 >= e0) return;
+    if (e0 - s0 > kSortLds) {
+        const int b = key[perm[e0 - 1]], s = start[b];
+        if (lane == 0) cnt[b] = fill[b] = 0;
+        const int nbits = 32 - __clz(S.nitems[a] - 1);
+        radix_sort_bin(perm + s, S.tmp[a] + s, e0 - s, nbits, L);
+        e0 = s;   // at most a share is left
+        __syncthreads();   // the LDS is free
+    }
+    const int total = e0 - s0;
+    for (int i = lane; i < total; i += 64) L.v[i] = perm[s0 + i];
+    wave_lds_sync();
+    for (int i = lane; i < total; i += 64) {
+        const int x = L.v[i], b = key[x], lo = start[b] - s0, hi = start[b + 1] - s0;
+        cnt[b] = 0;
+        fill[b] = 0;
+        int r = lo;
+#pragma unroll 8
+        for (int j = lo; j < hi; j++) r += (L.v[j] < x);
+        perm[s0 + r] = x;
     }
 }
 
@@ -347,10 +404,10 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_all(int M, int w, int Q
     for (int i = threadIdx.x; i < nt * w; i += kGatherBlock) ker[i] = lk[i];
 }
 
-// wavefronts per set of the per-bin sort (eight per SIMD): fewer bins than
-// that get one each (the 64^3 ellipses' 512 tiles: 10.5 us at two wavefronts
-// per CU and several bins each, 5.1 with one)
-constexpr int kSortWaves = 8192;
+// entries per wavefront of the per-bin sort: 64 while that leaves fewer wavefronts
+// than the chip holds (eight per SIMD), 256 at most
+constexpr int kSortWaves = 8192, kSortShare = 64, kSortShareMax = 256;
+static_assert(kSortShareMax <= kSortLds && 256 <= kSortLds, "a share, or the digits, in LDS");
 // arrays of at most this many bins are scanned by one workgroup each (one
 // launch, 5.0 us at 14112 bins and 7.4 at 21312; the three launches of the
 // blocked scan take 14 us)
@@ -372,12 +429,12 @@ void build_bins(bs_plan_t p) {
     S.fill[2] = (int *)p->nd_fill.p; S.perm[2] = (int *)p->nd_perm.p;
     S.nbins[0] = ntiles; S.nbins[1] = ncp; S.nbins[2] = nc3;
     S.nitems[0] = M; S.nitems[1] = M; S.nitems[2] = N;
+    S.tmp[0] = (int *)p->sp_q.p; S.tmp[1] = (int *)p->pq_pos.p; S.tmp[2] = (int *)p->nd_rec.p;
     for (int a = 0; a < 3; a++) {
-        // bins per wavefront: at least kSortWaves wavefronts per set while
-        // there are bins for them, and 64 bins at most
-        const int per = S.nbins[a] / kSortWaves;
-        S.per[a] = per < 1 ? 1 : (per > 64 ? 64 : per);
-        S.ngrp[a] = ceil_div(S.nbins[a], S.per[a]);
+        int sh = kSortShare;
+        while (sh < kSortShareMax && (int64_t)sh * kSortWaves < S.nitems[a]) sh *= 2;
+        S.share[a] = sh;
+        S.nwave[a] = S.nbins[a] == 1 ? 1 : ceil_div(S.nitems[a], sh);
     }
     const int maxb = ntiles > ncp ? ntiles : ncp;
     GatherOut G;
@@ -395,7 +452,7 @@ void build_bins(bs_plan_t p) {
         scan_arrays(p, 3, S.cnt, S.start, S.nbins, (int *)p->red_tmp.p, nullptr);
     }
     hipLaunchKernelGGL(k_scatter_all, dim3(ceil_div(2 * (int64_t)M + N, bs)), dim3(bs), 0, p->stream, S);
-    hipLaunchKernelGGL(k_sort_all, dim3(S.ngrp[0] + S.ngrp[1] + S.ngrp[2]), dim3(64), 0, p->stream, S);
+    hipLaunchKernelGGL(k_sort_all, dim3(S.nwave[0] + S.nwave[1] + S.nwave[2]), dim3(64), 0, p->stream, S);
     const dim3 gg(ceil_div(3 * (int64_t)M, kGatherBlock) + ceil_div(N, kGatherBlock));
     const double *x = (const double *)p->d_x.p;
     const int *off = (const int *)p->d_off.p, *fil = (const int *)p->d_fil.p;

@@ -120,6 +120,12 @@ __device__ __forceinline__ int prev_node_d(const int *off, const int *fil, int j
     return (j > off[f]) ? j - 1 : off[f + 1] - 1;
 }
 
+// lanes below this one with their bit set
+__device__ __forceinline__ int bits_below(unsigned long long m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                          __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+
 // Wavefront sums by data-parallel moves (no LDS): inclusive prefix sum over the
 // lanes, and the total of a double, which ends in lane 63.
 template <int CTRL, int ROWS>

@@ -56,12 +56,6 @@ PairGeom pair_geom(bs_plan_t p);
 // accepted candidates queued per wavefront (a ring of two steps' worth)
 constexpr int kQueue = 128;
 
-// lanes below this one with their bit set
-__device__ __forceinline__ int bits_below(unsigned long long m) {
-    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                          __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-}
-
 // A wavefront's queue of candidates within r_c (ring, positions [head, tail),
 // wavefront-uniform) and the sums of their terms, run 64 at a time.
 template <bool PSI>
