@@ -241,33 +241,50 @@ __device__ __forceinline__ void radix_sort_bin(int *a, int *t, int n, int nbits,
     for (int sh = 0; sh < nbits; sh += 8) {
         for (int i = lane; i < 256; i += 64) cnt[i] = 0;
         wave_lds_sync();
-        for (int i = lane; i < n; i += 64) atomicAdd(&cnt[(src[i] >> sh) & 255], 1);
+        // (four steps' loads in flight)
+        for (int i0 = 0; i0 < n; i0 += 256) {
+            int x[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) x[u] = src[min(i0 + 64 * u + lane, n - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+                if (i0 + 64 * u + lane < n) atomicAdd(&cnt[(x[u] >> sh) & 255], 1);
+        }
         wave_lds_sync();
         int c[4], s = 0;
         for (int k = 0; k < 4; k++) { c[k] = cnt[4 * lane + k]; s += c[k]; }
         int e = wave_incl_sum(s) - s;
         for (int k = 0; k < 4; k++) { cnt[4 * lane + k] = e; e += c[k]; }
         wave_lds_sync();
-        int next = lane < n ? src[lane] : 0;
-        for (int i0 = 0; i0 < n; i0 += 64) {
-            const int x = next, i = i0 + lane, d = (x >> sh) & 255;
-            const bool act = i < n;
-            if (i + 64 < n) next = src[i + 64];
-            // the lanes with the same digit
-            unsigned long long m = __ballot(act);
+        int next[4];
 #pragma unroll
-            for (int k = 0; k < 8; k++) {
-                const unsigned long long bit = __ballot((d >> k) & 1);
-                m &= ((d >> k) & 1) ? bit : ~bit;
+        for (int u = 0; u < 4; u++) next[u] = src[min(64 * u + lane, n - 1)];
+        for (int i0 = 0; i0 < n; i0 += 256) {
+            int x[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                x[u] = next[u];
+                next[u] = src[min(i0 + 256 + 64 * u + lane, n - 1)];
             }
-            const int base = cnt[d];
-            wave_lds_sync();   // read before the group's last lane moves it on
-            const int r = bits_below(m);
-            if (act) {
-                dst[base + r] = x;
-                if (r + 1 == __popcll(m)) cnt[d] = base + r + 1;
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const bool act = i0 + 64 * u + lane < n;
+                const int d = (x[u] >> sh) & 255;
+                // the lanes with the same digit
+                unsigned long long m = __ballot(act);
+#pragma unroll
+                for (int k = 0; k < 8; k++) {
+                    const unsigned long long bit = __ballot((d >> k) & 1);
+                    m &= ((d >> k) & 1) ? bit : ~bit;
+                }
+                const int base = cnt[d], r = bits_below(m);
+                wave_lds_sync();   // read before the group's last lane moves it on
+                if (act) {
+                    dst[base + r] = x[u];
+                    if (r + 1 == __popcll(m)) cnt[d] = base + r + 1;
+                }
+                wave_lds_sync();
             }
-            wave_lds_sync();
         }
         __threadfence();   // the pass's stores before the next one's loads
         int *const p = src; src = dst; dst = p;

@@ -15,6 +15,9 @@
 // is the kernel's transform per axis (one factor undoes the spreading, the
 // other pre-compensates the interpolation).  Every other mode is set to 0
 // (k = 0 by zero net vorticity; |m_i| > K by truncation).
+#include <algorithm>
+#include <climits>
+
 #include "bs_internal.h"
 #include "bs_device.h"
 
@@ -53,13 +56,13 @@ namespace bs {
 // run on one XCD), so neighbouring tiles, which share candidate bins and the
 // cache lines of their grid rows, go through the same L2.
 //
+// One tile; nothing if it has more than `full` candidates.
 template <typename R, int W, int TT, int WAVES, bool MMA>
-__global__ __launch_bounds__(64 * WAVES) void k_spread(int n, int NT, int nbv, int per_xcd,
-                                                       const int *__restrict__ start,
-                                                       const int4 *__restrict__ base,
-                                                       const R *__restrict__ ker,
-                                                       const R *__restrict__ q,
-                                                       R *__restrict__ grid) {
+__device__ __forceinline__ void spread_tile(int tile, int n, int NT, int nbv, int full,
+                                            const int *__restrict__ start,
+                                            const int4 *__restrict__ base,
+                                            const R *__restrict__ ker, const R *__restrict__ q,
+                                            R *__restrict__ grid) {
     constexpr int T3 = TT * TT * TT;
     constexpr int ZL = T3 / 64;
     // staged words per candidate: the vector form stages T weights per axis
@@ -74,9 +77,6 @@ __global__ __launch_bounds__(64 * WAVES) void k_spread(int n, int NT, int nbv, i
     __shared__ R lds[STAGE > RED ? STAGE : RED];
     __shared__ int bin_s[NB3], bin_o[NB3], bin_total;
     __shared__ int soff[MMA ? WAVES * 64 : 1];
-    const int ntiles = NT * NT * NT;
-    const int tile = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (tile >= ntiles) return;
     const int tx = tile % NT, ty = (tile / NT) % NT, tz = tile / (NT * NT);
     const int t0[3] = {tx * TT, ty * TT, tz * TT};
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -124,6 +124,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_spread(int n, int NT, int nbv, i
     }
     __syncthreads();
     const int total = bin_total;
+    if (total > full) return;
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     // wavefront w takes chunks w, w + WAVES, ...; every wavefront runs the
     // same number of rounds so that the block barriers match
@@ -333,15 +334,95 @@ __global__ __launch_bounds__(64 * WAVES) void k_spread(int n, int NT, int nbv, i
     }
 }
 
-// Grids with fewer tiles than this split each tile's candidates over 4
-// wavefronts (more parallelism for small grids), in float64 on the matrix
-// cores: at 64^3 (512 tiles) 21.5 us against 42.3 with one wavefront per tile,
-// at 128^3 (4096) 73.4 against 49.8 and at 160^3 (8000) 145 against 59 (the
-// vector form: 22, 75 and 148).  float32 grids keep their summation order: the
-// vector form below 8192 tiles, over 8 wavefronts up to kSpreadWideTiles.
+template <typename R, int W, int TT, int WAVES, bool MMA>
+__global__ __launch_bounds__(64 * WAVES) void k_spread(int n, int NT, int nbv, int per_xcd, int full,
+                                                       const int *__restrict__ start,
+                                                       const int4 *__restrict__ base,
+                                                       const R *__restrict__ ker,
+                                                       const R *__restrict__ q,
+                                                       R *__restrict__ grid) {
+    const int tile = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (tile >= NT * NT * NT) return;
+    spread_tile<R, W, TT, WAVES, MMA>(tile, n, NT, nbv, full, start, base, ker, q, grid);
+}
+
+// The tiles of more than `full` candidates, which the form of one wavefront per tile
+// leaves out, by four wavefronts each (in the vector form, as fast there and with
+// the same LDS at every width): a workgroup finds them among its kFullTiles tiles,
+// dealt round-robin over a prime number of workgroups, so that neighbours along
+// any axis go to different ones.
+constexpr int kFullBlocks = 509, kFullTiles = 17;
+template <typename R, int W, int TT>
+__global__ __launch_bounds__(256) void k_spread_full(int n, int NT, int nbv, int full,
+                                                     const int *__restrict__ start,
+                                                     const int4 *__restrict__ base,
+                                                     const R *__restrict__ ker,
+                                                     const R *__restrict__ q,
+                                                     R *__restrict__ grid) {
+    __shared__ int tot[kFullTiles];
+    const int ntiles = NT * NT * NT, nbins = nbv * nbv * nbv, k = threadIdx.x >> 3;
+    if (threadIdx.x < kFullTiles) tot[threadIdx.x] = 0;
+    __syncthreads();
+    const int t = blockIdx.x + kFullBlocks * k;
+    if (k < kFullTiles && t < ntiles) {
+        const int tx = t % NT, ty = (t / NT) % NT, tz = t / (NT * NT);
+        int s = 0;
+        for (int i = threadIdx.x & 7; i < nbins; i += 8) {
+            int bz = tz - i / (nbv * nbv), by = ty - (i / nbv) % nbv, bx = tx - i % nbv;
+            if (bz < 0) bz += NT;
+            if (by < 0) by += NT;
+            if (bx < 0) bx += NT;
+            const int bin = (bz * NT + by) * NT + bx;
+            s += start[bin + 1] - start[bin];
+        }
+        atomicAdd(&tot[k], s);
+    }
+    __syncthreads();
+    for (int j = 0; j < kFullTiles; j++) {
+        if (tot[j] <= full) continue;   // uniform over the workgroup
+        spread_tile<R, W, TT, 4, false>(blockIdx.x + kFullBlocks * j, n, NT, nbv, INT_MAX, start, base,
+                                        ker, q, grid);
+        __syncthreads();   // its LDS is free
+    }
+}
+
+// Float32, and the 4^3 tiles of grids that are no multiple of 8 (which have no
+// matrix-core form): the vector form, below kSpreadSplitTiles tiles over 4
+// wavefronts per tile (more parallelism for small grids), in float32 over 8 up to
+// kSpreadWideTiles, and keep their summation order.
 constexpr int kSpreadSplitTiles = 8192;
-constexpr int kSpreadSplitTiles64 = 2048;
 constexpr int kSpreadWideTiles = 512;
+
+// Float64 on 8^3 tiles, below kSpreadSplitTiles tiles (us for tangles of 1e4, 5e4
+// and 2e5 nodes, the vector form over 4 wavefronts first, the matrix cores over 4
+// second, with one wavefront per tile third):
+//   64^3, w = 8     47 122 380     45 110 364
+//   64^3, w = 12    86 264 907    104 305 1014
+//   104^3, w = 8    59 118 337     57 117 329     62 146 445
+//   112^3, w = 8    64 126 339     64             57 134 421
+//   128^3, w = 8    80 139 341     78 136 338     53 121 381
+//   160^3, w = 8   117 185 372    121 187 375     49 112 321
+//   128^3, w = 12  110 271 833                    86 256 860
+//   144^3, w = 14  141 323 980                   112 324 1101
+//   128^3, w = 16  143 357 1135                  152 481 1640
+//   160^3, w = 16  183 389 1142                  157 449 1526
+// Up to w = 11 the staging of 4 wavefronts leaves two workgroups per CU and the
+// matrix cores win; beyond, the vector form does.  One wavefront per tile needs
+// tiles enough to fill the chip, of few points each (`reach`: the points that reach a
+// tile were they evenly spread), the fewer the wider the kernel.
+enum class Spread64 { vector, split, one };
+static Spread64 spread64_form(int w, int ntiles, int64_t Nq) {
+    const double side = (w + 7) / 8.0, reach = side * side * side * Nq / ntiles;
+    if (w <= 11)
+        return ntiles >= 6000 || (ntiles >= 2560 && reach <= 200.0) ? Spread64::one : Spread64::split;
+    return ntiles >= 4096 && reach <= (w <= 13 ? 900.0 : 100.0) ? Spread64::one : Spread64::vector;
+}
+// One wavefront per tile leaves the tiles that a cluster of filaments fills to
+// k_spread_full (20000 nodes within 0.1 L on 128^3: 0.70 ms, without it 2.4, the
+// vector form for every tile 0.69; 3 to 4 us where no tile is full): those of more
+// candidates than this, and than this many times what evenly spread points give.
+constexpr int kSpreadFull = 1024, kSpreadFullTimes = 4;
+static_assert(kSpreadSplitTiles <= kFullBlocks * kFullTiles, "every tile is looked at");
 
 template <typename R, int TT>
 static void spread_tt(bs_plan_t p) {
@@ -351,7 +432,13 @@ static void spread_tt(bs_plan_t p) {
     if (nbv > nb) return;   // the kernel's bin table holds nb^3 bins
     const int ntiles = p->NT * p->NT * p->NT;
     const int per = ceil_div(ntiles, 8);
-    const bool split = ntiles < (sizeof(R) == 8 ? kSpreadSplitTiles64 : kSpreadSplitTiles);
+    const bool few = ntiles < kSpreadSplitTiles;
+    const Spread64 form = sizeof(R) == 8 && TT == 8 && few ? spread64_form(w, ntiles, p->Nq)
+                                                           : Spread64::vector;
+    const bool split = few && form != Spread64::one;
+    const int64_t even = (int64_t)nbv * nbv * nbv * p->Nq / ntiles;   // candidates per tile
+    const int full = form == Spread64::one ? (int)std::max<int64_t>(kSpreadFull, kSpreadFullTimes * even)
+                                           : INT_MAX;
     const bool wide = sizeof(R) == 4 && TT == 8 && ntiles <= kSpreadWideTiles;
     dim3 grid(8 * per), block(wide ? 512 : (split ? 256 : 64));
     const int *start = (const int *)p->sp_start.p;
@@ -363,16 +450,30 @@ static void spread_tt(bs_plan_t p) {
         if constexpr (sizeof(R) == 4) {                                                          \
             if (wide) {                                                                          \
                 hipLaunchKernelGGL((k_spread<R, WW, TT, 8, false>), grid, block, 0, p->stream,   \
-                                   p->n, p->NT, nbv, per, start, base, ker, q, g);               \
+                                   p->n, p->NT, nbv, per, full, start, base, ker, q, g);         \
+                break;                                                                           \
+            }                                                                                    \
+        }                                                                                        \
+        if constexpr (sizeof(R) == 8 && TT == 8) {                                               \
+            if (form == Spread64::one) {                                                         \
+                hipLaunchKernelGGL((k_spread<R, WW, TT, 1, true>), grid, block, 0, p->stream,    \
+                                   p->n, p->NT, nbv, per, full, start, base, ker, q, g);         \
+                hipLaunchKernelGGL((k_spread_full<R, WW, TT>), dim3(kFullBlocks), dim3(256), 0,  \
+                                   p->stream, p->n, p->NT, nbv, full, start, base, ker, q, g);   \
+                break;                                                                           \
+            }                                                                                    \
+            if (form == Spread64::split) {                                                       \
+                hipLaunchKernelGGL((k_spread<R, WW, TT, 4, (WW) <= 11>), grid, block, 0,         \
+                                   p->stream, p->n, p->NT, nbv, per, full, start, base, ker, q, g); \
                 break;                                                                           \
             }                                                                                    \
         }                                                                                        \
         if (split)                                                                               \
-            hipLaunchKernelGGL((k_spread<R, WW, TT, 4, TT == 8 && sizeof(R) == 8>), grid, block,  \
-                               0, p->stream, p->n, p->NT, nbv, per, start, base, ker, q, g);     \
+            hipLaunchKernelGGL((k_spread<R, WW, TT, 4, false>), grid, block, 0, p->stream,       \
+                               p->n, p->NT, nbv, per, full, start, base, ker, q, g);             \
         else                                                                                     \
             hipLaunchKernelGGL((k_spread<R, WW, TT, 1, TT == 8>), grid, block, 0, p->stream,     \
-                               p->n, p->NT, nbv, per, start, base, ker, q, g);                   \
+                               p->n, p->NT, nbv, per, full, start, base, ker, q, g);             \
         break;
     switch (w) {
         SPREAD_CASE(4) SPREAD_CASE(5) SPREAD_CASE(6) SPREAD_CASE(7) SPREAD_CASE(8)

@@ -1,0 +1,96 @@
+"""The float64 spread's forms on 8^3 tiles (one or four wavefronts per tile, matrix
+cores or vector, the full tiles of a cluster by themselves): the vorticity's Fourier
+coefficients are linear in the filaments, so those of a set are the sums of those
+of ten parts, which take the direct path of small inputs.  Both sum the same float64
+terms in other orders, up to 1e4 of them in a cell of a cluster: 1e-12 of the
+grid's transform, that is, of the coefficients before the division by the
+kernel's, which raises the rounding of the highest ones by up to 1e4 at w = 12.
+
+A cluster fills a few tiles: its spread must not be one wavefront's work per
+tile (2.4 and 5 ms for the two below; 0.93 and 1.5 with the full tiles shared out,
+so 1.8 and 3)."""
+import math
+
+import numpy as np
+import pytest
+
+from paper_2406_07366_amd import workloads as W
+from tests.test_gpu_clusters import cluster
+
+pytestmark = pytest.mark.gpu
+
+L = 2 * math.pi
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2406_07366_amd import binding
+    return binding
+
+
+def plan_for(B, fs, n, w):
+    return B.Plan(B.make_params(L=fs.L, a=fs.a, tol=1e-6, grid_n=n, w=w, alpha=35.0 / fs.L,
+                                rcut=0.1 * fs.L))
+
+
+def kernel_transform(p):
+    """F(m), m = 0..K, of the Kaiser-Bessel kernel the plan spreads with."""
+    z, wt = np.polynomial.legendre.leggauss(256)
+    sq = np.sqrt(1 - z * z)
+    phi = np.sinh(p.zeta * sq) / (np.sinh(p.zeta) * sq)
+    m = np.arange(p.K + 1)
+    return 0.5 * p.w * (wt * phi * np.cos(np.pi * np.outer(m, z) * p.w / p.grid_n)).sum(1)
+
+
+SETS = {"spread out": lambda: W.ellipses(200, 100, seed=3), "cluster": lambda: cluster(200, 100, 0.1 * L),
+        "dense cluster": lambda: cluster(200, 100, 0.02 * L)}
+
+
+@pytest.mark.parametrize("which", list(SETS))
+@pytest.mark.parametrize("n,w", [(128, 8), (160, 12), (112, 8), (104, 11), (96, 12), (128, 16),
+                                 (144, 14), (64, 8), (120, 4)])
+def test_forms_agree(B, n, w, which):
+    fs = SETS[which]()
+    print(f"\n[case] {which}, grid {n} w {w}", flush=True)
+    plan = plan_for(B, fs, n, w)
+    xyz, g = B.load_workload(fs)
+
+    def modes(f0, f1):
+        a, b = fs.offsets[f0], fs.offsets[f1]
+        plan.set_filaments(fs.offsets[f0:f1 + 1] - a, xyz[a:b].contiguous(), g[f0:f1].contiguous())
+        return plan.vorticity_modes().cpu().numpy()
+
+    whole = modes(0, fs.n_fil)
+    again = modes(0, fs.n_fil)
+    assert np.array_equal(whole, again)
+    parts = sum(modes(f, f + 20) for f in range(0, fs.n_fil, 20))
+    plan.status()
+    p = plan.params()
+    plan.close()
+    F = kernel_transform(p)
+    Fs = F[np.abs(np.arange(-p.K, p.K + 1))]
+    scale = F[:, None, None] * Fs[None, :, None] * Fs[None, None, :]   # [mz][my + K][mx + K]
+    whole, parts = whole * scale[..., None, None], parts * scale[..., None, None]
+    err = np.abs(whole - parts).max() / np.abs(whole).max()
+    print(f"  {err:.2e}")
+    assert err < 1e-12
+
+
+@pytest.mark.parametrize("R,limit", [(0.1, 1.8), (0.02, 3.0)])
+def test_full_tiles_are_shared_out(B, R, limit):
+    fs = cluster(200, 100, R * L)
+    print(f"\n[case] spread of a cluster within {R} L on 128^3", flush=True)
+    plan = B.Plan(B.make_params(L=fs.L, a=fs.a, tol=1e-6, grid_n=128))
+    xyz, g = B.load_workload(fs)
+    plan.set_profiling(True)
+    ms = []
+    for _ in range(4):
+        plan.stage_times(reset=True)
+        plan.set_filaments(fs.offsets, xyz, g)
+        plan.velocity()
+        ms.append(plan.stage_times(reset=True)["spread"][0])
+    plan.close()
+    print(f"  {min(ms):.3f} ms")
+    assert min(ms) < limit
