@@ -14,6 +14,8 @@
 //
 // Within a bin, entries are ordered by original index so that every sum the
 // later kernels form has a fixed order (bitwise reproducible results).
+#include <algorithm>
+
 #include "bs_internal.h"
 #include "bs_device.h"
 
@@ -426,8 +428,8 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_all(int M, int w, int Q
 constexpr int kSortWaves = 8192, kSortShare = 64, kSortShareMax = 256;
 static_assert(kSortShareMax <= kSortLds && 256 <= kSortLds, "a share, or the digits, in LDS");
 // arrays of at most this many bins are scanned by one workgroup each (one
-// launch, 5.0 us at 14112 bins and 7.4 at 21312; the three launches of the
-// blocked scan take 14 us)
+// launch, 5.0 us at 14112 bins and 7.4 at 21312, but 240 at the 98^3 node cells of a
+// loose tolerance on 256^3; the three launches of the blocked scan take 14 us)
 constexpr int kScanSmall = 32768;
 
 void build_bins(bs_plan_t p) {
@@ -453,7 +455,7 @@ void build_bins(bs_plan_t p) {
         S.share[a] = sh;
         S.nwave[a] = S.nbins[a] == 1 ? 1 : ceil_div(S.nitems[a], sh);
     }
-    const int maxb = ntiles > ncp ? ntiles : ncp;
+    const int maxb = std::max({ntiles, ncp, nc3});
     GatherOut G;
     G.base = (int4 *)p->sp_base.p;
     G.ker = p->sp_ker.p;
