@@ -516,10 +516,10 @@ static int set_filaments(bs_plan_t P, int64_t nfil, const int64_t *offsets, cons
             (rc = ensure<int>(P, P->nd_fill, nc3 + 1)) || (rc = ensure<int>(P, P->nd_perm, N)) ||
             (rc = ensure<double4>(P, P->nd_rec, N)))
             return rc;
-        if (P->order == 4 && maxn > kPcrLds && (rc = ensure<double>(P, P->spline_tmp, 12 * N)))
+        if (P->order == 4 && maxn > kPcrLds && (rc = ensure<double>(P, P->spline_tmp, kPcrScratch * N)))
             return rc;
         if (P->order == 6 && maxn > kPcr5Lds &&
-            (rc = ensure<double>(P, P->spline_tmp, 36 * N)))
+            (rc = ensure<double>(P, P->spline_tmp, kBlkScratch * N)))
             return rc;
         if (P->prm.ns_mode != BS_NS_OFF) {
             size_t mp = (size_t)N * P->ns_max_per_node;

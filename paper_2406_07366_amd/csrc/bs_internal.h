@@ -18,6 +18,8 @@ constexpr int kMaxQ = 4;
 // longer filaments use the plan's global scratch
 constexpr int kPcrLds = 128;
 constexpr int kPcr5Lds = 64;
+// doubles per node of the two systems that the solve alternates between
+constexpr int kPcrScratch = 2 * 7, kBlkScratch = 2 * 22;
 constexpr int kMinW = 4, kMaxW = 16;
 
 // Gauss-Legendre nodes h_i in [0,1] and weights w_i (sum 1) for Q = 1..4.
