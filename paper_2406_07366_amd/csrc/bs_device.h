@@ -94,15 +94,31 @@ __device__ __forceinline__ double kb_phi(double z, double zeta, double inv_den) 
 }
 
 // The same in float64 for one exponential: with a = exp(zeta (s - 1)) and c2 =
-// exp(-2 zeta), phi = (a - c2 / a) / s * inv_den.  The difference loses
-// relative digits only near s = 0, where phi is ~1e-6 of its centre value
-// (absolute error there ~1e-22); ~60 instructions instead of ~200.
+// exp(-2 zeta), phi = (a - c2 / a) / s * inv_den.  The difference cancels where
+// y = zeta s is small (an absolute error of eps exp(-zeta) / s: 9e-12 at w = 4 for z
+// within rounding of 1, 4e-15 at w = 8); below y = 1 phi is the Taylor series of
+// sinh(y) / y times its value at the edge (remainder 1 / 19!), so the relative
+// error stays at rounding everywhere.
 __device__ __forceinline__ double kb_phi64(double z, const KbPhi &K) {
     const double s2 = 1.0 - z * z;
     if (s2 <= 0.0) return K.edge;
-    const double r = rsqrt_nr(s2);
-    const double a = exp(K.zeta * (s2 * r - 1.0));
-    return (a - K.c2 * rcp_nr(a)) * r * K.inv_den;
+    const double s = sqrt(s2);
+    const double a = exp(K.zeta * (s - 1.0));
+    const double far = (a - K.c2 * rcp_nr(a)) * rcp_nr(s) * K.inv_den;
+    const double t = K.zeta * K.zeta * s2;   // y^2
+    constexpr double c[9] = {1.0,
+                             1.0 / 6.0,
+                             1.0 / 120.0,
+                             1.0 / 5040.0,
+                             1.0 / 362880.0,
+                             1.0 / 39916800.0,
+                             1.0 / 6227020800.0,
+                             1.0 / 1307674368000.0,
+                             1.0 / 355687428096000.0};
+    double p = c[8];
+#pragma unroll
+    for (int k = 7; k >= 0; k--) p = fma(p, t, c[k]);
+    return t < 1.0 ? p * K.edge : far;
 }
 template <typename R>
 __device__ __forceinline__ R kb_value(double z, const KbPhi &K) {
