@@ -46,12 +46,13 @@ __device__ __forceinline__ int cell_key(const double *p, double L, int ncx, int 
 }
 
 // 1 / sqrt(a) for a > 0: the hardware estimate and two Newton steps
-// y <- y (3 - a y^2) / 2 (each squares the relative error), to rounding
+// y <- y + y (1 - a y^2) / 2 (each squares the relative error), to rounding: at most
+// 1.7e-16, where y (3 - a y^2) / 2, whose factor near 1 is rounded, reaches 2.8e-16
 __device__ __forceinline__ double rsqrt_nr(double a) {
     double y = __builtin_amdgcn_rsq(a);
     const double h = 0.5 * a;
-    y = y * fma(-h * y, y, 1.5);
-    y = y * fma(-h * y, y, 1.5);
+    y = fma(y, fma(-h * y, y, 0.5), y);
+    y = fma(y, fma(-h * y, y, 0.5), y);
     return y;
 }
 
