@@ -29,7 +29,6 @@ struct PairGeom {
     float ry, ratio;        // r_c in y cells with the margin, x cells per y cell
     int ncx, ncy;
 };
-template <bool PSI>
 __device__ __forceinline__ double g_short64(double x, const ShortFit &F) {
     constexpr double two_over_sqrtpi = 1.12837916709551257389615890312154517;
     const double inv = rcp_nr(kErfcxShift + x);
@@ -44,8 +43,7 @@ __device__ __forceinline__ double g_short64(double x, const ShortFit &F) {
 #pragma unroll
     for (int k = kExpDeg - 1; k >= 0; k--) e = fma(e, r, k < 2 ? 1.0 : (k == 2 ? 0.5 : F.e[k]));
     e = ldexp(e, (int)n);
-    // psi: erfc(x) = exp(-x^2) erfcx(x)
-    return PSI ? e * (p * inv) : e * fma(p, inv, two_over_sqrtpi * x);
+    return e * fma(p, inv, two_over_sqrtpi * x);
 }
 
 // rows of the cell list are found in float32 with this margin, in cells
@@ -80,13 +78,14 @@ struct PairQueue {
             const double4 q = chg[qp[sl]];
             const double fx = qx[sl], fy = qy[sl], fz = qz[sl];
             const double r2 = fx * fx + fy * fy + fz * fz;
-            const double ir = rsqrt_nr(r2);
-            const double g = g_short64<PSI>(alpha * (r2 * ir), fit);
             if (PSI) {
-                const double f = g * ir;
+                // (erfc and quotients to rounding: the fitted polynomial's error, 3e-15,
+                // would be the streamfunction's, to which every term adds alike)
+                const double rr = sqrt(r2), f = erfc(alpha * rr) / rr;
                 acc0 += f * q.x; acc1 += f * q.y; acc2 += f * q.z;
             } else {
-                const double f = g * (ir * ir * ir);
+                const double ir = rsqrt_nr(r2);
+                const double f = g_short64(alpha * (r2 * ir), fit) * (ir * ir * ir);
                 acc0 += f * (fy * q.z - fz * q.y);
                 acc1 += f * (fz * q.x - fx * q.z);
                 acc2 += f * (fx * q.y - fy * q.x);
