@@ -28,6 +28,7 @@
 
 #include "bs_internal.h"
 #include "bs_device.h"
+#include "ns_panels.h"
 
 namespace bs {
 
@@ -765,33 +766,6 @@ __device__ __forceinline__ double ns_delta(const double *C, const double *d1) {
     const double delta = 0.5 * sqrt(r2 / sp2);
     return delta < 1e-13 ? 1e-13 : delta;
 }
-// Panel k: 0 the centre panel, then those to its left up to 0, each ending at
-// three times the distance from ub at which it begins, then those to its right up
-// to 1 (clipped).  None when the distance is not a number.
-__device__ __forceinline__ int ns_panels(double ub, double delta) {
-    const double a0 = ub - delta < 0.0 ? 0.0 : ub - delta, b0 = ub + delta > 1.0 ? 1.0 : ub + delta;
-    int n = b0 > a0 ? 1 : 0;
-    for (double e = a0, w = delta; e > 0.0; w *= 3.0, n++) e = ub - 3.0 * w;
-    for (double e = b0, w = delta; e < 1.0; w *= 3.0, n++) e = ub + 3.0 * w;
-    return n;
-}
-__device__ __forceinline__ void ns_panel_bounds(double ub, double delta, int k, double *lo,
-                                                double *hi) {
-    *lo = fmax(ub - delta, 0.0);
-    *hi = fmin(ub + delta, 1.0);
-    double w = delta;
-    for (; k > 0 && *lo > 0.0; k--, w *= 3.0) {
-        *hi = *lo;
-        *lo = fmax(ub - 3.0 * w, 0.0);
-    }
-    if (k == 0) return;
-    *hi = fmin(ub + delta, 1.0);
-    for (w = delta; k > 0; k--, w *= 3.0) {
-        *lo = *hi;
-        *hi = fmin(ub + 3.0 * w, 1.0);
-    }
-}
-
 template <int DEG = 5>
 __device__ void ns_seg_integral(const Seg &s, const double *xs, const NsRule &R, double *acc) {
     const double ub = closest_u<DEG>(s, xs);
@@ -799,11 +773,11 @@ __device__ void ns_seg_integral(const Seg &s, const double *xs, const NsRule &R,
     seg_eval<DEG>(s, ub, C, d1);
     for (int q = 0; q < 3; q++) C[q] -= xs[q];
     const double delta = ns_delta(C, d1);
-    const int n = ns_panels(ub, delta);
+    const NsPanels pn = ns_panels(ub, delta);
     acc[0] = acc[1] = acc[2] = 0.0;
-    for (int k = 0; k < n; k++) {
+    for (int k = 0; k < pn.n; k++) {
         double lo, hi;
-        ns_panel_bounds(ub, delta, k, &lo, &hi);
+        ns_panel_bounds(ub, delta, pn, k, &lo, &hi);
         ns_panel<DEG>(s, xs, lo, hi, R, acc);
     }
 }
@@ -843,7 +817,7 @@ template <int DEG>
 struct NsIntLds {
     double c[(DEG + 1) * 3][64], ub[64], dl[64];
     double part[3][64];
-    unsigned char own[64];
+    unsigned char own[64], left[64], count[64];   // (at most 30 panels a side)
 };
 
 template <int DEG>
@@ -879,7 +853,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DEG == 3 ? 4
             double C[3], d1[3];
             seg_eval<DEG>(s, ub, C, d1);
             const double dl = ns_delta(C, d1);
-            np = ns_panels(ub, dl);
+            const NsPanels pn = ns_panels(ub, dl);
+            np = pn.n;
+            W.left[lane] = (unsigned char)pn.left;
+            W.count[lane] = (unsigned char)pn.n;
 #pragma unroll
             for (int k = 0; k <= DEG; k++)
 #pragma unroll
@@ -905,7 +882,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DEG == 3 ? 4
                 for (int q = 0; q < 3; q++) s.c4[q] = s.c5[q] = 0.0;
             seg_derivs(s);
             double lo, hi, v[3] = {0.0, 0.0, 0.0};
-            ns_panel_bounds(W.ub[e], W.dl[e], k, &lo, &hi);
+            ns_panel_bounds(W.ub[e], W.dl[e], NsPanels{W.count[e], W.left[e]}, k, &lo, &hi);
             ns_panel<DEG>(s, zero, lo, hi, R, v);
             for (int q = 0; q < 3; q++) W.part[q][lane] = v[q];
             wave_lds_sync();
