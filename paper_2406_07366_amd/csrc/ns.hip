@@ -218,11 +218,16 @@ __global__ __launch_bounds__(64) void k_ns_sort(const int *__restrict__ ncp,
 }
 
 // period index of v (floor(v / L), clamped to +-511) and v wrapped into the
-// box by it; kept consistent so that v = w + L k up to rounding
+// box by it; kept consistent so that v = w + L k up to rounding.  A v so little
+// below a period that the fold rounds to L is 0 of the next one, the cell it is in.
 __device__ __forceinline__ int period_of(double v, double L, double *w) {
     double k = floor(v / L);
     k = k < -511.0 ? -511.0 : (k > 511.0 ? 511.0 : k);
     *w = v - L * k;
+    if (*w >= L && fabs(k) < 511.0) {
+        *w -= L;
+        k += 1.0;
+    }
     return (int)k;
 }
 __device__ __forceinline__ int pack_periods(const int *k) {
