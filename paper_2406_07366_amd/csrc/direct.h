@@ -101,13 +101,16 @@ __device__ __forceinline__ void direct_piece(Piece *out, const double *pos, int 
                                              double L) {
     const int lane = threadIdx.x & 63;
     float hi[3] = {-3.0e38f, -3.0e38f, -3.0e38f}, lo[3] = {-3.0e38f, -3.0e38f, -3.0e38f};
+    bool finite = true;   // (the maxima pass over NaN)
     for (int t = lane; t < nq; t += 64)
 #pragma unroll
         for (int a = 0; a < 3; a++) {
             const float v = (float)pos[3 * t + a];
+            finite = finite && fabsf(v) < 1.0e38f;
             hi[a] = fmaxf(hi[a], v);
             lo[a] = fmaxf(lo[a], -v);
         }
+    const bool all = __ballot(!finite) == 0;
     Piece P;
 #pragma unroll
     for (int a = 0; a < 3; a++) {
@@ -116,6 +119,10 @@ __device__ __forceinline__ void direct_piece(Piece *out, const double *pos, int 
         // target's offset from it: below 1e-6 of the magnitudes
         P.c[a] = 0.5f * (h + l);
         P.e[a] = 0.5f * (h - l) + 1e-6f * (fabsf(h) + fabsf(l) + (float)L);
+        if (!all) {   // its points fold to 0: near every target
+            P.c[a] = 0.0f;
+            P.e[a] = INFINITY;
+        }
     }
     P.q0 = q0;
     P.nq = nq;
