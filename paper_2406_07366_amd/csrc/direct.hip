@@ -276,13 +276,33 @@ void launch_spread_direct(bs_plan_t p) { spread_any(p, nullptr, nullptr); }
 void launch_spread_pairs(bs_plan_t p, const double *base, double *out) { spread_any(p, base, out); }
 
 // Taken where scanning every point per tile and per target costs less than the
-// four launches of the sorts and the second stream (evaluation at 64 nodes
-// 76 -> 41 us, at 2560 nodes on 64^3 98 -> 73): up to 8192 points, and as many
-// point-tile tests as 8192 points have on 128^3.
-constexpr int64_t kDirectPoints = 8192, kDirectTests = (int64_t)1 << 25;
+// four launches of the sorts and the second stream: evaluations of rings of 64 nodes
+// in us, through the sorts and direct,
+//              64 nodes   640       1280      2560      4096      6400
+//   32^3 w 8   76  37     84  47    100  55   138  93   189 151   312 268
+//   64^3 w 8   80  46     85  52     88  57    97  73   109  93   127 130
+//   96^3 w 8  119  82    131  89    131  94   139 108   146 127   155 161
+//   128^3 w 8 149 123    155 134    160 145   168 168   174 198
+//   160^3 w 8 213 196    223 215    226 235   232 271
+//   192^3 w 8 310 312    318 339
+//   128^3 w 12 164 134   173 149    179 162   202 191   213 227
+//   64^3 w 16  94  62    104  75    114  87   134 121   156 169
+//   128^3 w 16 166 157   179 193    189 222   223 278   239 346
+//   160^3 w 16 231 248   250 298
+//   256^3 w 16 745 928   778 1100
+// so up to 8192 points on up to 8192 tiles with up to 2^24 tests of a point against a
+// tile; wide kernels, whose staging leaves few workgroups per CU, up to 4096 tiles
+// and 3 2^20 tests.
+constexpr int64_t kDirectPoints = 8192;
+constexpr int64_t kDirectTiles = 8192, kDirectTests = (int64_t)1 << 24;
+constexpr int64_t kDirectTilesWide = 4096, kDirectTestsWide = (int64_t)3 << 20;
+constexpr int kDirectWide = 13;
 bool direct_path(bs_plan_t p, int64_t Nq) {
     const int64_t nt = (int64_t)p->NT * p->NT * p->NT;
-    return !p->fp32 && p->T == kTile && Nq <= kDirectPoints && nt * Nq <= kDirectTests;
+    const bool wide = p->prm.w >= kDirectWide;
+    return !p->fp32 && p->T == kTile && Nq <= kDirectPoints &&
+           nt <= (wide ? kDirectTilesWide : kDirectTiles) &&
+           nt * Nq <= (wide ? kDirectTestsWide : kDirectTests);
 }
 
 }  // namespace bs

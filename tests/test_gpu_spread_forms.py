@@ -1,7 +1,7 @@
 """The float64 spread's forms on 8^3 tiles (one or four wavefronts per tile, matrix
 cores or vector, the full tiles of a cluster by themselves): the vorticity's Fourier
 coefficients are linear in the filaments, so those of a set are the sums of those
-of ten parts, which take the direct path of small inputs.  Both sum the same float64
+of ten parts, which take other forms or the direct path of small inputs.  Both sum the same float64
 terms in other orders, up to 1e4 of them in a cell of a cluster: 1e-12 of the
 grid's transform, that is, of the coefficients before the division by the
 kernel's, which raises the rounding of the highest ones by up to 1e4 at w = 12.
