@@ -718,6 +718,7 @@ int bs_mlp_loss_grad(bs_mlp_t M, int64_t B, const float *X, const float *T, floa
     if (!M || B <= 0 || !X || !T) return BS_EINVAL;
     if (!loss_dev && !grad_dev) return BS_OK;
     const int blocks = mlp_partials(M, B, X, T);
+    if (hipGetLastError() != hipSuccess) return BS_EDEVICE;
     AdamArgs A{};
     if (grad_dev)
         hipLaunchKernelGGL(k_mlp_reduce<false>, dim3(kRedBlocks + 1), dim3(256), 0, M->stream,
@@ -732,6 +733,7 @@ int bs_mlp_adam_step(bs_mlp_t M, int64_t B, const float *X, const float *T, floa
                      float beta1, float beta2, float eps, float *loss_dev) {
     if (!M || B <= 0 || !X || !T) return BS_EINVAL;
     const int blocks = mlp_partials(M, B, X, T);
+    if (hipGetLastError() != hipSuccess) return BS_EDEVICE;   // no step was taken
     M->step++;
     AdamArgs A;
     A.P = M->P; A.m = M->m; A.v = M->v; A.wf = M->wf; A.bg = M->bg; A.wg = M->wg;
