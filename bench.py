@@ -41,7 +41,8 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
 FP32_VECTOR_TFLOPS = 157.3     # MI355X dense fp32 vector
 FP64_VECTOR_TFLOPS = 78.6
 PAIR_FLOP = 60.0               # per interacting pair (erfc, exp, sqrt, div, cross, fma)
-# stages made of exactly one kernel launch, and the source file of that kernel
+# stages made of exactly one kernel launch, and the source file of that kernel (its
+# counters are quoted while the file and the headers it includes are unchanged)
 SINGLE_KERNEL_STAGES = {"spread": "nufft.hip", "spectral": "nufft.hip", "interp": "nufft.hip",
                         "pairs": "pairs.hip"}
 # the single-kernel stages on the plan's stream (the pair sum runs on the second)

@@ -9,8 +9,9 @@
       --pmc runs (FETCH_SIZE, WRITE_SIZE; KiB per dispatch), each scaled by the
       ratio of the known size of the largest plain device copy in the same
       run to what the same counter reads for it.  The summary records the
-      SHA-1 of the kernel's source file: a reader compares it with the file as
-      it stands and ignores the figure once the source has changed.
+      SHA-1 of the kernel's source file and of the headers beside it that it
+      includes, directly or through others: a reader compares it with the files
+      as they stand and ignores the figure once any of them has changed.
 
 The bench reads `traffic_bytes_per_launch` and `source_sha1` back from the
 pmc summary (see read_traffic).
@@ -19,6 +20,7 @@ from __future__ import annotations
 
 import csv
 import hashlib
+import os
 import re
 import sys
 
@@ -52,9 +54,27 @@ def _per_dispatch(path, counter):
     return list(out.values())
 
 
+def sources_of(path):
+    """A source file and the headers beside it that it includes, directly or
+    through others, in the order of their first inclusion."""
+    out, todo = [], [os.path.abspath(path)]
+    while todo:
+        p = todo.pop(0)
+        if p in out or not os.path.exists(p):
+            continue
+        out.append(p)
+        with open(p) as f:
+            names = re.findall(r'^\s*#\s*include\s+"([^"]+)"', f.read(), re.M)
+        todo += [os.path.join(os.path.dirname(p), n) for n in names]
+    return out
+
+
 def sha1_of(path):
-    with open(path, "rb") as f:
-        return hashlib.sha1(f.read()).hexdigest()
+    h = hashlib.sha1()
+    for p in sources_of(path):
+        with open(p, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def pmc(regex, fetch_csv, write_csv, copy_bytes, source, out_path, command):
