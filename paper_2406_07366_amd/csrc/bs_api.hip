@@ -399,7 +399,7 @@ int bs_plan(const bs_params *p, void *hip_stream, bs_plan_t *out) {
     // pruned transforms: twiddles exp(-+2 pi i k / n), k < n, from float64
     if (P->pruned) {
         P->fft_ops = pruned_ops(P->n, P->fp32);
-        pruned_batches(P->n, cs, &P->fft_rb, &P->fft_kb, &P->fft_kz);
+        P->fft_kz = pruned_z_batch(P->n, cs);
         // (A, 3 n^2 (K + 1) values, K + 1 <= n / 2, fits the spectrum's 3 n^2 (n / 2 + 1))
         if ((rc = ensure<char>(P, P->fft_tw, 2 * n * cs))) return fail(rc);
         // [n] exp(-2 pi i k / n), then [n] exp(+2 pi i k / n)

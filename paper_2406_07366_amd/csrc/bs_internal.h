@@ -84,7 +84,7 @@ struct bs_plan_s {
     bs::DBuf fftwork;
     bool pruned = false;
     const bs::FftOps *fft_ops = nullptr;
-    int fft_rb = 1, fft_kb = 1, fft_kz = 1;
+    int fft_kz = 1;
     bs::DBuf fft_tw;
 
     // short-range cell lists: nodes (and float32 points) in nc^3 cells, points
@@ -235,7 +235,7 @@ const FftOps *mixed_ops_a(int n);
 const FftOps *mixed_ops_b(int n);
 const FftOps *mixed_ops_c(int n);
 const FftOps *mixed_ops_d(int n);
-void pruned_batches(int n, size_t csize, int *rb, int *kb, int *kz);
+int pruned_z_batch(int n, size_t csize);
 void pruned_forward(bs_plan_t p);
 void pruned_spectral_op(bs_plan_t p, int psi);
 void pruned_inverse(bs_plan_t p);

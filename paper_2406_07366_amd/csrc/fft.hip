@@ -1,6 +1,8 @@
 // Pruned transforms: which grids they serve, their batch sizes and dispatch,
 // and the instantiations for the powers of two (the other sizes are in
 // fft_mixed_*.hip, split so that they compile side by side).
+#include <algorithm>
+
 #include "fft_kernels.h"
 
 namespace bs {
@@ -52,35 +54,22 @@ void pruned_spectral_op(bs_plan_t p, int psi) { p->fft_ops->spectral(p, psi); }
 void pruned_inverse(bs_plan_t p) { p->fft_ops->inverse(p); }
 
 
-// Batch sizes: sequences per workgroup for the x and y passes (rb = kb, a
-// power of two) and columns for the z pass (kz, times 3 components): about
-// 256 threads of one item each (128 in float64), with the LDS buffer and its
-// padded pitch within kFftLds.
-static int pow2_floor(int v) {
-    int p = 1;
-    while (2 * p <= v) p *= 2;
-    return p;
-}
-
-void pruned_batches(int n, size_t csize, int *rb, int *kb, int *kz) {
+// Columns per workgroup of the z pass on planes (times 3 components): 3 kz
+// sequences of mnj items, about 256 threads (128 in float64) of ipt items each and
+// at most kFftMaxThreads, with 2 twiddle tables and 3 kz + 1 columns in the LDS.
+int pruned_z_batch(int n, size_t csize) {
     const int mnj = fft_max_nj(n), ipt = z_ipt(n, (int)csize);
     const int threads = csize > 8 ? 128 : 256;
-    int b = threads / mnj;
-    // twiddles (n, 2n in the z pass) + rows of about n + n/16 + 1 entries
     const int lds = (int)(kFftLds / (csize * (n + n / 16 + 1))) - 2;
-    b = b < lds ? b : lds;
-    b = pow2_floor(b < 1 ? 1 : b);
-    *rb = b;
-    *kb = b;
-    // z pass: 3 kz sequences of mnj items, ipt items per thread, at most
-    // kFftMaxThreads threads; LDS 2 twiddle tables + 3 kz + 1 columns
+    const int b = std::max(1, std::min(threads / mnj, lds));
+    int p2 = 1;   // the power of two below
+    while (2 * p2 <= b) p2 *= 2;
     const size_t zlds = ipt > 1 ? kFftLdsZ : kFftLds;
-    int z = ipt > 1 ? kFftMaxThreads * ipt / (3 * mnj) : b / 3;
-    z = z < 1 ? 1 : z;
+    int z = std::max(1, ipt > 1 ? kFftMaxThreads * ipt / (3 * mnj) : p2 / 3);
     while (z > 1 && ((size_t)(2 * n + n * (3 * z + 1)) * csize > zlds ||
                      ceil_div(3 * z * mnj, ipt) > kFftMaxThreads))
         z--;
-    *kz = z;
+    return z;
 }
 
 }  // namespace bs
