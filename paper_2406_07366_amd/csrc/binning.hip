@@ -226,11 +226,20 @@ __global__ void k_scatter_all(SortSet S) {
 // may be moving entries meanwhile, but only within their bins: a position's bin
 // can be read at any time.
 constexpr int kSortLds = 1024;
+// entries per wavefront of the per-bin sort: 16 to 64 on small inputs, up to 256 where
+// that leaves more wavefronts than the chip holds (eight per SIMD).  A wavefront's
+// last bin reaches beyond its share, so 16 saves a round of counting (1134 nodes
+// 7.7 -> 6.6 us), but not where it only makes more wavefronts (1e5 nodes 9.4 -> 12.9)
+constexpr int kSortShare = 16, kSortFew = 512, kSortWaves = 8192, kSortShareMax = 256;
+static_assert(kSortShareMax <= kSortLds && 256 <= kSortLds, "a share, or the digits, in LDS");
 
-// LDS of the per-bin sort: the staged entries, or the digits' counts
+// LDS of the per-bin sort: the staged entries (or the digits' counts) and, of those in
+// the share, where their bin begins and ends among them
 struct SortLds {
     int v[kSortLds];
+    int range[kSortShareMax];
 };
+static_assert(kSortLds < 1 << 15, "both ends in an int");
 
 // n distinct entries below 2^nbits at a, in ascending order, by one wavefront:
 // stable passes over eight bits at a time between a and t (n values of scratch).
@@ -296,13 +305,6 @@ __device__ __forceinline__ void radix_sort_bin(int *a, int *t, int n, int nbits,
     }
 }
 
-// where the first bin that begins at or after position v of the entries begins
-__device__ __forceinline__ int sort_bound(const SortSet &S, int a, int v) {
-    if (v >= S.nitems[a]) return S.nitems[a];
-    const int b = S.key[a][S.perm[a][v]], s = S.start[a][b];
-    return s == v ? v : S.start[a][b + 1];
-}
-
 __global__ __launch_bounds__(64) void k_sort_all(SortSet S) {
     int w = blockIdx.x, a = 0;
     if (w >= S.nwave[0]) { w -= S.nwave[0]; a = 1; }
@@ -317,28 +319,58 @@ __global__ __launch_bounds__(64) void k_sort_all(SortSet S) {
         if (lane == 0) cnt[0] = fill[0] = 0;
         return;
     }
-    const int s0 = sort_bound(S, a, w * S.share[a]);
-    int e0 = sort_bound(S, a, (w + 1) * S.share[a]);
-    if (s0 >= e0) return;
+    // the share's entries and their bins, up to four per lane (three round trips to
+    // memory; with its ends looked up first, six, 1e4 nodes took 7.4 us instead of 5.8)
+    constexpr int U = kSortShareMax / 64;
+    const int share = S.share[a], v0 = w * share, v1 = min(v0 + share, S.nitems[a]);
+    int x[U], b[U], lo[U], hi[U];
+#pragma unroll
+    for (int u = 0; u < U; u++)
+        if (64 * u < share) x[u] = perm[min(v0 + 64 * u + lane, v1 - 1)];
+#pragma unroll
+    for (int u = 0; u < U; u++)
+        if (64 * u < share) b[u] = key[x[u]];
+    int bl = 0, lol = 0, e0 = 0;   // the bin of the share's last entry, its range
+#pragma unroll
+    for (int u = 0; u < U; u++)
+        if (64 * u < share) {
+            lo[u] = start[b[u]];
+            hi[u] = start[b[u] + 1];
+            bl = b[u]; lol = lo[u]; e0 = hi[u];
+        }
+    bl = __shfl(bl, 63);
+    lol = __shfl(lol, 63);
+    e0 = __shfl(e0, 63);
+    const int first = __shfl(lo[0], 0), s0 = first == v0 ? v0 : __shfl(hi[0], 0);
+    if (s0 >= v1) return;
     if (e0 - s0 > kSortLds) {
-        const int b = key[perm[e0 - 1]], s = start[b];
-        if (lane == 0) cnt[b] = fill[b] = 0;
+        if (lane == 0) cnt[bl] = fill[bl] = 0;
         const int nbits = 32 - __clz(S.nitems[a] - 1);
-        radix_sort_bin(perm + s, S.tmp[a] + s, e0 - s, nbits, L);
-        e0 = s;   // at most a share is left
+        radix_sort_bin(perm + lol, S.tmp[a] + lol, e0 - lol, nbits, L);
+        e0 = lol;   // at most a share is left
         __syncthreads();   // the LDS is free
     }
-    const int total = e0 - s0;
-    for (int i = lane; i < total; i += 64) L.v[i] = perm[s0 + i];
+    // beyond m - s0, the last bin's entries outside the share
+    const int m = min(e0, v1), total = e0 - s0;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int i = v0 + 64 * u + lane;
+        if (64 * u < share && i >= s0 && i < m) {
+            L.v[i - s0] = x[u];
+            L.range[i - s0] = (lo[u] - s0) | (hi[u] - s0) << 16;
+            cnt[b[u]] = 0;
+            fill[b[u]] = 0;
+        }
+    }
+    for (int i = v1 + lane; i < e0; i += 64) L.v[i - s0] = perm[i];
     wave_lds_sync();
     for (int i = lane; i < total; i += 64) {
-        const int x = L.v[i], b = key[x], lo = start[b] - s0, hi = start[b + 1] - s0;
-        cnt[b] = 0;
-        fill[b] = 0;
-        int r = lo;
+        const int y = L.v[i], g = i < m - s0 ? L.range[i] : (lol - s0) | total << 16;
+        const int l = g & 0xffff, h = g >> 16;
+        int r = l;
 #pragma unroll 8
-        for (int j = lo; j < hi; j++) r += (L.v[j] < x);
-        perm[s0 + r] = x;
+        for (int j = l; j < h; j++) r += (L.v[j] < y);
+        perm[s0 + r] = y;
     }
 }
 
@@ -423,10 +455,6 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_all(int M, int w, int Q
     for (int i = threadIdx.x; i < nt * w; i += kGatherBlock) ker[i] = lk[i];
 }
 
-// entries per wavefront of the per-bin sort: 64 while that leaves fewer wavefronts
-// than the chip holds (eight per SIMD), 256 at most
-constexpr int kSortWaves = 8192, kSortShare = 64, kSortShareMax = 256;
-static_assert(kSortShareMax <= kSortLds && 256 <= kSortLds, "a share, or the digits, in LDS");
 // arrays of at most this many bins are scanned by one workgroup each (one
 // launch, 5.0 us at 14112 bins and 7.4 at 21312, but 240 at the 98^3 node cells of a
 // loose tolerance on 256^3; the three launches of the blocked scan take 14 us)
@@ -451,7 +479,9 @@ void build_bins(bs_plan_t p) {
     S.tmp[0] = (int *)p->sp_q.p; S.tmp[1] = (int *)p->pq_pos.p; S.tmp[2] = (int *)p->nd_rec.p;
     for (int a = 0; a < 3; a++) {
         int sh = kSortShare;
-        while (sh < kSortShareMax && (int64_t)sh * kSortWaves < S.nitems[a]) sh *= 2;
+        while (sh < kSortShareMax &&
+               (int64_t)sh * (sh < 64 ? kSortFew : kSortWaves) < S.nitems[a])
+            sh *= 2;
         S.share[a] = sh;
         S.nwave[a] = S.nbins[a] == 1 ? 1 : ceil_div(S.nitems[a], sh);
     }
