@@ -105,6 +105,9 @@ struct bs_plan_s {
     int order = 4;          // spline order: 4 cubic, 6 quintic
     std::vector<int64_t> off_host;
     bool have_filaments = false;
+    // one allocation for the buffers that the filaments' sizes decide (those below but
+    // d_shift, d_status, scan_tmp, red_tmp and rk_k; d_piece and d_pfirst above)
+    bs::DBuf points;
     bs::DBuf d_off, d_fil, d_gamma;            // int32 [nfil+1], int32 [N], f64 [nfil]
     bs::DBuf d_x;                              // f64 [N][3] private copy of nodes
     bs::DBuf d_xn;                             // f64 [N][3] end node of segment j in
