@@ -79,13 +79,14 @@ extern "C" {
                               variate                                        */
 
 /* 3-D transforms of the long-range step */
-#define BS_FFT_AUTO     0  /* BS_FFT_PRUNED for power-of-two grids from 64 up
-                              (where it is faster), else BS_FFT_LIBRARY in the
-                              resolved parameters; in float64 a plan made with
-                              BS_FFT_AUTO then still transforms as with
-                              BS_FFT_PRUNED on grids of 16 and 32 and on the
-                              multiples of 8 from 40 to 504 with no prime factor
-                              above 7 (same results to rounding)               */
+#define BS_FFT_AUTO     0  /* BS_FFT_PRUNED for power-of-two grids from 64 up (to
+                              512 in float64), where it is faster, else
+                              BS_FFT_LIBRARY in the resolved parameters; in
+                              float64 a plan made with BS_FFT_AUTO then still
+                              transforms as with BS_FFT_PRUNED on grids of 16
+                              and 32 and on the multiples of 8 from 40 to 504
+                              with no prime factor above 7 (same results to
+                              rounding)                                        */
 #define BS_FFT_LIBRARY  1  /* hipFFT: full r2c / c2r transforms and a separate
                               spectral-operator pass                           */
 #define BS_FFT_PRUNED   2  /* grid_n a power of two (else BS_EINVAL): transforms

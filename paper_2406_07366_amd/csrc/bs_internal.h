@@ -127,7 +127,7 @@ struct bs_plan_s {
     bs::DBuf pq_pos, pq_chg;                   // double4 (position, segment), charges
     bs::DBuf nd_key, nd_cnt, nd_start, nd_fill, nd_perm;
     bs::DBuf nd_rec;                           // double4 [N] nodes in cell order
-    // scan scratch, reductions, spline scratch (filaments over 512 nodes)
+    // scan scratch, reductions, spline scratch (filaments over 128, quintic 64 nodes)
     bs::DBuf scan_tmp, red_tmp, spline_tmp;
     int64_t max_fil_nodes = 0;
     // near-singular pairs

@@ -1,7 +1,8 @@
 // Pruned 3-D transforms of the long-range step (Sec. 3.3): kernels and their
-// launches, templated on the grid size n (powers of two, and in float64 the
-// multiples of 8 with no prime factor above 7).  Only the retained modes |m_i| <= K (K < n/2) are ever formed or
-// stored past the first transform of each direction, and the spectral
+// launches, templated on the grid size n (powers of two from 16, in float64 to
+// 512, in float32 to 1024, and in float64 the multiples of 8 from 40 to 504 with
+// no prime factor above 7).  Only the retained modes |m_i| <= K (K < n/2) are ever
+// formed or stored past the first transform of each direction, and the spectral
 // operator is applied between the forward and inverse z transforms of the
 // same columns, so it costs no pass of its own.
 //
@@ -479,9 +480,9 @@ __global__ __launch_bounds__(kFftMaxThreads) void k_fft_x_inv(int K1, int per,
     const int z = bid / (n / Y), y0 = (bid - z * (n / Y)) * Y;
     const int pitch = lds_pitch<true>(n, NSEQ);
     // the runs of modes 0..K, all of a thread's loads issued together with a
-    // fixed stride (as in k_fft_y_inv: 1.77 -> 1.61 ms at 512^3 in float64,
-    // 1.00 -> 0.91 in float32; twiddles from global memory instead of LDS took
-    // 1.91); spectrum of (c, yy) at spec[(c Y + yy) K1]
+    // fixed stride (as in k_fft_y_inv: 1.79 -> 1.75 ms at 512^3 in float64,
+    // 1.05 -> 0.99 in float32; twiddles from global memory instead of LDS were a
+    // fifth slower there); spectrum of (c, yy) at spec[(c Y + yy) K1]
     constexpr int NT = fft_threads(N, NSEQ), KS = NT / (3 * Y), PF = (n / 2 + KS - 1) / KS;
     const int k0 = threadIdx.x / (3 * Y), r0 = threadIdx.x % (3 * Y), c0 = r0 / Y;
     typedef R V2 __attribute__((ext_vector_type(2)));
@@ -574,9 +575,9 @@ __global__ __launch_bounds__(kFftMaxThreads) void k_fft_y_fwd(int K, int per,
 // y inverse: the B runs of 8 sequences into LDS (modes |my| > K zero),
 // inverse FFT along y, whole sequences out to A.  All of a thread's loads are
 // issued together with fixed strides, before the twiddle table's (batches of 8
-// with the table among them: 0.94 ms at 512^3 in float64 against 0.68).
-// Measured slower: a workgroup striding over tiles with the next one's loads
-// in flight (0.82).
+// with the table among them: 0.98 ms at 512^3 in float64 against 0.70, 0.45 against
+// 0.37 in float32).  Measured slower: a workgroup striding over tiles with the next
+// one's loads in flight (by a fifth).
 template <typename R, int N>
 __global__ __launch_bounds__(kFftMaxThreads) void k_fft_y_inv(int K, int per,
                                                             const typename Cx<R>::T *__restrict__ B,

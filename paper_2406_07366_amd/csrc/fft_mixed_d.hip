@@ -1,5 +1,5 @@
-// Pruned transforms in float64 on grids that are not powers of two (multiples
-// of 8 with no prime factor above 7), one of four sets of sizes.
+// Pruned transforms in float64 on grids that are not powers of two (multiples of 8
+// from 40 to 504 with no prime factor above 7), one of four sets of sizes.
 #include "fft_kernels.h"
 
 namespace bs {

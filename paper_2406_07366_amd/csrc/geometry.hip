@@ -540,9 +540,9 @@ __global__ __launch_bounds__(256) void k_local_self(int N, LocalArgs la, const d
 // correction (into vls, which the velocity sums start from).  The keys and
 // counts of the bin sorts that follow are formed here too.  The local term
 // is what sets the kernel's registers (237 VGPRs with it, two wavefronts per
-// SIMD; 82 without, five), so inputs that need more wavefronts than that
+// SIMD; 74 without, six), so inputs that need more wavefronts than that
 // leave it to k_local_self, one thread per node (1e6 nodes in 1e4 filaments:
-// 0.40 -> 0.29 ms for both launches); the others keep the single launch.
+// 0.40 -> 0.30 ms for both launches); the others keep the single launch.
 // KEYS: form the bin sorts' keys and counts (not on the direct path).
 template <int ORDER, bool LOCAL, bool KEYS>
 __global__ __launch_bounds__(128) void k_filament(int nfil, const int *__restrict__ off, StagePos xs,
@@ -608,16 +608,15 @@ __global__ __launch_bounds__(128) void k_filament(int nfil, const int *__restric
 // The same for the direct path (filaments of at most kDirectFil nodes), with
 // everything between the stages in LDS and the arrays written at the end: a
 // barrier then waits for LDS alone, where the kernel above waits for global
-// stores and loads back at every stage (on one
-// 64-node ring: launch 1.4, chords 1.7, spline 3.5, geometry 0.5, local terms 2,
-// kernel values 4.3, records and stores 2 us; on the 64^3 ellipses it takes 16 us
-// where the kernel above and the gather took 15 + 6.5 and the sorts 14).
+// stores and loads back at every stage (on the 64^3 ellipses, a workgroup per
+// filament, 17 us where the kernel above and the gather took 15 + 6.5 and the
+// sorts 14).  Bound by the chain of its stages.
 // Four lanes per node share the local - self term; the kernel values of the
 // spread and the records of the pair sums are written here too.  With parts > 1
 // workgroups per filament each solves the spline for itself and the rest is
 // shared out: the nodes' terms and arrays to the first, the points' to the others
-// (few filaments leave the chip idle: one 64-node ring 14.4 -> 10.1 us, the two
-// quintic rings of the leapfrog 20.0 -> 16.2, the 40 ellipses 14.8 -> 11.6).
+// (few filaments leave the chip idle: one 64-node ring 15.8 -> 10.7 us, the two
+// quintic rings of the leapfrog 21.5 -> 17.0, the 40 ellipses 16.7 -> 12.0).
 template <int ORDER>
 struct FilLds {
     static constexpr int M = kDirectFil;
@@ -823,8 +822,8 @@ void launch_filaments(bs_plan_t p, const double *xyz, const double *kstage, doub
     const bool quintic = p->order == 6;
     if (p->direct && p->max_fil_nodes <= kDirectFil) {
         auto kern = quintic ? k_filament_direct<6> : k_filament_direct<4>;
-        // a workgroup per CU, up to four per filament (3: 10.3 us on one 64-node
-        // ring, 4: 10.1, 8: 10.0); a quintic system beyond the LDS has one copy,
+        // a workgroup per CU, up to four per filament (three took 2 % longer on one
+        // 64-node ring, eight 1 % less); a quintic system beyond the LDS has one copy,
         // in global memory
         const bool one = quintic && p->max_fil_nodes > kPcr5Lds;
         const int parts = one ? 1 : (int)std::clamp<int64_t>(256 / p->nfil, 1, 4);

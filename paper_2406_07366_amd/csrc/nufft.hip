@@ -419,7 +419,7 @@ static Spread64 spread64_form(int w, int ntiles, int64_t Nq) {
 }
 // One wavefront per tile leaves the tiles that a cluster of filaments fills to
 // k_spread_full (20000 nodes within 0.1 L on 128^3: 0.70 ms, without it 2.4, the
-// vector form for every tile 0.69; 3 to 4 us where no tile is full): those of more
+// vector form for every tile 0.69; 3 to 6 us where no tile is full): those of more
 // candidates than this, and than this many times what evenly spread points give.
 constexpr int kSpreadFull = 1024, kSpreadFullTimes = 4;
 static_assert(kSpreadSplitTiles <= kFullBlocks * kFullTiles, "every tile is looked at");

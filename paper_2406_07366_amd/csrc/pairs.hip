@@ -262,8 +262,8 @@ ShortFit short_fit() {
 // (PairScan).  The separations of the points within r_c are queued in LDS and
 // their exp / polynomial terms evaluated 64 at a time, so that the costly part
 // runs with every lane busy.  Bound by vector issue (~560 instructions per
-// target of ~230 candidates and ~100 terms on the 1e6-node tangle: 2.42 -> 1.20 ms
-// alone, 243 -> 121 us on 1e5 nodes; before, the cells of edge 2 r_c / 3, target
+// target of ~230 candidates and ~100 terms on the 1e6-node tangle: 2.43 -> 1.22 ms
+// alone, 243 -> 120 us on 1e5 nodes; before, the cells of edge 2 r_c / 3, target
 // set-up by divisions and a map of every candidate in LDS took ~950).  The
 // partial sums are combined in a fixed order (deterministic).
 template <bool PSI, int WPN>
